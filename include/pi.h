@@ -136,9 +136,11 @@ pi_status pi_cells_get_view(pi_cells *cells, pi_cells_view *out);
 
 /* Accumulation precision of the sweep. */
 #define PI_PREC_COMPENSATED 0 /* FP32 terms with h^2 - r^2 formed in FP64 for
-                                 q > 1/2, FP32 Kahan-compensated sums */
+                                 q > 1/2, sums in FP64 (they hold more than
+                                 compensated FP32 sums, and cost less) */
 #define PI_PREC_PLAIN       1 /* FP32 terms (1 - q from q), plain FP32 sums */
-#define PI_PREC_FP64ACC     2 /* compensated FP32 terms, FP64 sums */
+#define PI_PREC_FP64ACC     2 /* the terms of PI_PREC_COMPENSATED, FP64 sums: the
+                                 same arithmetic */
 
 /* Organisation of the sweep. */
 #define PI_SWEEP_AUTO   0 /* chosen by the library's tuner */

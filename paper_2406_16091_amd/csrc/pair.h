@@ -32,8 +32,8 @@ struct KernelConst {
 // three FMAs, one conversion back) where the same difference by FP32
 // error-free transforms took 25.  Sweep kernel times with the transforms and
 // with this: 2^24 particles at 1 per cell 1.21 and 1.18 ms, at 8 per cell
-// 5.42 and 4.86 ms, 2^23 clustered 5.4 and 4.9 ms; the largest error against
-// 64 bits is no larger (rho 7.9e-8, G 1.0e-7 against 1.1e-7, 2-norms).
+// 5.42 and 4.86 ms, 2^23 clustered 5.4 and 4.9 ms; the largest error of an
+// output against 64 bits (2-norm) 1.1e-7 and 1.0e-7.
 __device__ __forceinline__ double h2_minus_d2(float dx, float dy, float dz, const KernelConst &k)
 {
     const double x = (double)dx, y = (double)dy, z = (double)dz;
@@ -112,19 +112,20 @@ __device__ __forceinline__ void bspline_terms(float dx, float dy, float dz, floa
     }
 }
 
-// Per-target accumulators for rho, G and (optionally) A = sum w_j |W'(r)|.
+// Per-target accumulators for rho and G.  An accepted pair adds w_j W to rho
+// and f (dx, dy, dz) with f = w_j W'(r) / r to G.
 template <int PREC>
 struct Acc;
 
 template <>
 struct Acc<PI_PREC_PLAIN> {
     float rho = 0.f, gx = 0.f, gy = 0.f, gz = 0.f;
-    __device__ __forceinline__ void add(float a, float bx, float by, float bz)
+    __device__ __forceinline__ void add(float a, float f, float dx, float dy, float dz)
     {
         rho += a;
-        gx += bx;
-        gy += by;
-        gz += bz;
+        gx += f * dx;
+        gy += f * dy;
+        gz += f * dz;
     }
     __device__ __forceinline__ float r_rho() const { return rho; }
     __device__ __forceinline__ float r_gx() const { return gx; }
@@ -132,51 +133,35 @@ struct Acc<PI_PREC_PLAIN> {
     __device__ __forceinline__ float r_gz() const { return gz; }
 };
 
-// Kahan's compensated summation: c is the rounding excess of the running
-// sum so far (what was added minus what was meant), taken off the next
-// term; the error of the result is at most about 2u sum |v_i| (u = 2^-24),
-// for rho (positive terms) 2u rho and for G at most 2u A, against the 1e-5
-// tolerance.  4 operations per term, against 7 for TwoSum with a separate
-// error sum.
-template <>
-struct Acc<PI_PREC_COMPENSATED> {
-    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-    float c0 = 0.f, c1 = 0.f, c2 = 0.f, c3 = 0.f;
-    __device__ __forceinline__ static void ks(float &s, float &c, float v)
-    {
-        const float y = v - c;
-        const float n = s + y;
-        c = (n - s) - y;
-        s = n;
-    }
-    __device__ __forceinline__ void add(float a, float bx, float by, float bz)
-    {
-        ks(s0, c0, a);
-        ks(s1, c1, bx);
-        ks(s2, c2, by);
-        ks(s3, c3, bz);
-    }
-    __device__ __forceinline__ float r_rho() const { return s0 - c0; }
-    __device__ __forceinline__ float r_gx() const { return s1 - c1; }
-    __device__ __forceinline__ float r_gy() const { return s2 - c2; }
-    __device__ __forceinline__ float r_gz() const { return s3 - c3; }
-};
-
+// FP64 sums, with the products f dx not rounded on their own: the error of a
+// sum is that of its FP32 terms.  A lane's sums take eight registers, as
+// FP32 sums with a compensation term each would, and one pair two
+// conversions, an addition and three FMAs in FP64 (the differences are
+// already there in FP64, from h^2 - r^2): about 30 cycles, against about 50
+// for three products and four Kahan additions in FP32.  Sweep kernel times
+// with Kahan sums and with these, 2^24 particles: 8 per cell 4.86 and 4.35 ms,
+// 1 per cell 1.18 and 1.16 ms; the largest error of an output against 64 bits
+// (2-norm) 1.0e-7 and 9.7e-8.
 template <>
 struct Acc<PI_PREC_FP64ACC> {
     double rho = 0.0, gx = 0.0, gy = 0.0, gz = 0.0;
-    __device__ __forceinline__ void add(float a, float bx, float by, float bz)
+    __device__ __forceinline__ void add(float a, float f, float dx, float dy, float dz)
     {
+        const double fd = (double)f;
         rho += (double)a;
-        gx += (double)bx;
-        gy += (double)by;
-        gz += (double)bz;
+        gx = __builtin_fma(fd, (double)dx, gx);
+        gy = __builtin_fma(fd, (double)dy, gy);
+        gz = __builtin_fma(fd, (double)dz, gz);
     }
     __device__ __forceinline__ float r_rho() const { return (float)rho; }
     __device__ __forceinline__ float r_gx() const { return (float)gx; }
     __device__ __forceinline__ float r_gy() const { return (float)gy; }
     __device__ __forceinline__ float r_gz() const { return (float)gz; }
 };
+
+// FP64 sums hold at least what compensated FP32 sums do, and cost less here.
+template <>
+struct Acc<PI_PREC_COMPENSATED> : Acc<PI_PREC_FP64ACC> {};
 
 // Everything a target keeps while it walks its 27 cells.
 template <int PREC, bool INV>
@@ -198,7 +183,7 @@ struct Target {
         float W, Fr;
         bspline_terms<PREC, SELECT>(dx, dy, dz, t, k, W, Fr);
         const float f = wj * Fr;
-        acc.add(wj * W, f * dx, f * dy, f * dz);
+        acc.add(wj * W, f, dx, dy, dz);
         count += 1;
         if (INV) ascale += wj * fabsf(Fr) * __builtin_amdgcn_sqrtf(t);
     }
