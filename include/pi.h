@@ -376,13 +376,13 @@ pi_status pi_sync(pi_ctx *ctx, pi_cells *cells, pi_stream stream);
  * timed runs (a candidate already 1.5x slower than the best so far stops
  * after one), and waits for the stream.  In
  * PI_TUNE_STATIC mode (or with PI_AUTOTUNE=off in the environment) AUTO uses
- * a fixed rule on the mean occupancy instead: the 6x6x6 sub-box while its
- * staged halo is expected to fit in LDS (mean + 6 standard deviations of a
- * Poisson count, up to about 1.2 particles per cell), then 4x4x4 (up to
- * about 6), then no LDS.  The same fit test picks the tile of PI_SWEEP_PENCIL
- * and PI_SWEEP_SUBBOX when tile[] is zero; PI_SWEEP_CELL with tile[] zero
- * takes every cell (one per workgroup) from 32 particles per cell on, else
- * the cells holding 32 or more with the no-LDS walk for the rest.
+ * a fixed rule on the mean occupancy instead: the largest of nine sub-boxes
+ * (6x6x6 down to 3x2x2 cells) whose staged halo is expected to fit in LDS (mean
+ * + 6 standard deviations of a Poisson count), up to about 15 particles per
+ * cell, then no LDS.  The same rule picks the tile of PI_SWEEP_SUBBOX, and the
+ * same fit test that of PI_SWEEP_PENCIL, when tile[] is zero; PI_SWEEP_CELL with
+ * tile[] zero takes every cell (one per workgroup) from 32 particles per cell
+ * on, else the cells holding 32 or more with the no-LDS walk for the rest.
  */
 #define PI_TUNE_STATIC 0
 #define PI_TUNE_TIMED  1

@@ -18,6 +18,8 @@ struct KernelConst {
     float sig_h2;       // sigma / h^2        (W'(r)/r = sig_h2 (18 q - 12) for q <= 1/2)
     float six_sig_h;    // 6 sigma / h        (W'(r)   = -six_sig_h (1-q)^2 for q > 1/2)
     float w;            // cell width
+    float inv_w;        // 1 / w
+    float rc2_cells;    // (rc / w)^2
 };
 
 // h^2 - (dx^2 + dy^2 + dz^2) in FP64, which the vector units issue at the rate
@@ -63,6 +65,26 @@ __device__ __forceinline__ float sq_dist(float dx, float dy, float dz)
     return __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
 }
 
+// c ? a : b with the lane mask of c in an SGPR pair.  Two selects in a row in
+// the short encoding, which reads the mask from VCC, cost about 30 cycles more
+// than the two selects (measured: 43 cycles for a compare and two selects,
+// 12 with the long encoding).
+__device__ __forceinline__ float lane_select(uint64_t c, float a, float b)
+{
+    float r;
+    asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(b), "v"(a), "s"(c));
+    return r;
+}
+
+// v + 1 in the lanes of c.
+__device__ __forceinline__ int32_t lane_add(uint64_t c, int32_t v)
+{
+    int32_t r;
+    uint64_t carry;
+    asm("v_addc_co_u32_e64 %0, %1, %2, 0, %3" : "=v"(r), "=s"(carry) : "v"(v), "s"(c));
+    return r;
+}
+
 // Kernel value W(r) and W'(r)/r of an accepted pair.  With SELECT both
 // pieces of the spline are evaluated and one is chosen, with the same
 // values as the branch: where a wavefront evaluates queued pairs together it
@@ -88,9 +110,9 @@ __device__ __forceinline__ void bspline_terms(float dx, float dy, float dz, floa
         const float omq2 = omq * omq;
         const float w_out = k.two_sigma * omq2 * omq;
         const float f_out = -k.six_sig_h * omq2 * __builtin_amdgcn_rsqf(t);
-        const bool inner = t <= k.hh_quarter;
-        W = inner ? w_in : w_out;
-        Fr = inner ? f_in : f_out;
+        const uint64_t inner = __builtin_amdgcn_ballot_w64(t <= k.hh_quarter);
+        W = lane_select(inner, w_in, w_out);
+        Fr = lane_select(inner, f_in, f_out);
         return;
     }
     if (t <= k.hh_quarter) {
@@ -177,6 +199,23 @@ struct Target {
         if (t < k.hi && inside_cutoff(dx, dy, dz, t, k)) accept(dx, dy, dz, t, wj, k);
     }
 
+    // The same for a wavefront that evaluates queued pairs together: every lane
+    // runs, and a lane whose `ok` is false adds zeros, which change no sum (its
+    // differences must be finite).  One straight piece of code: accumulators
+    // that a branch carries cost a register copy each per round.
+    __device__ __forceinline__ void pair_if(bool ok, float dx, float dy, float dz, float t, float wj,
+                                            const KernelConst &k)
+    {
+        float W, Fr;
+        bspline_terms<PREC, true>(dx, dy, dz, t, k, W, Fr);
+        // (the products, not a factor: either may be infinite)
+        const uint64_t in = __builtin_amdgcn_ballot_w64(ok);
+        const float a = lane_select(in, wj * W, 0.0f), f = lane_select(in, wj * Fr, 0.0f);
+        acc.add(a, f, dx, dy, dz);
+        count = lane_add(in, count);
+        if (INV) ascale += -f * __builtin_amdgcn_sqrtf(t); // (Fr <= 0)
+    }
+
     template <bool SELECT = false>
     __device__ __forceinline__ void accept(float dx, float dy, float dz, float t, float wj, const KernelConst &k)
     {
@@ -185,6 +224,6 @@ struct Target {
         const float f = wj * Fr;
         acc.add(wj * W, f, dx, dy, dz);
         count += 1;
-        if (INV) ascale += wj * fabsf(Fr) * __builtin_amdgcn_sqrtf(t);
+        if (INV) ascale += -f * __builtin_amdgcn_sqrtf(t); // w_j |W'|: Fr <= 0
     }
 };

@@ -17,6 +17,9 @@
 namespace {
 
 constexpr int kBlock = 256;
+constexpr int kMaskQ = 4; // chunk masks a lane of a sub-box tile can hold
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef _Float16 v4h __attribute__((ext_vector_type(4)));
 
 struct SweepArgs {
     const int32_t *off;
@@ -346,6 +349,24 @@ __global__ __launch_bounds__(kBlock) void k_sweep_stream(SweepArgs a)
     }
 }
 
+// x as the sum of two FP16 numbers: the leading one (11 bits of x) in the low
+// half of the word, the rest (its leading 11 bits) in the high half.
+__device__ __forceinline__ uint32_t split_f16(float x)
+{
+    const float hi = __uint_as_float(__float_as_uint(x) & 0xffffe000u);
+    return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(hi, x - hi));
+}
+
+// Position of the lowest set bit of m (some position below 64 if there is none).
+__device__ __forceinline__ uint32_t first_bit(uint64_t m)
+{
+    const uint32_t lo = (uint32_t)m, hi = (uint32_t)(m >> 32);
+    uint32_t a, b;
+    asm("v_ffbl_b32 %0, %1" : "=v"(a) : "v"(lo)); // -1 for zero
+    asm("v_ffbl_b32 %0, %1" : "=v"(b) : "v"(hi));
+    return min(a, b + 32u);
+}
+
 // ------------------------------------------------------------------ LDS tiles
 // A workgroup owns a tile of TX x TY x TZ target cells.  The tile's halo box
 // ((TX+2) x (TY+2) x (TZ+2) cells, clipped to the grid) is staged in LDS:
@@ -361,25 +382,7 @@ __global__ __launch_bounds__(kBlock) void k_sweep_stream(SweepArgs a)
 // difference of two staged positions is the pair's difference vector (exact
 // for positions on a power-of-two lattice with a power-of-two cell width,
 // and then bit-identical to the cell-relative differences of the other
-// organisations), and the (up to) three cells a target needs from one X-row
-// form a single range: 9 row segments per target instead of 27 cells.  Each
-// lane first writes its target's non-empty segments, in canonical order,
-// into an LDS table; a neighbour cell whose nearest face is provably beyond
-// the cutoff (a conservative test in squared distances) is left out of its
-// segment, which removes about a quarter of the candidates without changing
-// which pairs are accepted or their order.
-//
-// Candidate testing and pair evaluation are decoupled: each lane walks its
-// segments in lockstep with the wavefront and pushes the staging-area byte
-// offset of every accepted source into a private FIFO of Q entries in LDS
-// (segments and queue entries are byte offsets, so no step scales an index);
-// whenever some
-// lane's FIFO is full, the wavefront pops one entry per non-empty lane and
-// evaluates the kernel.  Otherwise the wavefront would run the long
-// evaluation on almost every candidate step (about one candidate in six is
-// accepted, so some lane of 64 nearly always accepts).  FIFO order keeps each
-// target's accumulation order canonical, so results stay bit-identical to the
-// other organisations.
+// organisations).
 //
 // A tile whose halo holds more than CAP particles is flagged and left to the
 // dense pass, which walks each of its targets from global memory with the
@@ -424,8 +427,23 @@ __device__ __forceinline__ void walk_rows_global(const SweepArgs &a, int32_t k, 
     }
 }
 
+// X-pencils (k_sweep_pencil).  The (up to) three cells a target needs from one
+// X-row form a single range: 9 row segments per target instead of 27 cells.
+// Each lane first writes its target's non-empty segments, in canonical order,
+// into an LDS table; a neighbour cell whose nearest face is provably beyond
+// the cutoff (a conservative test in squared distances) is left out of its
+// segment, which removes about a quarter of the candidates without changing
+// which pairs are accepted or their order.  Candidate testing and pair
+// evaluation are decoupled: each lane walks its segments in lockstep with the
+// wavefront and pushes the staging-area byte offset of every accepted source
+// into a private FIFO of Q entries in LDS (segments and queue entries are byte
+// offsets, so no step scales an index); whenever some lane's FIFO is full, the
+// wavefront pops one entry per non-empty lane and evaluates the kernel.  FIFO
+// order keeps each target's accumulation order canonical.  (The sub-boxes test
+// on the matrix cores instead, below; a pencil's staged rows are up to 256
+// cells long, of which a wavefront's targets need a window of each.)
 template <int TX, int TY, int TZ, int CAP, int Q, int PREC, bool INV, bool BATCH>
-__global__ __launch_bounds__(kBlock) void k_sweep_tile(SweepArgs a, int32_t ntx, int32_t nty)
+__global__ __launch_bounds__(kBlock) void k_sweep_pencil(SweepArgs a, int32_t ntx, int32_t nty)
 {
     constexpr int HX = TX + 2, HY = TY + 2, HZ = TZ + 2;
     constexpr int R = HY * HZ;   // halo rows
@@ -692,6 +710,290 @@ __global__ __launch_bounds__(kBlock) void k_sweep_tile(SweepArgs a, int32_t ntx,
     }
     static_assert(sizeof(float4) * CAP >= sizeof(double) * 6 * kBlock, "the staging area parks the partials");
     if (INV) reduce_invariants_lds(a, lb, icnt, inx, iny, inz, isc, irs, reinterpret_cast<double *>(sp));
+}
+
+// Sub-boxes (k_sweep_tile).  The candidates are tested on the matrix cores: with
+// D_ij = |x_j|^2 - 2 x_j . x_i + (|x_i|^2 - rc^2 - slack), positions in cell
+// widths, every pair inside the cutoff has D < 0, and D is a product of K = 16
+// when each coordinate is split into two FP16 numbers (K slots per axis: high
+// and low part against the target's high part, high part against its low part,
+// and one for the constants).  One v_mfma_f32_16x16x16 tests 16 sources against
+// 16 targets, and one v_alignbit per lane and row shifts the four sign bits into
+// a mask, so a candidate costs about 35 / 256 of a wavefront-cycle where a lane
+// testing its own candidates spent about 60 / 64 (23 VALU instructions).  A
+// chunk of 64 staged sources against the wavefront's 64 targets gives every
+// lane 16-bit pieces for four targets; four lane swaps turn them into each
+// target's 64-bit mask in source order (the rows of operand A are permuted so
+// that a piece is 16 consecutive sources).  The staged order is the canonical
+// order (halo rows in z, y, sources in sorted order), so walking the set bits
+// of a target's masks from the lowest up accumulates in that order.
+//
+// Testing and evaluation are decoupled: a lane keeps up to Q masks in LDS, and
+// the wavefront evaluates one pair per lane (the lowest bit of the lane's oldest
+// mask) while some lane's slots are full, and at the end.  The product only
+// filters: an evaluated pair counts if the exact predicate holds (about 0.3% of
+// the pairs do not).  A round is straight code; lanes without work add zeros.
+//
+// Measured (sweep kernel): 2^24 particles at 1 per cell 1.17 ms with per-lane
+// tests and pair queues, 0.76 ms with this (6x6x6); at 8 per cell 4.35 ms with
+// the no-LDS walk, 2.5 ms with this (3x3x3).  What bounds it is VALU issue: at 1
+// per cell about 6,000 cycles per wavefront, 45% in the evaluation rounds (9.7
+// of them, 4.2 pairs per lane), 35% in the chunks, 20% in the set-up.  Matrix
+// and vector instructions of different wavefronts overlap only in part here, so
+// the FP16 form (17 cycles) is taken rather than FP32 (33 cycles for K = 4).
+template <int TX, int TY, int TZ, int CAP, int PREC, bool INV, bool BATCH>
+__global__ __launch_bounds__(kBlock, CAP <= 768 ? 6 : 4) void k_sweep_tile(SweepArgs a, int32_t ntx, int32_t nty)
+{
+    constexpr int HX = TX + 2, HY = TY + 2, HZ = TZ + 2;
+    constexpr int R = HY * HZ;   // halo rows
+    constexpr int TR = TY * TZ;  // target rows
+    constexpr int Q = kMaskQ;
+    static_assert(R <= 64 && TR <= 64, "row tables are scanned by one wavefront");
+    static_assert((Q & (Q - 1)) == 0 && Q <= 4, "a lane's chunk numbers are four bytes of one word");
+    static_assert(CAP % 64 == 0 && CAP / 64 <= 255, "chunks of 64 sources, numbered in a byte");
+    // the staged particles: x, y, z, |x|^2 in cell widths, weight; planes four
+    // words apart over a multiple of 64, so that the four components that a
+    // matrix operand reads lie in different banks
+    constexpr int kPlane = CAP + 4;
+    __shared__ __align__(16) float soa[5][kPlane];
+    __shared__ uint2 words[kBlock / 64][Q][64];   // per lane: chunk masks waiting to be evaluated
+    // halo row of every staged slot, and target row of every target
+    __shared__ uint8_t hrow[CAP];
+    __shared__ uint8_t trow[CAP];
+    __shared__ int32_t rstart[R + 1];
+    __shared__ int32_t gstart[R];
+    __shared__ int32_t rbase[R];
+    __shared__ int32_t tstart[TR + 1];
+    __shared__ int32_t tfirst[TR];
+
+    const uint32_t lb = xcd_remap(blockIdx.x, gridDim.x);
+    uint32_t tl = lb; // tile index within its system
+    if (BATCH) {
+        const SysDev &sd = a.sys[enter_system(a, lb)];
+        tl = lb - (uint32_t)sd.block_base;
+        ntx = sd.ntx;
+        nty = sd.nty;
+        // the system's workgroups past its tiles belong to its dense pass
+        if (tl >= (uint32_t)(ntx * nty * ((a.nz + TZ - 1) / TZ))) return;
+    }
+    const int32_t bx = (int32_t)(tl % (uint32_t)ntx);
+    const int32_t by = (int32_t)((tl / (uint32_t)ntx) % (uint32_t)nty);
+    const int32_t bz = (int32_t)(tl / ((uint32_t)ntx * (uint32_t)nty));
+    const int32_t x0 = bx * TX, y0 = by * TY, z0 = bz * TZ;
+    const int32_t cxlo = max(x0 - 1, 0);
+    const int32_t cxhi = min(x0 + TX, a.nx - 1);
+    const int32_t txhi = min(x0 + TX, a.nx); // exclusive end of target cells
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wid = tid >> 6;
+    const float W = a.k.w;
+
+    // 1. halo row ranges and their LDS starts; target row ranges
+    if (tid < 64) {
+        int32_t cnt = 0, gs = 0, rb32 = 0;
+        if (tid < R) {
+            const int32_t y = y0 - 1 + tid % HY, z = z0 - 1 + tid / HY;
+            if (y >= 0 && y < a.ny && z >= 0 && z < a.nz) {
+                const int64_t rb = (int64_t)a.nx * (y + (int64_t)a.ny * z);
+                rb32 = (int32_t)rb;
+                gs = a.off[rb + cxlo];
+                cnt = a.off[rb + cxhi + 1] - gs;
+            }
+        }
+        const int32_t inc = wave_incl_scan(cnt);
+        if (tid < R) {
+            rstart[tid] = inc - cnt;
+            gstart[tid] = gs;
+            rbase[tid] = rb32;
+            for (int32_t f = inc - cnt; f < min(inc, CAP); ++f) hrow[f] = (uint8_t)tid;
+        }
+        if (tid == R - 1) rstart[R] = inc;
+
+        int32_t tc = 0, tf = 0;
+        if (tid < TR) {
+            const int32_t y = y0 + tid % TY, z = z0 + tid / TY;
+            if (y < a.ny && z < a.nz && x0 < a.nx) {
+                const int64_t rb = (int64_t)a.nx * (y + (int64_t)a.ny * z);
+                tf = a.off[rb + x0];
+                tc = a.off[rb + txhi] - tf;
+            }
+        }
+        const int32_t tinc = wave_incl_scan(tc);
+        if (tid < TR) {
+            tstart[tid] = tinc - tc;
+            tfirst[tid] = tf;
+            for (int32_t f = tinc - tc; f < min(tinc, CAP); ++f) trow[f] = (uint8_t)tid;
+        }
+        if (tid == TR - 1) tstart[TR] = tinc;
+    }
+    __syncthreads();
+    const int32_t total = rstart[R];
+    const int32_t ntarget = tstart[TR];
+    long long icnt = 0;
+    double inx = 0, iny = 0, inz = 0, isc = 0, irs = 0;
+
+    if (tid == 0) a.tflag[lb] = total > CAP ? 1 : 0;
+    if (total > CAP) {
+        // halo too large for LDS: the dense pass (k_sweep_dense, or
+        // k_sweep_dense_batch for a batch) takes this tile's targets, one
+        // thread each across the system, so a dense region is not left to
+        // one workgroup
+        if (!BATCH && tid == 0) *a.ovf = a.epoch;
+        if (INV) reduce_invariants(a, lb, 0, 0.0, 0.0, 0.0, 0.0, 0.0);
+        return;
+    }
+
+    // 2. stage the halo particles in tile-relative coordinates: offsets from
+    //    the corner of the halo box clipped to the grid (cell (cxlo,
+    //    max(y0 - 1, 0), max(z0 - 1, 0))), so that a difference of two staged
+    //    positions is the pair's difference vector with no per-row shift, and
+    //    every staged coordinate lies inside the grid's extent (exact whenever
+    //    the positions are, measured from the grid's origin)
+    const int yoff = y0 > 0 ? 0 : 1, zoff = z0 > 0 ? 0 : 1;
+    const float iw = a.k.inv_w;
+    for (int32_t f = tid; f < total; f += kBlock) {
+        const int lo = hrow[f]; // rstart[lo] <= f < rstart[lo + 1]
+        const int32_t g = gstart[lo] + (f - rstart[lo]);
+        const int32_t cx = a.cell[g] - rbase[lo];
+        const float4 q = a.p4[g];
+        const float x = __builtin_fmaf((float)(cx - cxlo), W, q.x);
+        const float y = __builtin_fmaf((float)(lo % HY - yoff), W, q.y);
+        const float z = __builtin_fmaf((float)(lo / HY - zoff), W, q.z);
+        soa[0][f] = x;
+        soa[1][f] = y;
+        soa[2][f] = z;
+        soa[3][f] = sq_dist(x * iw, y * iw, z * iw);
+        soa[4][f] = q.w;
+    }
+    __syncthreads();
+
+    // 3. targets, in rounds of one per thread; the wavefronts go their own way
+    const int wave = __builtin_amdgcn_readfirstlane(wid);
+    uint2 *myq = &words[wave][0][lane];
+    // the lane's part of a matrix operand: row (or column) n, component kk
+    const int n = lane & 15, kk = lane >> 4;
+    const float *comp = &soa[kk][0];
+    const float ascl = kk < 3 ? iw : 1.0f;
+    const float *acomp = comp + 16 * (n >> 2) + (n & 3);
+    // D < 0 for every pair inside the cutoff: the terms of D are at most
+    // 4 M^2 with M^2 = HX^2 + HY^2 + HZ^2, and what the split into two halves
+    // drops, with the roundings of the sum, is below 10 x 2^-20 (M^2 + 1)
+    constexpr int M2 = HX * HX + HY * HY + HZ * HZ;
+    static_assert(4 * M2 < 60000, "the operands are FP16");
+    const float thr = a.k.rc2_cells + 1.52587890625e-5f * (float)(M2 + 1);
+    for (int32_t f0 = wave * 64; f0 < ntarget; f0 += kBlock) {
+        const int32_t nact = min(64, ntarget - f0);
+        const bool tgt = lane < nact;
+        int32_t k = 0, self = 0, rlo = 0, rhi = 0;
+        if (tgt) {
+            const int32_t f = f0 + lane;
+            const int lo = trow[f]; // tstart[lo] <= f < tstart[lo + 1]
+            k = tfirst[lo] + (f - tstart[lo]);
+            const int32_t ty_ = lo % TY, tz_ = lo / TY;
+            const int hr = (ty_ + 1) + HY * (tz_ + 1);
+            self = rstart[hr] + (k - gstart[hr]);
+            // the staged range of its nine neighbour rows
+            rlo = rstart[ty_ + HY * tz_];
+            rhi = rstart[ty_ + 2 + HY * (tz_ + 2) + 1];
+        }
+        const float xt = soa[0][self], yt = soa[1][self], zt = soa[2][self], wi = soa[4][self];
+        // the four blocks of 16 targets: operand, |x|^2 - threshold, source range
+        v4h bop[4];
+        int32_t blo[4], bhi[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int32_t sb = __builtin_amdgcn_ds_bpermute((16 * b + n) * 4, self);
+            const uint32_t v = split_f16(-2.0f * iw * comp[sb]);
+            const uint32_t c = split_f16(16 * b + n < nact ? soa[3][sb] - thr : 60000.0f);
+            const uint32_t hi = kk < 3 ? (v & 0xffffu) * 0x10001u : 0x3c003c00u;
+            const uint32_t lo = kk < 3 ? v >> 16 : 0u;
+            const uint32_t cc = kk == 0 ? c << 16 : (kk == 1 ? c & 0xffff0000u : 0u);
+            bop[b] = __builtin_bit_cast(v4h, make_uint2(hi, lo | cc));
+            const bool on = 16 * b < nact;
+            blo[b] = on ? __builtin_amdgcn_readlane(rlo, 16 * b) : 0;
+            bhi[b] = on ? __builtin_amdgcn_readlane(rhi, min(16 * b + 15, nact - 1)) : 0;
+        }
+        const int32_t cend = (__builtin_amdgcn_readlane(rhi, nact - 1) + 63) >> 6;
+        const uint64_t selfbit = 1ull << (self & 63);
+        Target<PREC, INV> T;
+        uint64_t m = 0;                       // the word being evaluated ...
+        uint32_t base = 0;                    // ... and its first staged slot
+        uint32_t ids = 0;                     // chunk numbers of the waiting words, oldest in the low byte
+        int cnt = 0, head = 0;                // waiting words, and the slot of the oldest
+        // every lane with an accepted candidate evaluates one
+        auto round = [&]() {
+            if ((m == 0) & (cnt > 0)) {
+                const uint2 w2 = myq[head * 64];
+                m = (uint64_t)w2.x | ((uint64_t)w2.y << 32);
+                base = (ids & 255u) << 6;
+                ids >>= 8;
+                head = (head + 1) & (Q - 1);
+                --cnt;
+            }
+            const bool live = m != 0;
+            // (a lane without work evaluates its own target, all finite)
+            const uint32_t e = __float_as_uint(lane_select(__builtin_amdgcn_ballot_w64(live),
+                                                           __uint_as_float(base + first_bit(m)),
+                                                           __int_as_float(self)));
+            m &= m - 1;
+            const float ddx = xt - soa[0][e], ddy = yt - soa[1][e], ddz = zt - soa[2][e];
+            const float t = sq_dist(ddx, ddy, ddz);
+            const bool in = PREC == PI_PREC_PLAIN ? inside_cutoff(ddx, ddy, ddz, t, a.k)
+                                                  : h2_minus_d2(ddx, ddy, ddz, a.k) > 0.0;
+            T.pair_if(live && in, ddx, ddy, ddz, t, soa[4][e], a.k);
+        };
+        for (int32_t c = blo[0] >> 6; c < cend; ++c) {
+            const int32_t c0 = c << 6;
+            v4h aop[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const uint32_t v = split_f16(ascl * acomp[c0 + 4 * s]);
+                aop[s] = __builtin_bit_cast(v4h, make_uint2(v, (v & 0xffffu) | 0x3c000000u));
+            }
+            uint32_t r[4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                r[b] = 0;
+                if (c0 < bhi[b] && c0 + 64 > blo[b]) {
+#pragma unroll
+                    for (int s = 3; s >= 0; --s) {
+                        const v4f d = __builtin_amdgcn_mfma_f32_16x16x16f16(aop[s], bop[b], v4f{0.f, 0.f, 0.f, 0.f}, 0,
+                                                                            0, 0);
+#pragma unroll
+                        for (int i = 3; i >= 0; --i)
+                            r[b] = __builtin_amdgcn_alignbit(r[b], __float_as_uint(d[i]), 31);
+                    }
+                }
+            }
+            const auto s02 = __builtin_amdgcn_permlane32_swap(r[0], r[2], false, false);
+            const auto s13 = __builtin_amdgcn_permlane32_swap(r[1], r[3], false, false);
+            const auto g01 = __builtin_amdgcn_permlane16_swap(s02[0], s13[0], false, false);
+            const auto g23 = __builtin_amdgcn_permlane16_swap(s02[1], s13[1], false, false);
+            uint64_t w = (uint64_t)(g01[0] | (g01[1] << 16)) | ((uint64_t)(g23[0] | (g23[1] << 16)) << 32);
+            if (total - c0 < 64) w &= (1ull << (total - c0)) - 1ull; // slots past the staged ones
+            w &= (self >> 6) == c ? ~selfbit : ~0ull;
+            // (the slot after the waiting words is free: written always, kept if any)
+            myq[((head + cnt) & (Q - 1)) * 64] = make_uint2((uint32_t)w, (uint32_t)(w >> 32));
+            ids |= w != 0 ? (uint32_t)c << (8 * cnt) : 0u;
+            cnt += w != 0 ? 1 : 0;
+            if (__any(cnt == Q)) { // until every lane has a free slot
+                do round(); while (__any(cnt == Q));
+            }
+        }
+        if (__any((m != 0) | (cnt > 0))) {
+            do round(); while (__any((m != 0) | (cnt > 0)));
+        }
+        if (tgt) {
+            write_target(a, k, T);
+            if (INV) {
+                long long c1;
+                double a1, a2, a3, a4, a5;
+                target_invariants(T, wi, c1, a1, a2, a3, a4, a5);
+                icnt += c1; inx += a1; iny += a2; inz += a3; isc += a4; irs += a5;
+            }
+        }
+    }
+    static_assert(sizeof(soa) >= sizeof(double) * 6 * kBlock, "the staging area parks the partials");
+    if (INV) reduce_invariants_lds(a, lb, icnt, inx, iny, inz, isc, irs, reinterpret_cast<double *>(&soa[0][0]));
 }
 
 // ------------------------------------------------------------------ pencil-reg
@@ -1351,6 +1653,8 @@ KernelConst pi_make_kernel_const(float rc, float cell_w)
     k.sig_h2 = (float)(sigma / (hd * hd));
     k.six_sig_h = (float)(6.0 * sigma / hd);
     k.w = cell_w;
+    k.inv_w = 1.0f / cell_w;
+    k.rc2_cells = (float)(r2 / ((double)cell_w * (double)cell_w));
     return k;
 }
 
@@ -1369,10 +1673,18 @@ const TileCfg kTiles[] = {
     {3, 30, 1, 1, 2560, PI_SWEEP_PENCIL},
     {4, 8, 8, 3, 768, PI_SWEEP_SUBBOX},
     {5, 6, 6, 6, 768, PI_SWEEP_SUBBOX},
-    {6, 4, 4, 4, 1536, PI_SWEEP_SUBBOX},
-    {7, 4, 4, 2, 1536, PI_SWEEP_SUBBOX},
+    {6, 4, 4, 4, 1408, PI_SWEEP_SUBBOX},
+    {7, 4, 4, 2, 1408, PI_SWEEP_SUBBOX},
     {8, 16, 4, 3, 768, PI_SWEEP_SUBBOX},
     {10, 7, 7, 5, 768, PI_SWEEP_SUBBOX},
+    {18, 5, 5, 4, 768, PI_SWEEP_SUBBOX},
+    {19, 5, 4, 4, 1024, PI_SWEEP_SUBBOX},
+    {20, 5, 4, 3, 1024, PI_SWEEP_SUBBOX},
+    {21, 4, 4, 3, 1152, PI_SWEEP_SUBBOX},
+    {22, 4, 3, 3, 1216, PI_SWEEP_SUBBOX},
+    {23, 3, 3, 3, 1408, PI_SWEEP_SUBBOX},
+    {24, 3, 3, 2, 1408, PI_SWEEP_SUBBOX},
+    {25, 3, 2, 2, 1408, PI_SWEEP_SUBBOX},
     // X-pencil-reg sub-boxes; cap = the largest Z-sheet staged at once
     {11, 8, 8, 4, 1024, PI_SWEEP_PENCILREG},
     {12, 4, 4, 2, 1024, PI_SWEEP_PENCILREG},
@@ -1392,7 +1704,7 @@ const TileCfg kTiles[] = {
 constexpr int kFifo = PI_FIFO_DEPTH; // pair queue entries per lane
 constexpr int kCellCap = 256;       // cell-SM: particles per LDS fill
 constexpr int kStreamId = 9; // organisation id of the FIFO stream sweep
-constexpr int kMaxOrgId = 17; // organisation ids are 0 .. kMaxOrgId
+constexpr int kMaxOrgId = 25; // organisation ids are 0 .. kMaxOrgId
 
 // Workgroups of the dense pass that follows a single-system tile launch: a
 // persistent grid of up to four per compute unit, one per 256 particles at
@@ -1427,12 +1739,15 @@ void launch_tile(pi_ctx *ctx, const char *name, const SweepArgs &a, hipStream_t 
     }
     if (BATCH) {
         // (nblk counts every system's tiles and dense workgroups)
-        if (REG)
+        if constexpr (REG)
             PI_LAUNCH(ctx, name, (k_sweep_pencilreg<TX, TY, TZ, CAP, PREC, INV, BATCH>), dim3(nblk), dim3(kBlock), 0,
                       s, a, ntx, nty);
+        else if constexpr (TY == 1 && TZ == 1)
+            PI_LAUNCH(ctx, name, (k_sweep_pencil<TX, TY, TZ, CAP, kFifo, PREC, INV, BATCH>), dim3(nblk),
+                      dim3(kBlock), 0, s, a, ntx, nty);
         else
-            PI_LAUNCH(ctx, name, (k_sweep_tile<TX, TY, TZ, CAP, kFifo, PREC, INV, BATCH>), dim3(nblk), dim3(kBlock),
-                      0, s, a, ntx, nty);
+            PI_LAUNCH(ctx, name, (k_sweep_tile<TX, TY, TZ, CAP, PREC, INV, BATCH>), dim3(nblk), dim3(kBlock), 0, s, a,
+                      ntx, nty);
         PI_LAUNCH(ctx, "k_sweep_dense_batch", (k_sweep_dense_batch<PREC, INV>), dim3(nblk), dim3(kBlock), 0, s, a, TX,
                   TY, TZ, (int32_t)nblk);
         return;
@@ -1440,12 +1755,15 @@ void launch_tile(pi_ctx *ctx, const char *name, const SweepArgs &a, hipStream_t 
     SweepArgs b = a;
     b.epoch = ++*a.host_epoch;
     if (b.epoch == 0) b.epoch = ++*a.host_epoch; // 0 is the word's initial value
-    if (REG)
+    if constexpr (REG)
         PI_LAUNCH(ctx, name, (k_sweep_pencilreg<TX, TY, TZ, CAP, PREC, INV, BATCH>), dim3(nblk), dim3(kBlock), 0, s,
                   b, ntx, nty);
-    else
-        PI_LAUNCH(ctx, name, (k_sweep_tile<TX, TY, TZ, CAP, kFifo, PREC, INV, BATCH>), dim3(nblk), dim3(kBlock), 0,
+    else if constexpr (TY == 1 && TZ == 1)
+        PI_LAUNCH(ctx, name, (k_sweep_pencil<TX, TY, TZ, CAP, kFifo, PREC, INV, BATCH>), dim3(nblk), dim3(kBlock), 0,
                   s, b, ntx, nty);
+    else
+        PI_LAUNCH(ctx, name, (k_sweep_tile<TX, TY, TZ, CAP, PREC, INV, BATCH>), dim3(nblk), dim3(kBlock), 0, s, b,
+                  ntx, nty);
     const unsigned nd = dense_blocks(a.n);
     PI_LAUNCH(ctx, "k_sweep_dense", (k_sweep_dense<PREC, INV>), dim3(nd), dim3(kBlock), 0, s, b, TX, TY, TZ, ntx,
               nty, nblk);
@@ -1492,10 +1810,18 @@ void launch_sweep(pi_ctx *ctx, int tile_id, const SweepArgs &a, hipStream_t s, u
     case 3: launch_tile<30, 1, 1, 2560, PREC, INV, BATCH>(ctx, "k_sweep_tile<30,1,1>", a, s, nblk); break;
     case 4: launch_tile<8, 8, 3, 768, PREC, INV, BATCH>(ctx, "k_sweep_tile<8,8,3>", a, s, nblk); break;
     case 5: launch_tile<6, 6, 6, 768, PREC, INV, BATCH>(ctx, "k_sweep_tile<6,6,6>", a, s, nblk); break;
-    case 6: launch_tile<4, 4, 4, 1536, PREC, INV, BATCH>(ctx, "k_sweep_tile<4,4,4>", a, s, nblk); break;
-    case 7: launch_tile<4, 4, 2, 1536, PREC, INV, BATCH>(ctx, "k_sweep_tile<4,4,2>", a, s, nblk); break;
+    case 6: launch_tile<4, 4, 4, 1408, PREC, INV, BATCH>(ctx, "k_sweep_tile<4,4,4>", a, s, nblk); break;
+    case 7: launch_tile<4, 4, 2, 1408, PREC, INV, BATCH>(ctx, "k_sweep_tile<4,4,2>", a, s, nblk); break;
     case 8: launch_tile<16, 4, 3, 768, PREC, INV, BATCH>(ctx, "k_sweep_tile<16,4,3>", a, s, nblk); break;
     case 10: launch_tile<7, 7, 5, 768, PREC, INV, BATCH>(ctx, "k_sweep_tile<7,7,5>", a, s, nblk); break;
+    case 18: launch_tile<5, 5, 4, 768, PREC, INV, BATCH>(ctx, "k_sweep_tile<5,5,4>", a, s, nblk); break;
+    case 19: launch_tile<5, 4, 4, 1024, PREC, INV, BATCH>(ctx, "k_sweep_tile<5,4,4>", a, s, nblk); break;
+    case 20: launch_tile<5, 4, 3, 1024, PREC, INV, BATCH>(ctx, "k_sweep_tile<5,4,3>", a, s, nblk); break;
+    case 21: launch_tile<4, 4, 3, 1152, PREC, INV, BATCH>(ctx, "k_sweep_tile<4,4,3>", a, s, nblk); break;
+    case 22: launch_tile<4, 3, 3, 1216, PREC, INV, BATCH>(ctx, "k_sweep_tile<4,3,3>", a, s, nblk); break;
+    case 23: launch_tile<3, 3, 3, 1408, PREC, INV, BATCH>(ctx, "k_sweep_tile<3,3,3>", a, s, nblk); break;
+    case 24: launch_tile<3, 3, 2, 1408, PREC, INV, BATCH>(ctx, "k_sweep_tile<3,3,2>", a, s, nblk); break;
+    case 25: launch_tile<3, 2, 2, 1408, PREC, INV, BATCH>(ctx, "k_sweep_tile<3,2,2>", a, s, nblk); break;
     case 11: launch_tile<8, 8, 4, 1024, PREC, INV, BATCH, true>(ctx, "k_sweep_pencilreg<8,8,4>", a, s, nblk); break;
     case 12: launch_tile<4, 4, 2, 1024, PREC, INV, BATCH, true>(ctx, "k_sweep_pencilreg<4,4,2>", a, s, nblk); break;
     case 13: launch_cell<kCellCap, PREC, INV, BATCH>(ctx, "k_sweep_cell<1,1>", 1, 1, a, s, nblk); break;
@@ -1530,10 +1856,7 @@ void launch_sweep_prec(pi_ctx *ctx, int prec, bool inv, int tile_id, const Sweep
         if (inv) launch_sweep<PI_PREC_PLAIN, true, BATCH>(ctx, tile_id, a, s, nblk);
         else if (!BATCH) launch_sweep<PI_PREC_PLAIN, false, false>(ctx, tile_id, a, s, nblk);
         break;
-    case PI_PREC_FP64ACC:
-        if (inv) launch_sweep<PI_PREC_FP64ACC, true, BATCH>(ctx, tile_id, a, s, nblk);
-        else if (!BATCH) launch_sweep<PI_PREC_FP64ACC, false, false>(ctx, tile_id, a, s, nblk);
-        break;
+    // (PI_PREC_FP64ACC is the same arithmetic as PI_PREC_COMPENSATED)
     default:
         if (inv) launch_sweep<PI_PREC_COMPENSATED, true, BATCH>(ctx, tile_id, a, s, nblk);
         else if (!BATCH) launch_sweep<PI_PREC_COMPENSATED, false, false>(ctx, tile_id, a, s, nblk);
@@ -1559,11 +1882,21 @@ bool halo_fits(int id, double ppc)
     return m + 6.0 * sqrt(m) <= (double)t.cap;
 }
 
-// Static rule: the 6x6x6 sub-box while its halo fits (up to about 1.2 per
-// cell), then 4x4x4 (up to about 6), then no LDS.
+// Static rule: the largest sub-box whose halo fits (its targets then come
+// nearest to one per thread): 6x6x6 up to about 1.2 per cell, 5x5x4 to 2.0,
+// 5x4x4 to 3.3, 5x4x3 to 4.1, 4x4x3 to 5.3, 4x3x3 to 6.8, 3x3x3 to 9.6, 3x3x2 to
+// 12, 3x2x2 to 15, then no LDS.  Sweep times on uniform systems of 80^3 or
+// 48^3 cells, the rule's pick against the no-LDS walk and the next best tile:
+// 2 per cell 83 us (no LDS 119, 5x4x4 94), 3 139 (212, 4x4x4 151), 4 212 (328,
+// 4x4x4 224), 6 108 (174, 4x4x2 110), 8 153 (265, 4x4x2 175), 12 296 (510,
+// 3x2x2 360).
+const int kStaticTiles[] = {5, 18, 19, 20, 21, 22, 23, 24, 25};
+
 int pick_tile_default(double ppc)
 {
-    return halo_fits(5, ppc) ? 5 : (halo_fits(6, ppc) ? 6 : 0);
+    for (const int id : kStaticTiles)
+        if (halo_fits(id, ppc)) return id;
+    return 0;
 }
 
 } // namespace
@@ -1633,7 +1966,8 @@ int pi_pick_tile(const pi_interact_opts &o, double ppc)
             return -1;
         }
         if (o.sweep == PI_SWEEP_PENCIL) return halo_fits(1, ppc) ? 1 : (halo_fits(2, ppc) ? 2 : 3);
-        return halo_fits(5, ppc) ? 5 : (halo_fits(6, ppc) ? 6 : 7);
+        const int id = pick_tile_default(ppc);
+        return id > 0 ? id : kStaticTiles[sizeof(kStaticTiles) / sizeof(kStaticTiles[0]) - 1];
     }
     return pick_tile_default(ppc);
 }
@@ -1729,11 +2063,19 @@ uint64_t tune_key(int prec, int64_t n, double ppc, bool batch)
 // near-ties (within run-to-run noise) resolve the same way every time.
 // Organisations that cannot win at mean occupancy ppc and are not timed: the
 // cell-SM over every cell below 16 particles per cell (a wavefront of mostly
-// idle lanes per cell), and its dense-cell pass below 2.
+// idle lanes per cell), and its dense-cell pass below 2; a sub-box whose mean
+// halo overflows its LDS area, or whose mean number of targets fills fewer than
+// 80 of its 256 threads.
 bool worth_timing(int id, double ppc)
 {
-    if (id < 13 || id > 17) return true;
-    return id <= 14 ? ppc >= 16.0 : ppc >= 2.0;
+    if (id <= 0 || id == kStreamId) return true;
+    const TileCfg &t = tile_cfg(id);
+    if (t.id != id) return true;
+    if (t.sweep == PI_SWEEP_SUBBOX)
+        return (double)(t.tx + 2) * (t.ty + 2) * (t.tz + 2) * ppc <= (double)t.cap &&
+               (double)t.tx * t.ty * t.tz * ppc >= 80.0;
+    if (t.sweep != PI_SWEEP_CELL) return true;
+    return t.ty == 1 ? ppc >= 16.0 : ppc >= 2.0;
 }
 
 int time_candidates(pi_ctx *ctx, const SweepArgs &a0, int prec, int first, bool inv, double ppc, hipStream_t s)
