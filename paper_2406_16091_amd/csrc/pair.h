@@ -10,7 +10,7 @@ struct KernelConst {
     float reach2;       // rc^2 (1 + 16 u) rounded up: a cell whose nearest face is at
                         // fl(distance^2) >= reach2 surely holds no pair inside the cutoff
     double hh64;        // h*h, exact in double
-    float hh;           // h*h rounded to float
+    float hh, eh;       // h*h rounded to float, and its residual: h^2 = hh + eh exactly
     float hh_quarter;   // hh / 4 (exact): r^2 <= hh/4  <=>  q <= 1/2
     float h, inv_h;
     float sigma;        // 8 / (pi h^3)
@@ -21,6 +21,17 @@ struct KernelConst {
     float inv_w;        // 1 / w
     float rc2_cells;    // (rc / w)^2
 };
+
+// The arithmetic of a time step with PI_PREC_COMPENSATED: h^2 - r^2 by FP32
+// error-free transforms and Kahan-compensated FP32 sums, as the first time
+// steps of this library had them.  A last bit of G that differs moves some
+// particles to the next point of the position lattice, and the trajectory leaves
+// its earlier course from there (with the FP64 forms below, G differed by up to
+// 1.5e-3 of its mean size after eight steps of 2^24 particles): the time steps
+// keep their arithmetic, so that a simulation can be taken up and checked against
+// earlier runs bit for bit.  In the sub-box tiles at 1 per cell it costs nothing:
+// four steps and a read-back take 8.11 ms either way.
+constexpr int kPrecStep = 3;
 
 // h^2 - (dx^2 + dy^2 + dz^2) in FP64, which the vector units issue at the rate
 // of (non-packed) FP32: the square of a float is exact in double (48
@@ -42,22 +53,65 @@ __device__ __forceinline__ double h2_minus_d2(float dx, float dy, float dz, cons
     return __builtin_fma(-z, z, __builtin_fma(-y, y, __builtin_fma(-x, x, k.hh64)));
 }
 
+// Error of a + b = s (Knuth's TwoSum, branch-free): a + b == s + err exactly.
+__device__ __forceinline__ float two_sum_err(float a, float b, float s)
+{
+    const float bb = s - a;
+    return (a - (s - bb)) + (b - bb);
+}
+
+// The same by error-free transforms in FP32: the squares are split into float +
+// exact FMA residual, their sum into float + TwoSum errors, and the large part
+// is subtracted from hh exactly (Sterbenz, since the sum is within a factor of
+// two of hh wherever this matters).  The sign is exact whenever
+// |h^2 - r^2| exceeds about 6 * 2^-48 h^2.
+__device__ __forceinline__ float h2_minus_d2_fp32(float dx, float dy, float dz, const KernelConst &k)
+{
+    const float p1 = dx * dx, e1 = __builtin_fmaf(dx, dx, -p1);
+    const float p2 = dy * dy, e2 = __builtin_fmaf(dy, dy, -p2);
+    const float p3 = dz * dz, e3 = __builtin_fmaf(dz, dz, -p3);
+    const float a = p1 + p2;
+    const float t1 = two_sum_err(p1, p2, a);
+    const float s = a + p3;
+    const float t2 = two_sum_err(a, p3, s);
+    const float tail = ((t1 + t2) + (e1 + e2)) + e3; // r^2 = s + tail
+    const float head = k.hh - s;
+    return head + (k.eh - tail);
+}
+
+// Whether h^2 - r^2 > 0, and its value as a term uses it.
+template <int PREC>
+__device__ __forceinline__ bool h2_above_d2(float dx, float dy, float dz, const KernelConst &k)
+{
+    if (PREC == kPrecStep) return h2_minus_d2_fp32(dx, dy, dz, k) > 0.0f;
+    return h2_minus_d2(dx, dy, dz, k) > 0.0;
+}
+
+template <int PREC>
+__device__ __forceinline__ float h2_minus_d2_term(float dx, float dy, float dz, const KernelConst &k)
+{
+    if (PREC == kPrecStep) return h2_minus_d2_fp32(dx, dy, dz, k);
+    return (float)h2_minus_d2(dx, dy, dz, k);
+}
+
 // The exact predicate in the band [lo, hi), which almost no candidate falls
 // into: the empty asm keeps the compiler from evaluating it for every
 // candidate ahead of the branch (cheap enough, in FP64, to be speculated).
+template <int PREC>
 __device__ __forceinline__ bool in_band_inside(float dx, float dy, float dz, const KernelConst &k)
 {
     asm volatile("");
-    return h2_minus_d2(dx, dy, dz, k) > 0.0;
+    return h2_above_d2<PREC>(dx, dy, dz, k);
 }
 
 // Filtered exact predicate r < rc from the FP32 value t = fl(r^2) computed as
 // fma(dz, dz, fma(dy, dy, dx * dx)) (relative error below 3.0001 * 2^-24).
+template <int PREC>
 __device__ __forceinline__ bool inside_cutoff(float dx, float dy, float dz, float t, const KernelConst &k)
 {
     if (t < k.lo) return true;
     if (t >= k.hi) return false;
-    return in_band_inside(dx, dy, dz, k);
+    return in_band_inside<PREC>(dx, dy, dz, k);
 }
 
 __device__ __forceinline__ float sq_dist(float dx, float dy, float dz)
@@ -104,7 +158,7 @@ __device__ __forceinline__ void bspline_terms(float dx, float dy, float dz, floa
         if (PREC == PI_PREC_PLAIN) {
             omq = fmaxf(1.0f - r * k.inv_h, 0.0f);
         } else {
-            const float D = (float)h2_minus_d2(dx, dy, dz, k);
+            const float D = h2_minus_d2_term<PREC>(dx, dy, dz, k);
             omq = D * __builtin_amdgcn_rcpf(k.h * (k.h + r));
         }
         const float omq2 = omq * omq;
@@ -125,7 +179,7 @@ __device__ __forceinline__ void bspline_terms(float dx, float dy, float dz, floa
             omq = fmaxf(1.0f - r * k.inv_h, 0.0f);
         } else {
             // 1 - q = (h^2 - r^2) / (h (h + r)), with h^2 - r^2 free of cancellation
-            const float D = (float)h2_minus_d2(dx, dy, dz, k);
+            const float D = h2_minus_d2_term<PREC>(dx, dy, dz, k);
             omq = D * __builtin_amdgcn_rcpf(k.h * (k.h + r));
         }
         const float omq2 = omq * omq;
@@ -185,6 +239,32 @@ struct Acc<PI_PREC_FP64ACC> {
 template <>
 struct Acc<PI_PREC_COMPENSATED> : Acc<PI_PREC_FP64ACC> {};
 
+// Kahan's compensated summation: c is the rounding excess of the running sum
+// so far (what was added minus what was meant), taken off the next term.
+template <>
+struct Acc<kPrecStep> {
+    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
+    float c0 = 0.f, c1 = 0.f, c2 = 0.f, c3 = 0.f;
+    __device__ __forceinline__ static void ks(float &s, float &c, float v)
+    {
+        const float y = v - c;
+        const float n = s + y;
+        c = (n - s) - y;
+        s = n;
+    }
+    __device__ __forceinline__ void add(float a, float f, float dx, float dy, float dz)
+    {
+        ks(s0, c0, a);
+        ks(s1, c1, f * dx);
+        ks(s2, c2, f * dy);
+        ks(s3, c3, f * dz);
+    }
+    __device__ __forceinline__ float r_rho() const { return s0 - c0; }
+    __device__ __forceinline__ float r_gx() const { return s1 - c1; }
+    __device__ __forceinline__ float r_gy() const { return s2 - c2; }
+    __device__ __forceinline__ float r_gz() const { return s3 - c3; }
+};
+
 // Everything a target keeps while it walks its 27 cells.
 template <int PREC, bool INV>
 struct Target {
@@ -196,7 +276,7 @@ struct Target {
     __device__ __forceinline__ void candidate(float dx, float dy, float dz, float wj, const KernelConst &k)
     {
         const float t = sq_dist(dx, dy, dz);
-        if (t < k.hi && inside_cutoff(dx, dy, dz, t, k)) accept(dx, dy, dz, t, wj, k);
+        if (t < k.hi && inside_cutoff<PREC>(dx, dy, dz, t, k)) accept(dx, dy, dz, t, wj, k);
     }
 
     // The same for a wavefront that evaluates queued pairs together: every lane
@@ -211,7 +291,8 @@ struct Target {
         // (the products, not a factor: either may be infinite)
         const uint64_t in = __builtin_amdgcn_ballot_w64(ok);
         const float a = lane_select(in, wj * W, 0.0f), f = lane_select(in, wj * Fr, 0.0f);
-        acc.add(a, f, dx, dy, dz);
+        // (adding zero would move a Kahan sum's excess into the sum)
+        if (PREC != kPrecStep || ok) acc.add(a, f, dx, dy, dz);
         count = lane_add(in, count);
         if (INV) ascale += -f * __builtin_amdgcn_sqrtf(t); // (Fr <= 0)
     }

@@ -28,11 +28,12 @@
 
 #include <algorithm>
 
-#include "pi_internal.h"
+#include "pair.h"
 
 namespace {
 
 constexpr int kBlock = 256;
+constexpr int64_t kRecordsMin = 1 << 18;             // particles from which a read-back goes through records
 constexpr int kScanThreads = 1024;                  // threads per block of the offsets scan
 constexpr int kScanPer = 4;                          // consecutive cells per thread
 constexpr int kScanBlock = kScanThreads * kScanPer;  // cells per block
@@ -473,6 +474,7 @@ extern "C" pi_status pi_step(pi_ctx *ctx, pi_cells *cells, const pi_step_opts *o
     for (int q = 0; q < 3; ++q) io.tile[q] = o.tile[q];
     pi_status st = pi_check_interact_opts(io, n, cells->grho, cells->ggx, cells->ggy, cells->ggz, nullptr, inv);
     if (st != PI_OK) return st;
+    if (io.precision == PI_PREC_COMPENSATED) io.precision = kPrecStep;
     st = pi_interact_run(ctx, cells, io, cells->grho, cells->ggx, cells->ggy, cells->ggz, nullptr, inv, s,
                          cells->partials, cells->cap_partials, false);
     if (st != PI_OK) return st;

@@ -211,7 +211,7 @@ __global__ __launch_bounds__(kBlock) void k_sweep_nolds(SweepArgs a)
                     const float4 s = a.p4[j];
                     const float ddx = tx - s.x, ddy = ty - s.y, ddz = tz - s.z;
                     const float t = sq_dist(ddx, ddy, ddz);
-                    if (t < a.k.hi && j != k && inside_cutoff(ddx, ddy, ddz, t, a.k))
+                    if (t < a.k.hi && j != k && inside_cutoff<PREC>(ddx, ddy, ddz, t, a.k))
                         T.accept(ddx, ddy, ddz, t, s.w, a.k);
                 }
             }
@@ -323,7 +323,7 @@ __global__ __launch_bounds__(kBlock) void k_sweep_stream(SweepArgs a)
                         const float ddx = sel(dxc, xm, xi, xp) - s.x, ddy = ty - s.y, ddz = tz - s.z;
                         const float t = sq_dist(ddx, ddy, ddz);
                         bool acc = t < a.k.lo;
-                        if (t >= a.k.lo && t < a.k.hi) acc = in_band_inside(ddx, ddy, ddz, a.k);
+                        if (t >= a.k.lo && t < a.k.hi) acc = in_band_inside<PREC>(ddx, ddy, ddz, a.k);
                         if (acc && j != k) {
                             myq[((qh + qc) & (Q - 1)) * 64] = make_float4(ddx, ddy, ddz, s.w);
                             ++qc;
@@ -420,7 +420,7 @@ __device__ __forceinline__ void walk_rows_global(const SweepArgs &a, int32_t k, 
                 const float4 s = a.p4[j];
                 const float ddx = tx - s.x, ddy = ty - s.y, ddz = tz - s.z;
                 const float t = sq_dist(ddx, ddy, ddz);
-                if (t < a.k.hi && j != k && inside_cutoff(ddx, ddy, ddz, t, a.k))
+                if (t < a.k.hi && j != k && inside_cutoff<PREC>(ddx, ddy, ddz, t, a.k))
                     T.accept(ddx, ddy, ddz, t, s.w, a.k);
             }
         }
@@ -682,7 +682,7 @@ __global__ __launch_bounds__(kBlock) void k_sweep_pencil(SweepArgs a, int32_t nt
                 // exact test (inside_cutoff, unrolled to keep the step short)
                 bool acc = t < a.k.lo;
                 const bool below_hi = t < a.k.hi;
-                if (below_hi && !acc) acc = in_band_inside(ddx, ddy, ddz, a.k);
+                if (below_hi && !acc) acc = in_band_inside<PREC>(ddx, ddy, ddz, a.k);
                 // the slot after the queue's tail is free (the queue is
                 // never full at this point), so it is written always and
                 // kept if accepted
@@ -937,8 +937,8 @@ __global__ __launch_bounds__(kBlock, CAP <= 768 ? 6 : 4) void k_sweep_tile(Sweep
             m &= m - 1;
             const float ddx = xt - soa[0][e], ddy = yt - soa[1][e], ddz = zt - soa[2][e];
             const float t = sq_dist(ddx, ddy, ddz);
-            const bool in = PREC == PI_PREC_PLAIN ? inside_cutoff(ddx, ddy, ddz, t, a.k)
-                                                  : h2_minus_d2(ddx, ddy, ddz, a.k) > 0.0;
+            const bool in = PREC == PI_PREC_PLAIN ? inside_cutoff<PREC>(ddx, ddy, ddz, t, a.k)
+                                                  : h2_above_d2<PREC>(ddx, ddy, ddz, a.k);
             T.pair_if(live && in, ddx, ddy, ddz, t, soa[4][e], a.k);
         };
         for (int32_t c = blo[0] >> 6; c < cend; ++c) {
@@ -1183,7 +1183,7 @@ __global__ __launch_bounds__(kBlock) void k_sweep_pencilreg(SweepArgs a, int32_t
                             const float4 src = sp[j];
                             const float ddx = t.x - src.x, ddy = t.y - src.y, ddz = t.z - src.z;
                             const float d2 = sq_dist(ddx, ddy, ddz);
-                            if (d2 < a.k.hi && j != own && inside_cutoff(ddx, ddy, ddz, d2, a.k))
+                            if (d2 < a.k.hi && j != own && inside_cutoff<PREC>(ddx, ddy, ddz, d2, a.k))
                                 T.accept(ddx, ddy, ddz, d2, src.w, a.k);
                         }
                     }
@@ -1380,7 +1380,7 @@ __global__ __launch_bounds__(kCellBlock) void k_sweep_cell(SweepArgs a, int32_t 
                         auto test = [&](int32_t sl, const float4 &src) {
                             const float ddx = tx - src.x, ddy = ty - src.y, ddz = tz - src.z;
                             const float t = sq_dist(ddx, ddy, ddz);
-                            if (en && t < a.k.hi && sl != self && inside_cutoff(ddx, ddy, ddz, t, a.k))
+                            if (en && t < a.k.hi && sl != self && inside_cutoff<PREC>(ddx, ddy, ddz, t, a.k))
                                 T.accept(ddx, ddy, ddz, t, src.w, a.k);
                         };
                         int32_t s = sa;
@@ -1644,6 +1644,7 @@ KernelConst pi_make_kernel_const(float rc, float cell_w)
     k.reach2 = nextafterf((float)(r2 * (1.0 + 16.0 * u)), INFINITY);
     k.hh64 = r2;
     k.hh = h * h;
+    k.eh = fmaf(h, h, -k.hh);
     k.hh_quarter = k.hh * 0.25f;
     k.h = h;
     k.inv_h = (float)(1.0 / hd);
@@ -1855,6 +1856,12 @@ void launch_sweep_prec(pi_ctx *ctx, int prec, bool inv, int tile_id, const Sweep
     case PI_PREC_PLAIN:
         if (inv) launch_sweep<PI_PREC_PLAIN, true, BATCH>(ctx, tile_id, a, s, nblk);
         else if (!BATCH) launch_sweep<PI_PREC_PLAIN, false, false>(ctx, tile_id, a, s, nblk);
+        break;
+    case kPrecStep: // pi_step only; never in a batch
+        if constexpr (!BATCH) {
+            if (inv) launch_sweep<kPrecStep, true, false>(ctx, tile_id, a, s, nblk);
+            else launch_sweep<kPrecStep, false, false>(ctx, tile_id, a, s, nblk);
+        }
         break;
     // (PI_PREC_FP64ACC is the same arithmetic as PI_PREC_COMPENSATED)
     default:
