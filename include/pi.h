@@ -152,9 +152,9 @@ pi_status pi_cells_get_view(pi_cells *cells, pi_cells_view *out);
 #define PI_SWEEP_SUBBOX 3 /* a workgroup owns a 3-D sub-box of target cells;
                              the sub-box and its ghost shell are staged in LDS
                              (Sec. 5.1, All-in-SM, Algorithm 4) */
-#define PI_SWEEP_STREAM 4 /* as NOLDS (nothing staged), with accepted pairs
-                             queued per thread in LDS and evaluated by the
-                             whole wavefront at once (works at any occupancy) */
+#define PI_SWEEP_STREAM 4 /* targets in cell-sorted order, one per thread, with
+                             the neighbour X-rows' sources streamed through LDS
+                             in chunks of 64 (works at any occupancy) */
 #define PI_SWEEP_PENCILREG 5 /* a workgroup owns a sub-box of target cells held
                              in registers, one target per thread; the halo's
                              X-pencils stream through LDS one Z-sheet at a time,
@@ -379,7 +379,7 @@ pi_status pi_sync(pi_ctx *ctx, pi_cells *cells, pi_stream stream);
  * a fixed rule on the mean occupancy instead: the largest of nine sub-boxes
  * (6x6x6 down to 3x2x2 cells) whose staged halo is expected to fit in LDS (mean
  * + 6 standard deviations of a Poisson count), up to about 15 particles per
- * cell, then no LDS.  The same rule picks the tile of PI_SWEEP_SUBBOX, and the
+ * cell, then the stream.  The same rule picks the tile of PI_SWEEP_SUBBOX, and the
  * same fit test that of PI_SWEEP_PENCIL, when tile[] is zero; PI_SWEEP_CELL with
  * tile[] zero takes every cell (one per workgroup) from 32 particles per cell
  * on, else the cells holding 32 or more with the no-LDS walk for the rest.

@@ -415,15 +415,15 @@ pi_status launch_batch(pi_server *s, Lane &ln, const std::vector<Ticket *> &ts)
     // AUTO never runs timed trials on a request's path: the tuner's cached
     // choice for the request's class if there is one, else the static rule;
     // a request whose densest cell would overflow the LDS tilings takes the
-    // no-LDS walk (the same choice alone and in a batch)
+    // stream (the same choice alone and in a batch)
     pi_interact_opts o1 = o;
     if (ln.alone && o1.sweep == PI_SWEEP_AUTO) {
         const double nc = (double)r0.grid.dims[0] * r0.grid.dims[1] * r0.grid.dims[2];
-        pi_tile_opts(clustered(ts[0]) ? 0 : pi_auto_tile(s->ctx, r0.precision, r0.n, (double)r0.n / nc), &o1);
+        pi_tile_opts(clustered(ts[0]) ? kOrgStream : pi_auto_tile(s->ctx, r0.precision, r0.n, (double)r0.n / nc), &o1);
     }
     std::vector<int32_t> org((size_t)m, -1);
     if (o.sweep == PI_SWEEP_AUTO)
-        for (int32_t i = 0; i < m; ++i) org[i] = clustered(ts[i]) ? 0 : -1;
+        for (int32_t i = 0; i < m; ++i) org[i] = clustered(ts[i]) ? kOrgStream : -1;
     bool jitter = false;
     for (const Ticket *t : ts) jitter = jitter || t->req.jitter_sigma > 0.0f;
     for (int32_t k = 0; k < R; ++k) {
@@ -609,9 +609,10 @@ bool inside_box(const pi_request &r, bool occupancy, int32_t *max_ppc)
 }
 
 // Whether a request's densest cell makes the LDS tilings overflow there, so
-// that AUTO should take the no-LDS walk: its most-occupied cell holds more
-// than four times the mean plus eight (the clustered inputs; the static rule
-// reads only the mean).
+// that AUTO should take the stream: its most-occupied cell holds more than
+// four times the mean plus eight (the clustered inputs; the static rule reads
+// only the mean).  Sweep of a clustered 8e4 particles alone: stream 331 us, no
+// LDS 684, 4x4x4 tiles 778.
 bool clustered(const Ticket *t)
 {
     const pi_grid &g = t->req.grid;

@@ -226,129 +226,6 @@ __global__ __launch_bounds__(kBlock) void k_sweep_nolds(SweepArgs a)
     }
 }
 
-// ------------------------------------------------------------------ stream
-// One thread per sorted target with sources read through the caches, as in
-// NOLDS (the same trimmed X-row walk, one row of the 9 at a time for the
-// whole wavefront), but with candidate testing decoupled from pair
-// evaluation by a per-lane LDS FIFO as in the tiles: the test of one
-// candidate is a few instructions, the evaluation of an accepted pair about a
-// hundred, and at several particles per cell some lane of a wavefront
-// accepts on nearly every step.  A queue entry holds the differences the
-// test computed and the source's weight, so a pop reads nothing from global
-// memory and evaluates the same values.  Nothing is staged, so the
-// organisation works at any occupancy.
-template <int Q, int PREC, bool INV, bool BATCH>
-__global__ __launch_bounds__(kBlock) void k_sweep_stream(SweepArgs a)
-{
-    static_assert((Q & (Q - 1)) == 0, "FIFO depth must be a power of two");
-    __shared__ float4 fifo[kBlock / 64][Q][64];   // accepted pair: (dx, dy, dz, w_j)
-
-    const uint32_t lb = xcd_remap(blockIdx.x, gridDim.x);
-    int32_t k, kend;
-    if (BATCH) {
-        const SysDev &sd = a.sys[enter_system(a, lb)];
-        k = (int32_t)sd.first + (int32_t)(lb - sd.block_base) * kBlock + (int32_t)threadIdx.x;
-        kend = (int32_t)sd.first + sd.n;
-    } else {
-        k = (int32_t)(lb * kBlock + threadIdx.x);
-        kend = min(a.off[a.nc], a.n);
-    }
-    const bool active = k < kend;
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const float W = a.k.w;
-    const float reach2 = a.k.reach2;
-    float xi = 0.f, yi = 0.f, zi = 0.f, wi = 0.f;
-    int32_t ix = 0, iy = 0, iz = 0;
-    if (active) {
-        const int32_t c = a.cell[k];
-        ix = c % a.nx;
-        iy = (c / a.nx) % a.ny;
-        iz = c / (a.nx * a.ny);
-        const float4 pk = a.p4[k];
-        xi = pk.x;
-        yi = pk.y;
-        zi = pk.z;
-        wi = pk.w;
-    }
-    // the target in the frame of a neighbour cell: x - d W for d = -1, 0, 1
-    // (the same roundings as the no-LDS walk)
-    const float xm = xi - (float)(-1) * W, xp = xi - (float)(1) * W;
-    const float ym = yi - (float)(-1) * W, yp = yi - (float)(1) * W;
-    const float zm = zi - (float)(-1) * W, zp = zi - (float)(1) * W;
-    auto sel = [](int q, float m, float o, float p) { return q == 0 ? m : (q == 1 ? o : p); };
-    const float gyl = yi * yi, gyr = (W - yi) * (W - yi);
-    const float gzl = zi * zi, gzr = (W - zi) * (W - zi);
-    const float tl = ix > 0 ? reach2 - xi * xi : -1.0f;
-    const float tr = ix + 1 < a.nx ? reach2 - (W - xi) * (W - xi) : -1.0f;
-
-    Target<PREC, INV> T;
-    float4 *myq = &fifo[wid][0][lane];
-    int qh = 0, qc = 0;
-    auto pop = [&]() {
-        const float4 e = myq[qh * 64];
-        qh = (qh + 1) & (Q - 1);
-        --qc;
-        T.template accept<true>(e.x, e.y, e.z, sq_dist(e.x, e.y, e.z), e.w, a.k);
-    };
-    for (int dz = -1; dz <= 1; ++dz) {
-        const float tz = dz < 0 ? zm : (dz > 0 ? zp : zi);
-        const float gz = dz < 0 ? gzl : (dz > 0 ? gzr : 0.f);
-        const bool zok = active && iz + dz >= 0 && iz + dz < a.nz;
-        for (int dy = -1; dy <= 1; ++dy) {
-            const float ty = dy < 0 ? ym : (dy > 0 ? yp : yi);
-            const float gyz = (dy < 0 ? gyl : (dy > 0 ? gyr : 0.f)) + gz;
-            // this lane's range of the row (empty if the row is outside the
-            // grid or out of reach) and its two inner cell boundaries
-            int32_t j = 0, j3 = 0, b1 = 0, b2 = 0;
-            if (zok && iy + dy >= 0 && iy + dy < a.ny && gyz < reach2) {
-                const int64_t rb = (int64_t)a.nx * ((iy + dy) + (int64_t)a.ny * (iz + dz)) + ix;
-                b1 = a.off[rb];
-                b2 = a.off[rb + 1];
-                j = gyz < tl ? a.off[rb - 1] : b1;
-                j3 = gyz < tr ? a.off[rb + 2] : b2;
-            }
-            // tests until some lane's queue is full (the accumulators are
-            // not touched in this inner loop, which keeps it free of
-            // register copies), then one round of pops.  The lanes walk the
-            // same row together, so their loads fall on neighbouring cells
-            // (walking each lane's rows as one sequence, so that the loop
-            // runs to the longest lane total instead of the sum of the
-            // longest rows, scattered the loads over rows and was 1.5x
-            // slower at 8 per cell).
-            while (__any(j < j3)) {
-                do {
-                    if (j < j3) {
-                        const int dxc = j < b1 ? 0 : (j < b2 ? 1 : 2);
-                        const float4 s = a.p4[j];
-                        const float ddx = sel(dxc, xm, xi, xp) - s.x, ddy = ty - s.y, ddz = tz - s.z;
-                        const float t = sq_dist(ddx, ddy, ddz);
-                        bool acc = t < a.k.lo;
-                        if (t >= a.k.lo && t < a.k.hi) acc = in_band_inside<PREC>(ddx, ddy, ddz, a.k);
-                        if (acc && j != k) {
-                            myq[((qh + qc) & (Q - 1)) * 64] = make_float4(ddx, ddy, ddz, s.w);
-                            ++qc;
-                        }
-                        ++j;
-                    }
-                } while (!__any(qc == Q) && __any(j < j3));
-                if (__any(qc == Q)) {
-                    if (qc > 0) pop();
-                }
-            }
-        }
-    }
-    for (int left = wave_max(qc); left > 0; --left) {
-        if (qc > 0) pop();
-    }
-    if (active) write_target(a, k, T);
-    if (INV) {
-        long long cnt = 0;
-        double nx = 0, ny = 0, nz = 0, sc = 0, rs = 0;
-        if (active) target_invariants(T, wi, cnt, nx, ny, nz, sc, rs);
-        reduce_invariants(a, lb, cnt, nx, ny, nz, sc, rs);
-    }
-}
-
 // x as the sum of two FP16 numbers: the leading one (11 bits of x) in the low
 // half of the word, the rest (its leading 11 bits) in the high half.
 __device__ __forceinline__ uint32_t split_f16(float x)
@@ -365,6 +242,295 @@ __device__ __forceinline__ uint32_t first_bit(uint64_t m)
     asm("v_ffbl_b32 %0, %1" : "=v"(a) : "v"(lo)); // -1 for zero
     asm("v_ffbl_b32 %0, %1" : "=v"(b) : "v"(hi));
     return min(a, b + 32u);
+}
+
+// ------------------------------------------------------------------ stream
+// Targets in cell-sorted order, one per lane, with sources streamed through LDS a
+// chunk of 64 at a time, so that any occupancy fits: the organisation for dense
+// and clustered systems.  Each wavefront goes its own way (no barriers).  Its
+// targets are taken in groups that share an X-row of cells (mostly one group);
+// the nine neighbour X-rows' sources within a cell of the group are one range
+// each, cut into chunks.  A chunk is loaded coalesced, one chunk ahead, staged in
+// a ring of RING chunks together with its matrix operand, tested against the 64
+// targets on the matrix cores as in the sub-box tiles (below: one FP16 product per
+// 16 x 16 pairs, sign bits gathered into a 64-bit mask per target, pairs
+// evaluated from the masks' bits), in a frame of the group in cell widths.  The
+// test only filters; a pair is evaluated from cell-relative positions with the
+// no-LDS walk's roundings, and each target sees its sources in the canonical
+// order, so the outputs are bitwise those of the no-LDS walk, also off the
+// lattice.  A ring slot is reused once no lane has a mask of its chunk left.
+//
+// What bounds it is VALU issue, at about 80 instructions per round, and the
+// number of rounds: with a ring of four chunks the lanes stay within four chunks
+// of each other, and at 64 per cell a wavefront takes about 480 rounds for 268
+// pairs per lane.  A longer ring takes fewer rounds but leaves too few wavefronts
+// per SIMD to hide the LDS latency (RING, Q = 4, 2: 29 KB, five workgroups per
+// CU): 64 per cell 2.34 ms with (4, 2), 2.47 with (4, 4), 2.93 with (2, 2), 2.98
+// with (8, 4); loading each lane's next pair a round ahead cost more registers
+// and copies than it saved (2.61).  Sweep times, no-LDS walk and this: clustered
+// 2^23 3.29 and 2.25 ms, 2^21 at 64 per cell 3.08 and 2.33 ms (plain sums 2.48
+// and 2.02), 24 per cell 1.65 and 1.15 ms; clustered 3e4 0.43 and 0.19 ms.
+template <int Q, int RING, int PREC, bool INV, bool BATCH>
+__global__ __launch_bounds__(kBlock, 4) void k_sweep_stream(SweepArgs a)
+{
+    static_assert((Q & (Q - 1)) == 0 && Q <= 4, "a lane's chunk numbers are four bytes of one word");
+    static_assert((RING & (RING - 1)) == 0 && RING <= 64, "ring slots are the low bits of a chunk number");
+    constexpr int kWaves = kBlock / 64;
+    constexpr uint32_t kNone = RING * 64; // an entry of zeros, for lanes without work
+    // per wavefront: the ring of staged chunks (cell-relative position and
+    // weight, and the cell along X from the group's first), each chunk's row
+    // shift, the operand of the chunk being tested, and each lane's masks
+    __shared__ float4 ring_p[kWaves][RING * 64 + 1];
+    __shared__ float ring_cx[kWaves][RING * 64 + 1];
+    __shared__ float2 ring_row[kWaves][RING];
+    __shared__ uint32_t opnd[kWaves][4][68];
+    __shared__ uint2 words[kWaves][Q][64];
+
+    const uint32_t lb = xcd_remap(blockIdx.x, gridDim.x);
+    int32_t k, kend;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (BATCH) {
+        const SysDev &sd = a.sys[enter_system(a, lb)];
+        k = (int32_t)sd.first + (int32_t)(lb - sd.block_base) * kBlock + tid;
+        kend = (int32_t)sd.first + sd.n;
+    } else {
+        k = (int32_t)(lb * kBlock) + tid;
+        kend = min(a.off[a.nc], a.n);
+    }
+    const bool active = k < kend;
+    const float W = a.k.w, iw = a.k.inv_w;
+    const float reach2 = a.k.reach2;
+    float xi = 0.f, yi = 0.f, zi = 0.f, wi = 0.f;
+    int32_t ix = 0, row = -1;
+    if (active) {
+        const int32_t c = a.cell[k];
+        row = c / a.nx;
+        ix = c - row * a.nx;
+        const float4 pk = a.p4[k];
+        xi = pk.x;
+        yi = pk.y;
+        zi = pk.z;
+        wi = pk.w;
+    }
+    float4 *rp = ring_p[wave];
+    float *rcx = ring_cx[wave];
+    uint2 *myq = &words[wave][0][lane];
+    if (lane == 0) {
+        rp[kNone] = make_float4(0.f, 0.f, 0.f, 0.f);
+        rcx[kNone] = 0.f;
+    }
+    const int n = lane & 15, kk = lane >> 4;
+    const uint32_t *acomp = &opnd[wave][kk][16 * (n >> 2) + (n & 3)];
+    const float gyl = yi * yi, gyr = (W - yi) * (W - yi);
+    const float gzl = zi * zi, gzr = (W - zi) * (W - zi);
+
+    Target<PREC, INV> T;
+    uint64_t m = 0;          // the mask being evaluated, ...
+    uint32_t base = 0;       // ... its first entry of the ring, ...
+    float ty = 0.f, tz = 0.f; // ... and the target in the frame of its row
+    uint32_t ids = 0;        // chunk numbers of the waiting masks, oldest in the low byte
+    uint32_t seq_m = 0;      // chunk number of the mask being evaluated
+    int cnt = 0, head = 0;   // waiting masks, and the slot of the oldest
+    float cxi = 0.f;         // the target's cell along X from the group's first
+    auto round = [&]() {
+        if ((m == 0) & (cnt > 0)) {
+            const uint2 w2 = myq[head * 64];
+            m = (uint64_t)w2.x | ((uint64_t)w2.y << 32);
+            seq_m = ids & 255u;
+            const uint32_t slot = ids & (RING - 1);
+            const float2 sh = ring_row[wave][slot];
+            base = slot << 6;
+            ty = __builtin_fmaf(-sh.x, W, yi);
+            tz = __builtin_fmaf(-sh.y, W, zi);
+            ids >>= 8;
+            head = (head + 1) & (Q - 1);
+            --cnt;
+        }
+        const bool live = m != 0;
+        const uint32_t e = __float_as_uint(lane_select(__builtin_amdgcn_ballot_w64(live),
+                                                       __uint_as_float(base + first_bit(m)),
+                                                       __uint_as_float(kNone)));
+        m &= m - 1;
+        const float4 q = rp[e];
+        // (x_i - d W with d the source's cell against the target's, -1, 0 or 1:
+        // the roundings of the no-LDS walk)
+        const float tx = __builtin_fmaf(cxi - rcx[e], W, xi);
+        const float ddx = tx - q.x, ddy = ty - q.y, ddz = tz - q.z;
+        const float t = sq_dist(ddx, ddy, ddz);
+        const bool in = PREC == PI_PREC_PLAIN ? inside_cutoff<PREC>(ddx, ddy, ddz, t, a.k)
+                                              : h2_above_d2<PREC>(ddx, ddy, ddz, a.k);
+        T.pair_if(live && in, ddx, ddy, ddz, t, q.w, a.k);
+    };
+
+    uint32_t seq = 0; // number of the next chunk
+    // groups of targets in one X-row of cells, at most 61 cells apart
+    uint64_t todo = __builtin_amdgcn_ballot_w64(active);
+    while (todo) {
+        const int first = __builtin_ctzll(todo);
+        const int32_t grow = __builtin_amdgcn_readlane(row, first);
+        const int32_t cA = __builtin_amdgcn_readlane(ix, first);
+        const uint64_t grp = __builtin_amdgcn_ballot_w64(active && row == grow && ix >= cA && ix - cA <= 60) & todo;
+        todo &= ~grp;
+        const bool mine = (grp >> lane) & 1ull;
+        const int last = 63 - __builtin_clzll(grp);
+        const int32_t cB = __builtin_amdgcn_readlane(ix, last);
+        const int32_t giz = grow / a.ny, giy = grow - giz * a.ny;
+        cxi = (float)(ix - cA);
+        // the nine neighbour rows' source ranges (lane r: dy = r % 3 - 1, dz = r / 3 - 1)
+        int32_t j0v = 0, j3v = 0;
+        if (lane < 9) {
+            const int32_t cy = giy + lane % 3 - 1, cz = giz + lane / 3 - 1;
+            if (cy >= 0 && cy < a.ny && cz >= 0 && cz < a.nz) {
+                const int64_t rb = (int64_t)a.nx * (cy + (int64_t)a.ny * cz);
+                j0v = a.off[rb + max(cA - 1, 0)];
+                j3v = a.off[rb + min(cB + 2, a.nx)];
+            }
+        }
+        // rows that no target of the group reaches
+        uint32_t rows = 0;
+#pragma unroll
+        for (int r = 0; r < 9; ++r) {
+            const int dy = r % 3 - 1, dz = r / 3 - 1;
+            const float gyz = (dy < 0 ? gyl : (dy > 0 ? gyr : 0.f)) + (dz < 0 ? gzl : (dz > 0 ? gzr : 0.f));
+            rows |= (__builtin_amdgcn_ballot_w64(mine && gyz < reach2) != 0 ? 1u : 0u) << r;
+        }
+        // the frame of the test, in cells: X from the middle of the group, Y and
+        // Z from the middle of the group's row
+        const float mid = 0.5f * (float)(cB - cA + 1);
+        const float half = mid + 1.0f;
+        const float thr = a.k.rc2_cells + 1.52587890625e-5f * (half * half + 5.5f);
+        const float xs = mine ? __builtin_fmaf(xi, iw, cxi - mid) : 0.0f;
+        const float ys = mine ? __builtin_fmaf(yi, iw, -0.5f) : 0.0f;
+        const float zs = mine ? __builtin_fmaf(zi, iw, -0.5f) : 0.0f;
+        v4h bop[4];
+        int32_t bmin[4], bmax[4];
+        {
+            const uint32_t vx = split_f16(-2.0f * xs), vy = split_f16(-2.0f * ys), vz = split_f16(-2.0f * zs);
+            const uint32_t vc = split_f16(mine ? sq_dist(xs, ys, zs) - thr : 60000.0f);
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const int src = (16 * b + n) * 4;
+                const uint32_t sx = __builtin_amdgcn_ds_bpermute(src, vx), sy = __builtin_amdgcn_ds_bpermute(src, vy),
+                               sz = __builtin_amdgcn_ds_bpermute(src, vz), c = __builtin_amdgcn_ds_bpermute(src, vc);
+                const uint32_t v = kk == 0 ? sx : (kk == 1 ? sy : sz);
+                const uint32_t hi = kk < 3 ? (v & 0xffffu) * 0x10001u : 0x3c003c00u;
+                const uint32_t lo = kk < 3 ? v >> 16 : 0u;
+                const uint32_t cc = kk == 0 ? c << 16 : (kk == 1 ? c & 0xffff0000u : 0u);
+                bop[b] = __builtin_bit_cast(v4h, make_uint2(hi, lo | cc));
+                // the cells of the block's targets (none: an empty range)
+                const uint32_t g16 = (uint32_t)(grp >> (16 * b)) & 0xffffu;
+                bmin[b] = g16 ? __builtin_amdgcn_readlane(ix, 16 * b + __builtin_ctz(g16 | 0x10000u)) : 0x7fffffff;
+                bmax[b] = g16 ? __builtin_amdgcn_readlane(ix, 16 * b + 31 - __builtin_clz(g16 | 1u)) : -2;
+            }
+        }
+
+        // the chunks, row by row; a chunk's sources are loaded one chunk ahead
+        int r = -1;
+        int32_t jc = 0, jend = 0;
+        auto next = [&]() {
+            while (jc >= jend) {
+                if (++r == 9) return false;
+                if (!((rows >> r) & 1u)) continue;
+                jc = __builtin_amdgcn_readlane(j0v, r);
+                jend = __builtin_amdgcn_readlane(j3v, r);
+            }
+            return true;
+        };
+        bool have = next();
+        float4 nq = make_float4(0.f, 0.f, 0.f, 0.f);
+        int32_t ncell = 0;
+        if (have) {
+            const int32_t j = min(jc + lane, jend - 1);
+            nq = a.p4[j];
+            ncell = a.cell[j];
+        }
+        while (have) {
+            const float4 q = nq;
+            const int32_t cj = jc, len = min(64, jend - jc), dy = r % 3 - 1, dz = r / 3 - 1;
+            const int32_t cx = ncell - a.nx * (giy + dy + a.ny * (giz + dz));
+            jc += 64;
+            have = next();
+            if (have) {
+                const int32_t j = min(jc + lane, jend - 1);
+                nq = a.p4[j];
+                ncell = a.cell[j];
+            }
+            // a ring slot that no lane still refers to
+            const uint32_t old = m != 0 ? seq_m : ids & 255u;
+            if (__any(((m != 0) | (cnt > 0)) & (((seq - old) & 255u) >= (uint32_t)RING))) {
+                bool behind;
+                do {
+                    round();
+                    const uint32_t o = m != 0 ? seq_m : ids & 255u;
+                    behind = ((m != 0) | (cnt > 0)) & (((seq - o) & 255u) >= (uint32_t)RING);
+                } while (__any(behind));
+            }
+            const uint32_t slot = seq & (RING - 1);
+            const float fcx = (float)(cx - cA);
+            rp[slot * 64 + lane] = q;
+            rcx[slot * 64 + lane] = fcx;
+            if (lane == 0) ring_row[wave][slot] = make_float2((float)dy, (float)dz);
+            {
+                const float sx = __builtin_fmaf(q.x, iw, fcx - mid), sy = __builtin_fmaf(q.y, iw, (float)dy - 0.5f),
+                            sz = __builtin_fmaf(q.z, iw, (float)dz - 0.5f);
+                opnd[wave][0][lane] = split_f16(sx);
+                opnd[wave][1][lane] = split_f16(sy);
+                opnd[wave][2][lane] = split_f16(sz);
+                opnd[wave][3][lane] = split_f16(sq_dist(sx, sy, sz));
+            }
+            __builtin_amdgcn_wave_barrier();
+            const int32_t cfirst = __builtin_amdgcn_readlane(cx, 0), clast = __builtin_amdgcn_readlane(cx, len - 1);
+            v4h aop[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const uint32_t v = acomp[4 * s];
+                aop[s] = __builtin_bit_cast(v4h, make_uint2(v, (v & 0xffffu) | 0x3c000000u));
+            }
+            uint32_t rr[4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                rr[b] = 0;
+                if (cfirst <= bmax[b] + 1 && clast >= bmin[b] - 1) {
+#pragma unroll
+                    for (int s = 3; s >= 0; --s) {
+                        const v4f d = __builtin_amdgcn_mfma_f32_16x16x16f16(aop[s], bop[b], v4f{0.f, 0.f, 0.f, 0.f}, 0,
+                                                                            0, 0);
+#pragma unroll
+                        for (int i = 3; i >= 0; --i)
+                            rr[b] = __builtin_amdgcn_alignbit(rr[b], __float_as_uint(d[i]), 31);
+                    }
+                }
+            }
+            const auto s02 = __builtin_amdgcn_permlane32_swap(rr[0], rr[2], false, false);
+            const auto s13 = __builtin_amdgcn_permlane32_swap(rr[1], rr[3], false, false);
+            const auto g01 = __builtin_amdgcn_permlane16_swap(s02[0], s13[0], false, false);
+            const auto g23 = __builtin_amdgcn_permlane16_swap(s02[1], s13[1], false, false);
+            uint64_t w = (uint64_t)(g01[0] | (g01[1] << 16)) | ((uint64_t)(g23[0] | (g23[1] << 16)) << 32);
+            if (len < 64) w &= (1ull << len) - 1ull;
+            if (dy == 0 && dz == 0) { // the target itself
+                const uint32_t o = (uint32_t)(k - cj);
+                w &= o < 64u ? ~(1ull << o) : ~0ull;
+            }
+            myq[((head + cnt) & (Q - 1)) * 64] = make_uint2((uint32_t)w, (uint32_t)(w >> 32));
+            ids |= w != 0 ? (seq & 255u) << (8 * cnt) : 0u;
+            cnt += w != 0 ? 1 : 0;
+            ++seq;
+            if (__any(cnt == Q)) { // until every lane has a free slot
+                do round(); while (__any(cnt == Q));
+            }
+        }
+        if (__any((m != 0) | (cnt > 0))) {
+            do round(); while (__any((m != 0) | (cnt > 0)));
+        }
+    }
+    if (active) write_target(a, k, T);
+    if (INV) {
+        long long cn = 0;
+        double nx = 0, ny = 0, nz = 0, sc = 0, rs = 0;
+        if (active) target_invariants(T, wi, cn, nx, ny, nz, sc, rs);
+        reduce_invariants(a, lb, cn, nx, ny, nz, sc, rs);
+    }
 }
 
 // ------------------------------------------------------------------ LDS tiles
@@ -1704,7 +1870,6 @@ const TileCfg kTiles[] = {
 #endif
 constexpr int kFifo = PI_FIFO_DEPTH; // pair queue entries per lane
 constexpr int kCellCap = 256;       // cell-SM: particles per LDS fill
-constexpr int kStreamId = 9; // organisation id of the FIFO stream sweep
 constexpr int kMaxOrgId = 25; // organisation ids are 0 .. kMaxOrgId
 
 // Workgroups of the dense pass that follows a single-system tile launch: a
@@ -1830,12 +1995,12 @@ void launch_sweep(pi_ctx *ctx, int tile_id, const SweepArgs &a, hipStream_t s, u
     case 15: launch_cell<kCellCap, PREC, INV, BATCH>(ctx, "k_sweep_cell<2,16>", 2, 16, a, s, nblk); break;
     case 16: launch_cell<kCellCap, PREC, INV, BATCH>(ctx, "k_sweep_cell<2,32>", 2, 32, a, s, nblk); break;
     case 17: launch_cell<kCellCap, PREC, INV, BATCH>(ctx, "k_sweep_cell<2,64>", 2, 64, a, s, nblk); break;
-    case kStreamId:
+    case kOrgStream:
         if (!BATCH) {
             nblk = (unsigned)((a.n + kBlock - 1) / kBlock);
             if (nblk == 0) nblk = 1;
         }
-        PI_LAUNCH(ctx, "k_sweep_stream", (k_sweep_stream<kFifo, PREC, INV, BATCH>), dim3(nblk), dim3(kBlock), 0, s,
+        PI_LAUNCH(ctx, "k_sweep_stream", (k_sweep_stream<2, 4, PREC, INV, BATCH>), dim3(nblk), dim3(kBlock), 0, s,
                   a);
         break;
     default:
@@ -1892,18 +2057,19 @@ bool halo_fits(int id, double ppc)
 // Static rule: the largest sub-box whose halo fits (its targets then come
 // nearest to one per thread): 6x6x6 up to about 1.2 per cell, 5x5x4 to 2.0,
 // 5x4x4 to 3.3, 5x4x3 to 4.1, 4x4x3 to 5.3, 4x3x3 to 6.8, 3x3x3 to 9.6, 3x3x2 to
-// 12, 3x2x2 to 15, then no LDS.  Sweep times on uniform systems of 80^3 or
+// 12, 3x2x2 to 15, then the stream.  Sweep times on uniform systems of 80^3 or
 // 48^3 cells, the rule's pick against the no-LDS walk and the next best tile:
 // 2 per cell 83 us (no LDS 119, 5x4x4 94), 3 139 (212, 4x4x4 151), 4 212 (328,
 // 4x4x4 224), 6 108 (174, 4x4x2 110), 8 153 (265, 4x4x2 175), 12 296 (510,
-// 3x2x2 360).
+// 3x2x2 360); the stream against no LDS at 24 per cell 1154 us (1651), 32 1924
+// (2743).
 const int kStaticTiles[] = {5, 18, 19, 20, 21, 22, 23, 24, 25};
 
 int pick_tile_default(double ppc)
 {
     for (const int id : kStaticTiles)
         if (halo_fits(id, ppc)) return id;
-    return 0;
+    return kOrgStream;
 }
 
 } // namespace
@@ -1925,7 +2091,7 @@ bool pi_tile_shape(int tile_id, int *tx, int *ty, int *tz)
 bool pi_org_valid(int id)
 {
     int tx, ty, tz;
-    return id == 0 || id == kStreamId || pi_tile_shape(id, &tx, &ty, &tz);
+    return id == 0 || id == kOrgStream || pi_tile_shape(id, &tx, &ty, &tz);
 }
 
 // The explicit options (organisation and tile shape) that run organisation
@@ -1940,7 +2106,7 @@ void pi_tile_opts(int tile, pi_interact_opts *out)
         out->tile[1] = ty;
         out->tile[2] = tz;
     } else {
-        out->sweep = tile == kStreamId ? PI_SWEEP_STREAM : PI_SWEEP_NOLDS;
+        out->sweep = tile == kOrgStream ? PI_SWEEP_STREAM : PI_SWEEP_NOLDS;
     }
 }
 
@@ -1949,7 +2115,7 @@ void pi_tile_opts(int tile, pi_interact_opts *out)
 int pi_pick_tile(const pi_interact_opts &o, double ppc)
 {
     if (o.sweep == PI_SWEEP_NOLDS) return 0;
-    if (o.sweep == PI_SWEEP_STREAM) return kStreamId;
+    if (o.sweep == PI_SWEEP_STREAM) return kOrgStream;
     if (o.sweep == PI_SWEEP_CELL) {
         if (o.tile[0] > 0) {
             for (const TileCfg &t : kTiles)
@@ -1974,7 +2140,7 @@ int pi_pick_tile(const pi_interact_opts &o, double ppc)
         }
         if (o.sweep == PI_SWEEP_PENCIL) return halo_fits(1, ppc) ? 1 : (halo_fits(2, ppc) ? 2 : 3);
         const int id = pick_tile_default(ppc);
-        return id > 0 ? id : kStaticTiles[sizeof(kStaticTiles) / sizeof(kStaticTiles[0]) - 1];
+        return id != kOrgStream ? id : kStaticTiles[sizeof(kStaticTiles) / sizeof(kStaticTiles[0]) - 1];
     }
     return pick_tile_default(ppc);
 }
@@ -2075,7 +2241,7 @@ uint64_t tune_key(int prec, int64_t n, double ppc, bool batch)
 // 80 of its 256 threads.
 bool worth_timing(int id, double ppc)
 {
-    if (id <= 0 || id == kStreamId) return true;
+    if (id <= 0 || id == kOrgStream) return true;
     const TileCfg &t = tile_cfg(id);
     if (t.id != id) return true;
     if (t.sweep == PI_SWEEP_SUBBOX)
@@ -2223,7 +2389,7 @@ namespace {
 int64_t sweep_blocks(int tile, int64_t n, int32_t nx, int32_t ny, int32_t nz)
 {
     int tx = 0, ty = 0, tz = 0;
-    if (tile > 0 && tile != kStreamId && pi_tile_shape(tile, &tx, &ty, &tz)) {
+    if (tile > 0 && tile != kOrgStream && pi_tile_shape(tile, &tx, &ty, &tz)) {
         if (tile_cfg(tile).sweep == PI_SWEEP_CELL) // runs of tx cells, after the no-LDS walk's records
             return (int64_t)((nx + tx - 1) / tx) * ny * nz + (ty > 1 ? (n + kBlock - 1) / kBlock : 0);
         return (int64_t)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty) * ((nz + tz - 1) / tz) + dense_blocks(n);
