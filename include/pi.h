@@ -286,7 +286,9 @@ pi_status pi_interact_noalloc(pi_ctx *ctx, const pi_cells *cells, const pi_inter
  * fits, else 2) or PI_SWEEP_AUTO (with the timed tuner mode, every
  * organisation is timed once per size and occupancy class and the fastest
  * reused, as in pi_interact; in static mode: no LDS from 6 particles per
- * cell up, else the widest sub-box whose halo fits).  tile[0] = 0 sizes a
+ * cell up, or the rows around a wavefront's targets staged in LDS from 20 per
+ * cell and 2^19 particles up (not the high-FLOP kernel), else the widest sub-box
+ * whose halo fits).  tile[0] = 0 sizes a
  * tile for about 384 targets, within the LDS capacity and the grid, and
  * shortens it while the launch has fewer than two workgroups per compute
  * unit; with AUTO a tile[0] beyond the chosen shape's limit is clamped to it

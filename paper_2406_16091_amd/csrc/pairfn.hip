@@ -14,7 +14,8 @@
 // the organisations give bit-identical results on lattice inputs.
 //
 // Organisations: one thread per target with sources read through the caches
-// (Algorithm 1, Par-Part-NoLoop), and LDS tiles -- X-pencils (Sec. 5.2,
+// (Algorithm 1, Par-Part-NoLoop) or, for dense cells, staged in LDS a row at a
+// time, and LDS tiles -- X-pencils (Sec. 5.2,
 // Algorithm 5) and 2 x 2 column sub-boxes (Sec. 5.1) -- whose length along X
 // is a launch parameter, so that the staged halo fits the LDS area at any
 // occupancy (the paper shortens its pencils the same way as the particles
@@ -31,6 +32,7 @@
 namespace {
 
 constexpr int kBlock = 256;
+constexpr int kPfChunk = 384; // sources of an X-row that a wavefront stages at once
 constexpr int kPfCap = 3072;  // staged particles per tile (48 KB)
 // halo cells along X (tile length + 2) for t x t columns
 constexpr int pf_max_hx(int t) { return t == 1 ? 256 : (t == 2 ? 160 : 96); }
@@ -58,7 +60,8 @@ struct PfArgs {
     PfConst k;
 };
 
-// One pair term K and (with INV) its magnitude scale A.
+// One pair term and (with INV) its magnitude scale A, both without the factor
+// 4 e0 (4 |e0|) of the Lennard-Jones kernels, which multiplies the sums.
 template <int KF, bool INV>
 __device__ __forceinline__ float pf_term(float dx, float dy, float dz, const PfConst &p, float &A)
 {
@@ -69,13 +72,21 @@ __device__ __forceinline__ float pf_term(float dx, float dy, float dz, const PfC
     const float s2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, __builtin_fmaf(dx, dx, p.eps2)));
     const float u = p.sigma2 * __builtin_amdgcn_rcpf(s2);
     const float u3 = u * u * u;
-    float K = p.four_e0 * __builtin_fmaf(u3, u3, -u3);
-    if (INV) A = p.four_abs_e0 * __builtin_fmaf(u3, u3, u3);
+    float K = __builtin_fmaf(u3, u3, -u3);
+    if (INV) A = __builtin_fmaf(u3, u3, u3);
     if (KF == PI_PAIRFN_HIGHFLOP) {
 #pragma unroll
         for (int t = 0; t < 75; ++t) K = __builtin_fmaf(K, p.a, p.b);
     }
     return K;
+}
+
+// The constants in vector registers: a product or sum with a scalar register
+// operand issues in 4.4 cycles here, with vector registers only in 2.7.
+__device__ __forceinline__ PfConst pf_in_vgprs(PfConst p)
+{
+    asm("" : "+v"(p.sigma2), "+v"(p.eps2), "+v"(p.a), "+v"(p.b));
+    return p;
 }
 
 // Scalar accumulators: plain FP32, or Kahan-compensated FP32 (the same
@@ -109,8 +120,11 @@ struct PfTarget {
     {
         float A = 0.f;
         acc.add(pf_term<KF, INV>(dx, dy, dz, p, A));
-        count += 1;
         if (INV) ascale += A;
+    }
+    __device__ __forceinline__ float value(const PfConst &p) const
+    {
+        return KF == PI_PAIRFN_LOWFLOP ? acc.r() : p.four_e0 * acc.r();
     }
 };
 
@@ -118,19 +132,45 @@ template <int KF, int PREC, bool INV>
 __device__ __forceinline__ void pf_write(const PfArgs &a, int32_t k, const PfTarget<KF, PREC, INV> &T)
 {
     const int32_t o = a.orig_order ? a.perm[k] : k;
-    a.v[o] = T.acc.r();
+    a.v[o] = T.value(a.k);
     if (a.count) a.count[o] = T.count;
 }
 
-// The target's 27 cells from global memory, each neighbour X-row as one
-// index range over its (up to) three cells; the two inner cell boundaries
-// give each source's shift along X.
+// Sources [j, jz) of one cell, four at a time (their loads are in flight
+// together, and the loop's own instructions are paid once).
 template <int KF, int PREC, bool INV>
+__device__ __forceinline__ void pf_walk_cell(const float4 *p4, int32_t j, int32_t jz, float tx, float ty,
+                                             float tz, const PfConst &p, PfTarget<KF, PREC, INV> &T)
+{
+    const float4 *s = p4 + j;
+    int32_t left = jz - j;
+    for (; left >= 4; left -= 4, s += 4) {
+        const float4 q0 = s[0], q1 = s[1], q2 = s[2], q3 = s[3];
+        T.cand(tx - q0.x, ty - q0.y, tz - q0.z, p);
+        T.cand(tx - q1.x, ty - q1.y, tz - q1.z, p);
+        T.cand(tx - q2.x, ty - q2.y, tz - q2.z, p);
+        T.cand(tx - q3.x, ty - q3.y, tz - q3.z, p);
+    }
+    for (; left > 0; --left, ++s) {
+        const float4 q = *s;
+        T.cand(tx - q.x, ty - q.y, tz - q.z, p);
+    }
+}
+
+// The target's 27 cells from global memory.  CELLS: cell by cell, so that the
+// inner loop is the pair term and the loads; the target's own cell alone tests
+// for the target itself.  Otherwise each neighbour X-row is one range over its
+// three cells, with the shift along X selected per source: four more
+// instructions on every candidate, but a wavefront's loop then runs as long as
+// its longest row instead of its longest cell three times.
+template <bool CELLS, int KF, int PREC, bool INV>
 __device__ __forceinline__ void pf_walk_global(const PfArgs &a, int32_t k, int32_t ix, int32_t iy, int32_t iz,
                                                float xi, float yi, float zi, PfTarget<KF, PREC, INV> &T)
 {
+    const PfConst p = pf_in_vgprs(a.k);
     const float W = a.k.w;
     const float xm = xi - (float)(-1) * W, xp = xi - (float)(1) * W;
+    int32_t count = -1; // not the target itself
     for (int dz = -1; dz <= 1; ++dz) {
         const int32_t cz = iz + dz;
         if (cz < 0 || cz >= a.nz) continue;
@@ -143,25 +183,41 @@ __device__ __forceinline__ void pf_walk_global(const PfArgs &a, int32_t k, int32
             const int32_t b1 = a.off[rb], b2 = a.off[rb + 1];
             const int32_t j0 = ix > 0 ? a.off[rb - 1] : b1;
             const int32_t j3 = ix + 1 < a.nx ? a.off[rb + 2] : b2;
-            for (int32_t j = j0; j < j3; ++j) {
-                const float tx = j < b1 ? xm : (j < b2 ? xi : xp);
-                const float4 s = a.p4[j];
-                if (j != k) T.cand(tx - s.x, ty - s.y, tz - s.z, a.k);
+            count += j3 - j0;
+            if (!CELLS) {
+                for (int32_t j = j0; j < j3; ++j) {
+                    const float tx = j < b1 ? xm : (j < b2 ? xi : xp);
+                    const float4 s = a.p4[j];
+                    if (j != k) T.cand(tx - s.x, ty - s.y, tz - s.z, p);
+                }
+                continue;
             }
+            pf_walk_cell(a.p4, j0, b1, xm, ty, tz, p, T);
+            if (dy == 0 && dz == 0) {
+                for (int32_t j = b1; j < b2; ++j) {
+                    const float4 s = a.p4[j];
+                    if (j != k) T.cand(xi - s.x, ty - s.y, tz - s.z, p);
+                }
+            } else {
+                pf_walk_cell(a.p4, b1, b2, xi, ty, tz, p, T);
+            }
+            pf_walk_cell(a.p4, b2, j3, xp, ty, tz, p, T);
         }
     }
+    T.count = count;
 }
 
 template <int KF, int PREC, bool INV>
-__device__ __forceinline__ void pf_fold(const PfTarget<KF, PREC, INV> &T, long long &cnt, double &sc, double &rs)
+__device__ __forceinline__ void pf_fold(const PfArgs &a, const PfTarget<KF, PREC, INV> &T, long long &cnt, double &sc,
+                                        double &rs)
 {
     cnt += T.count;
-    sc += (double)T.ascale;
-    rs += (double)T.acc.r();
+    sc += (double)(KF == PI_PAIRFN_LOWFLOP ? T.ascale : a.k.four_abs_e0 * T.ascale);
+    rs += (double)T.value(a.k);
 }
 
 // ------------------------------------------------------------------ no LDS
-template <int KF, int PREC, bool INV>
+template <bool CELLS, int KF, int PREC, bool INV>
 __global__ __launch_bounds__(kBlock) void k_pairfn_nolds(PfArgs a)
 {
     const uint32_t lb = xcd_remap(blockIdx.x, gridDim.x);
@@ -174,9 +230,110 @@ __global__ __launch_bounds__(kBlock) void k_pairfn_nolds(PfArgs a)
         const int32_t ix = c % a.nx, iy = (c / a.nx) % a.ny, iz = c / (a.nx * a.ny);
         const float4 pk = a.p4[k];
         PfTarget<KF, PREC, INV> T;
-        pf_walk_global(a, k, ix, iy, iz, pk.x, pk.y, pk.z, T);
+        pf_walk_global<CELLS>(a, k, ix, iy, iz, pk.x, pk.y, pk.z, T);
         pf_write(a, k, T);
-        if (INV) pf_fold(T, cnt, sc, rs);
+        if (INV) pf_fold(a, T, cnt, sc, rs);
+    }
+    if (INV) block_reduce_partial(a.partials + lb, cnt, 0.0, 0.0, 0.0, sc, rs);
+}
+
+// ------------------------------------------------------------------ staged rows
+// One thread per target as in the no-LDS walk, each wavefront on its own, with
+// the sources of one neighbour X-row at a time -- the cells around the
+// wavefront's targets in it, one contiguous range -- staged in LDS by the
+// wavefront, up to kPfChunk at once.  The dense case: at 100 per cell the no-LDS
+// walk is bound by its vector loads (the low-FLOP kernel takes as long as
+// Lennard-Jones: every lane fetches 16 bytes per candidate through the L1), and
+// here a source is fetched once per 64 targets and read from LDS, so that the
+// pair term's VALU issue bounds it (about 39 of the 41 cycles per candidate that
+// its instructions take).  The same sources, roundings and order as the no-LDS
+// walk: bitwise the same outputs.  Lennard-Jones, 32^3 cells: 100 per cell 4.23 ms
+// by rows from global memory, 3.85 cell by cell, 2.47 here; 30 per cell 426, 440
+// and 320 us; 10 per cell 73, 69 and 83 us.  (256 staged sources: 2.86 ms at 100
+// per cell; 512: 2.53.)
+template <int KF, int PREC, bool INV>
+__global__ __launch_bounds__(kBlock) void k_pairfn_rows(PfArgs a)
+{
+    __shared__ float4 stage[kBlock / 64][kPfChunk];
+    const uint32_t lb = xcd_remap(blockIdx.x, gridDim.x);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int32_t k = (int32_t)(lb * kBlock) + tid;
+    const bool active = k < min(a.off[a.nc], a.n);
+    float4 *st = stage[__builtin_amdgcn_readfirstlane(tid >> 6)];
+    const PfConst p = pf_in_vgprs(a.k);
+    const float W = a.k.w;
+    float xi = 0.f, yi = 0.f, zi = 0.f;
+    int32_t ix = 0, row = -1;
+    if (active) {
+        const int32_t c = a.cell[k];
+        row = c / a.nx;
+        ix = c - row * a.nx;
+        const float4 pk = a.p4[k];
+        xi = pk.x;
+        yi = pk.y;
+        zi = pk.z;
+    }
+    const float xm = xi - (float)(-1) * W, xp = xi - (float)(1) * W;
+    PfTarget<KF, PREC, INV> T;
+    int32_t count = -1; // not the target itself
+    // the wavefront's targets, an X-row of cells at a time
+    uint64_t todo = __builtin_amdgcn_ballot_w64(active);
+    while (todo) {
+        const int first = __builtin_ctzll(todo);
+        const int32_t grow = __builtin_amdgcn_readlane(row, first);
+        const uint64_t grp = __builtin_amdgcn_ballot_w64(row == grow) & todo;
+        todo &= ~grp;
+        const bool mine = (grp >> lane) & 1ull;
+        const int32_t cA = __builtin_amdgcn_readlane(ix, first);
+        const int32_t cB = __builtin_amdgcn_readlane(ix, 63 - __builtin_clzll(grp));
+        const int32_t giz = grow / a.ny, giy = grow - giz * a.ny;
+        for (int dz = -1; dz <= 1; ++dz) {
+            const int32_t cz = giz + dz;
+            if (cz < 0 || cz >= a.nz) continue;
+            const float tz = zi - (float)dz * W;
+            for (int dy = -1; dy <= 1; ++dy) {
+                const int32_t cy = giy + dy;
+                if (cy < 0 || cy >= a.ny) continue;
+                const float ty = yi - (float)dy * W;
+                const int64_t rb0 = (int64_t)a.nx * (cy + (int64_t)a.ny * cz);
+                const int32_t J0 = a.off[rb0 + max(cA - 1, 0)], J3 = a.off[rb0 + min(cB + 2, a.nx)];
+                int32_t b0 = J0, b1 = J0, b2 = J0, b3 = J0;
+                if (mine) {
+                    const int32_t *o = a.off + rb0 + ix;
+                    b1 = o[0];
+                    b2 = o[1];
+                    b0 = ix > 0 ? o[-1] : b1;
+                    b3 = ix + 1 < a.nx ? o[2] : b2;
+                    count += b3 - b0;
+                }
+                for (int32_t P = J0; P < J3; P += kPfChunk) {
+                    const int32_t len = min(kPfChunk, J3 - P);
+                    for (int32_t i = lane; i < len; i += 64) st[i] = a.p4[P + i];
+                    __builtin_amdgcn_wave_barrier(); // (one wavefront: its LDS accesses are in order)
+                    const int32_t c0 = min(max(b0 - P, 0), len), c1 = min(max(b1 - P, 0), len),
+                                  c2 = min(max(b2 - P, 0), len), c3 = min(max(b3 - P, 0), len);
+                    pf_walk_cell(st, c0, c1, xm, ty, tz, p, T);
+                    if (dy == 0 && dz == 0) {
+                        const int32_t self = k - P;
+                        for (int32_t j = c1; j < c2; ++j) {
+                            const float4 s = st[j];
+                            if (j != self) T.cand(xi - s.x, ty - s.y, tz - s.z, p);
+                        }
+                    } else {
+                        pf_walk_cell(st, c1, c2, xi, ty, tz, p, T);
+                    }
+                    pf_walk_cell(st, c2, c3, xp, ty, tz, p, T);
+                    __builtin_amdgcn_wave_barrier();
+                }
+            }
+        }
+    }
+    long long cnt = 0;
+    double sc = 0.0, rs = 0.0;
+    if (active) {
+        T.count = count;
+        pf_write(a, k, T);
+        if (INV) pf_fold(a, T, cnt, sc, rs);
     }
     if (INV) block_reduce_partial(a.partials + lb, cnt, 0.0, 0.0, 0.0, sc, rs);
 }
@@ -269,9 +426,9 @@ __global__ __launch_bounds__(kBlock) void k_pairfn_tile(PfArgs a, int32_t tx_len
             const int32_t ix = a.cell[k] - a.nx * (y + a.ny * z);
             const float4 pk = a.p4[k];
             PfTarget<KF, PREC, INV> T;
-            pf_walk_global(a, k, ix, y, z, pk.x, pk.y, pk.z, T);
+            pf_walk_global<false>(a, k, ix, y, z, pk.x, pk.y, pk.z, T);
             pf_write(a, k, T);
-            if (INV) pf_fold(T, icnt, isc, irs);
+            if (INV) pf_fold(a, T, icnt, isc, irs);
         }
         if (INV) block_reduce_partial(a.partials + lb, icnt, 0.0, 0.0, 0.0, isc, irs);
         return;
@@ -306,6 +463,7 @@ __global__ __launch_bounds__(kBlock) void k_pairfn_tile(PfArgs a, int32_t tx_len
     __syncthreads();
 
     // 4. targets, one per thread per round
+    const PfConst p = pf_in_vgprs(a.k);
     for (int32_t f = tid; f < ntarget; f += kBlock) {
         const int tr = target_row(f);
         const int32_t k = tfirst[tr] + (f - tstart[tr]);
@@ -319,18 +477,21 @@ __global__ __launch_bounds__(kBlock) void k_pairfn_tile(PfArgs a, int32_t tx_len
         const int jl = ix > 0 ? jc - 1 : jc;
         const int jr = ix + 1 < a.nx ? jc + 2 : jc + 1;
         PfTarget<KF, PREC, INV> T;
+        int32_t count = -1; // not the target itself
         for (int dz = -1; dz <= 1; ++dz) {
             for (int dy = -1; dy <= 1; ++dy) {
                 const int hr = own + dy + HY * dz; // rows outside the grid are empty
-                const int32_t s1 = cs[hr][jr];
-                for (int32_t j = cs[hr][jl]; j < s1; ++j) {
+                const int32_t s0 = cs[hr][jl], s1 = cs[hr][jr];
+                count += s1 - s0;
+                for (int32_t j = s0; j < s1; ++j) {
                     const float4 s = sp[j];
-                    if (j != self) T.cand(t.x - s.x, t.y - s.y, t.z - s.z, a.k);
+                    if (j != self) T.cand(t.x - s.x, t.y - s.y, t.z - s.z, p);
                 }
             }
         }
+        T.count = count;
         pf_write(a, k, T);
-        if (INV) pf_fold(T, icnt, isc, irs);
+        if (INV) pf_fold(a, T, icnt, isc, irs);
     }
     if (INV) block_reduce_partial(a.partials + lb, icnt, 0.0, 0.0, 0.0, isc, irs);
 }
@@ -349,8 +510,12 @@ int pf_fit_length(int t, double ppc)
     return 0;
 }
 
-// An organisation of the pair-kernel sweep: no LDS (t = 0), or tiles of
-// len x t x t target cells (t = 1: X-pencil; t = 2, 4: sub-boxes).
+// An organisation of the pair-kernel sweep: no LDS (t = 0), staged rows (t =
+// kPfRows, taken by AUTO only), or tiles of len x t x t target cells (t = 1:
+// X-pencil; t = 2, 4: sub-boxes).
+constexpr int kPfRows = 8;
+constexpr bool pf_tiled(int t) { return t > 0 && t != kPfRows; }
+
 struct PfOrg {
     int t;
     int32_t len;
@@ -359,7 +524,7 @@ struct PfOrg {
 // Workgroups of one launch.
 int64_t pf_blocks(const PfOrg &g, const PfArgs &a)
 {
-    if (g.t == 0) {
+    if (!pf_tiled(g.t)) {
         const int64_t b = ((int64_t)a.n + kBlock - 1) / kBlock;
         return b > 0 ? b : 1;
     }
@@ -388,7 +553,21 @@ template <int KF, int PREC, bool INV>
 void pf_launch(pi_ctx *ctx, const PfOrg &g, const PfArgs &a, hipStream_t s, unsigned nblk)
 {
     if (g.t == 0) {
-        PI_LAUNCH(ctx, "k_pairfn_nolds", (k_pairfn_nolds<KF, PREC, INV>), dim3(nblk), dim3(kBlock), 0, s, a);
+        // Cell by cell from where its shorter inner loop outweighs the longer trip
+        // counts (row walk and cell walk, 32^3 cells): Lennard-Jones 1 per cell 16.9
+        // and 18.5 us, 3 per cell 26.8 and 24.6; high-FLOP 3 per cell 60.6 and 67.1, 6
+        // per cell 126.8 and 118, 10 per cell 289 and 236.
+        const double ppc = a.nc > 0 ? (double)a.n / (double)a.nc : 0.0;
+        if (ppc >= (KF == PI_PAIRFN_HIGHFLOP ? 6.0 : 3.0))
+            PI_LAUNCH(ctx, "k_pairfn_nolds", (k_pairfn_nolds<true, KF, PREC, INV>), dim3(nblk), dim3(kBlock), 0, s,
+                      a);
+        else
+            PI_LAUNCH(ctx, "k_pairfn_nolds", (k_pairfn_nolds<false, KF, PREC, INV>), dim3(nblk), dim3(kBlock), 0, s,
+                      a);
+        return;
+    }
+    if (g.t == kPfRows) {
+        PI_LAUNCH(ctx, "k_pairfn_rows", (k_pairfn_rows<KF, PREC, INV>), dim3(nblk), dim3(kBlock), 0, s, a);
         return;
     }
     const int32_t ntx = (a.nx + g.len - 1) / g.len;
@@ -425,13 +604,18 @@ void pf_dispatch(pi_ctx *ctx, int kernel, int prec, bool inv, const PfOrg &g, co
 #undef PF_PREC
 }
 
-// Static rule for AUTO: no LDS from 6 particles per cell up (every candidate
-// is evaluated, so the sweep is bound by its arithmetic there, and a staged
-// halo holds too few targets per tile), else the widest sub-box whose halo
-// fits the LDS area.
-int pf_static_t(double ppc)
+// Whether the staged rows can win: dense cells, and a pair term short enough for
+// the no-LDS walk to be bound by its loads.
+bool pf_rows_pay(int kernel, double ppc) { return kernel != PI_PAIRFN_HIGHFLOP && ppc >= 20.0; }
+
+// Static rule for AUTO: from 6 particles per cell up no tiles (every candidate
+// is evaluated, and a staged halo holds too few targets per tile): staged rows
+// where they pay and the launch has enough wavefronts for their lower occupancy
+// (16^3 cells of 30, 480 workgroups: no LDS 75 us, rows 93), else no LDS; below,
+// the widest sub-box whose halo fits the LDS area.
+int pf_static_t(int kernel, int64_t n, double ppc)
 {
-    if (ppc >= 6.0) return 0;
+    if (ppc >= 6.0) return pf_rows_pay(kernel, ppc) && n >= (1 << 19) ? kPfRows : 0;
     if (pf_fit_length(4, ppc) > 0) return 4;
     if (pf_fit_length(2, ppc) > 0) return 2;
     return 0;
@@ -459,14 +643,15 @@ int pf_time_orgs(pi_ctx *ctx, int kernel, int prec, bool inv, int first, const P
     }
     const int was = ctx->timing_on;
     ctx->timing_on = 0;
-    const int order[5] = {first, 0, 1, 2, 4};
+    const int order[6] = {first, 0, 1, 2, 4, kPfRows};
     int best = -1;
     float best_ms = 0.f;
-    for (int i = 0; i < 5; ++i) {
+    for (int i = 0; i < 6; ++i) {
         const int t = order[i];
         if (i > 0 && t == first) continue;
-        if (t > 0 && pf_fit_length(t, ppc) == 0) continue;
-        const PfOrg g{t, t > 0 ? pf_length(t, want_len, ppc, a, ctx->num_cu) : 0};
+        if (t == kPfRows && !pf_rows_pay(kernel, ppc)) continue;
+        if (pf_tiled(t) && pf_fit_length(t, ppc) == 0) continue;
+        const PfOrg g{t, pf_tiled(t) ? pf_length(t, want_len, ppc, a, ctx->num_cu) : 0};
         const unsigned nblk = (unsigned)pf_blocks(g, a);
         float ms = 0.f;
         bool ok = true;
@@ -553,7 +738,7 @@ extern "C" pi_status pi_interact_pairfn(pi_ctx *ctx, const pi_cells *cells, cons
     // every organisation's launch fits the partial records: one per
     // workgroup (at most one per cell or per 256 particles) plus the fold's
     if (n > 0 && t < 0) {
-        t = pf_static_t(ppc);
+        t = pf_static_t(o.kernel, n, ppc);
         pi_tuner *tu = ctx->tuner;
         if (tu && tu->mode == PI_TUNE_TIMED) {
             const uint64_t key = pf_tune_key(o.kernel, o.precision, want_inv, n, ppc);
@@ -578,7 +763,7 @@ extern "C" pi_status pi_interact_pairfn(pi_ctx *ctx, const pi_cells *cells, cons
         }
     }
     if (t < 0) t = 0;
-    const PfOrg g{t, t > 0 ? pf_length(t, o.tile[0], ppc, a, ctx->num_cu) : 0};
+    const PfOrg g{t, pf_tiled(t) ? pf_length(t, o.tile[0], ppc, a, ctx->num_cu) : 0};
     const int64_t blocks = n > 0 ? pf_blocks(g, a) : 0;
     if (want_inv && blocks + (blocks + 1023) / 1024 > cells->cap_partials) return PI_ENOMEM;
     const unsigned nblk = (unsigned)blocks;
