@@ -24,6 +24,9 @@
 // cell-relative coordinates.  Counts, offsets and M_C then come from the
 // runs of equal ids in the sorted cell ids (k_cell_ranges: wave ballots,
 // each count and offset written once).
+//
+// Few particles take one pass over the top digit, or none, and a workgroup per
+// digit sorts the rest in LDS (k_bucket_sort, bucket_plan).
 #include <string.h>
 
 #include "pi_internal.h"
@@ -163,12 +166,17 @@ struct SortArgs {
     // (ping-pong buffers)
     uint2 *kv_out;
     float4 *p_out;
-    // the last pass writes the final arrays in sorted order: local cell id,
-    // original index, cell-relative (x, y, z) and w; in batch mode also the
-    // global cell ids (for the run count)
+    // the last pass, or the bucket sort, writes the final arrays in sorted
+    // order: local cell id, original index, cell-relative (x, y, z) and w; in
+    // batch mode also the global cell ids (for the run count)
     int32_t *cell, *perm;
     float4 *xyzw;
     uint32_t *ids;
+    // the bucket sort also the counts, offsets and M_C
+    int32_t *counts, *offsets, *max_per_cell;
+    int32_t nc;       // cells
+    int32_t low_bits; // bits of a key that the radix passes leave to it
+    int32_t nbuckets;
     const int32_t *gbase; // per digit: exclusive scan of its per-tile counts
     const int32_t *dtot;  // per digit: total count
     int32_t *hist;
@@ -208,6 +216,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_hist(SortArgs a)
     // keys are not counted)
     // (each XCD takes a contiguous run of tiles: neighbouring tiles share
     // its L2, which merges their partial-line writes of a histogram column)
+    if (FIRST && !BATCH && blockIdx.x == 0 && threadIdx.x == 0) *a.max_per_cell = 0; // (the bucket sort raises it)
     const int32_t tile = (int32_t)xcd_remap(blockIdx.x, gridDim.x);
     const int64_t base = (int64_t)tile * kSortTile;
     const int64_t last = (int64_t)a.n - 1;
@@ -593,6 +602,251 @@ __global__ __launch_bounds__(1024) void k_max_reduce(const int32_t *__restrict__
     }
 }
 
+// Bucket sort: a workgroup takes the 2^low_bits consecutive cells whose ids
+// share their top bits (after a radix pass over those; or all cells and the
+// caller's arrays, FIRST) and writes every final array of theirs: the particles
+// in order, counts, offsets and M_C.  A call of few particles is bound by its
+// launches and the latency of each (5 to 12 µs a kernel, a CU or a few busy), so
+// this replaces seven launches by one, or by four: 512 particles in 8^3 cells
+// took 67 µs in them and take 9, 32768 in 32^3 67 and 43.  One workgroup has a
+// CU to itself (at most 256 buckets): 1024 threads, the bucket in registers, and
+// LDS as large as ranking wants it.  Bound by the latency of its phases.
+constexpr int kBBlock = 1024;           // threads per bucket
+constexpr int kBWaves = kBBlock / 64;
+constexpr int kLowBits = 12;            // most bits of a key sorted here
+constexpr int kFItems = 4;
+constexpr int kFast = kFItems * kBBlock; // a small bucket: at most this many particles,
+constexpr int kFastCell = 64;            // and this many in its fullest cell
+constexpr int kBucketCounters = 1 << 15; // counters of a large bucket's wavefronts
+constexpr int64_t kBucketMax = 64 * kSortTile; // most particles sorted by buckets
+
+template <bool FIRST>
+__global__ __launch_bounds__(kBBlock) void k_bucket_sort(SortArgs a)
+{
+    // per cell its particles, then where they start in the bucket
+    __shared__ int32_t start[(1 << kLowBits) + 1];
+    // a small bucket's list of positions and then its reordered records; a
+    // large one's particles per cell and wavefront
+    __shared__ __align__(16) uint32_t area[kBucketCounters];
+    static_assert(kBucketCounters >= 4 * kFast, "a small bucket's payload fits");
+    __shared__ int32_t wsum[kBWaves];
+    __shared__ int32_t wmost[kBWaves];
+    __shared__ int32_t ends[2];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int32_t b = (int32_t)blockIdx.x;
+    const int lb = a.low_bits;
+    const int64_t g0 = (int64_t)b << lb;
+    const int32_t ncell = (int32_t)min((int64_t)1 << lb, (int64_t)a.nc - g0);
+    const uint32_t lmask = (1u << lb) - 1u;
+
+    // 1. the bucket's range, from the totals of the digits
+    if (!FIRST) {
+        static_assert(kRadix <= kBBlock, "a thread per digit");
+        const int32_t v = tid < kRadix ? a.dtot[tid] : 0;
+        const int32_t inc = wave_incl_scan(v);
+        if (lane == 63) wsum[wid] = inc;
+        __syncthreads();
+        if (tid == b) {
+            int32_t before = inc - v;
+            for (int w = 0; w < wid; ++w) before += wsum[w];
+            ends[0] = before;
+            ends[1] = before + v;
+        }
+    }
+    for (int i = tid; i < ncell; i += kBBlock) start[i] = 0;
+    __syncthreads();
+    const int32_t s0 = FIRST ? 0 : ends[0];
+    const int32_t m = (FIRST ? a.n : ends[1]) - s0;
+
+    // (key, index) and payload of particle e of the bucket
+    auto record = [&](int32_t e, uint2 &kv, float4 &p) {
+        if (FIRST) {
+            p = make_float4(a.x[e], a.y[e], a.z[e], a.w[e]);
+            kv.y = (uint32_t)e;
+        } else {
+            kv = a.kv_in[s0 + e];
+            p = a.p_in[s0 + e];
+        }
+    };
+
+    // 2. particles per cell.  A bucket of at most kFast particles keeps them in
+    //    registers, and the counter's value is a particle's arrival in its
+    //    cell; in a larger one each wavefront counts a contiguous part.
+    const bool few = m <= kFast;
+    uint2 kv[kFItems];
+    float4 p[kFItems];
+    int32_t pos[kFItems];
+    const int sets = min(kBWaves, kBucketCounters >> lb);
+    const int32_t part = (m + 64 * sets - 1) / (64 * sets) * 64;
+    const int32_t e0 = wid * part, e1 = wid < sets ? min(e0 + part, m) : e0;
+    int32_t *cnt = reinterpret_cast<int32_t *>(area) + (wid < sets ? wid << lb : 0);
+    auto count_parts = [&]() { // and, from every cell's counts, where the parts start in the cell
+        for (int i = tid; i < sets << lb; i += kBBlock) area[i] = 0;
+        __syncthreads();
+        for (int32_t e = e0 + lane; e < e1; e += 64) {
+            uint32_t k;
+            if (FIRST) k = cell_key(a.x[e], a.y[e], a.z[e], a.g, a.err);
+            else k = a.kv_in[s0 + e].x;
+            atomicAdd(&cnt[k & lmask], 1);
+        }
+        __syncthreads();
+        for (int i = tid; i < ncell; i += kBBlock) {
+            int32_t run = 0;
+            for (int w = 0; w < sets; ++w) {
+                const int32_t c = (int32_t)area[(w << lb) + i];
+                area[(w << lb) + i] = (uint32_t)run;
+                run += c;
+            }
+            if (!few) start[i] = run;
+        }
+        __syncthreads();
+    };
+    if (few) {
+#pragma unroll
+        for (int r = 0; r < kFItems; ++r) {
+            if (r * kBBlock >= m) break;
+            record(min(r * kBBlock + tid, m - 1), kv[r], p[r]);
+        }
+#pragma unroll
+        for (int r = 0; r < kFItems; ++r) {
+            if (r * kBBlock >= m) break;
+            if (FIRST) kv[r].x = cell_key(p[r].x, p[r].y, p[r].z, a.g, a.err);
+            if (r * kBBlock + tid < m) pos[r] = atomicAdd(&start[kv[r].x & lmask], 1);
+        }
+        __syncthreads();
+    } else {
+        count_parts();
+    }
+
+    // 3. exclusive scan over the cells (four consecutive ones per thread), the
+    //    counts and offsets, M_C
+    int32_t most = 0;
+    {
+        constexpr int kPer = (1 << kLowBits) / kBBlock;
+        int32_t v[kPer], sum = 0;
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const int i = tid * kPer + q;
+            v[q] = i < ncell ? start[i] : 0;
+            sum += v[q];
+            most = max(most, v[q]);
+        }
+        const int32_t inc = wave_incl_scan(sum);
+        most = wave_max(most);
+        if (lane == 63) wsum[wid] = inc;
+        if (lane == 0) wmost[wid] = most;
+        __syncthreads();
+        int32_t run = inc - sum;
+        for (int w = 0; w < wid; ++w) run += wsum[w];
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const int i = tid * kPer + q;
+            if (i < ncell) start[i] = run;
+            run += v[q];
+        }
+        if (tid == 0) start[ncell] = m;
+    }
+    __syncthreads();
+    for (int w = 0; w < kBWaves; ++w) most = max(most, wmost[w]);
+    if (tid == 0) { // (few buckets raise M_C)
+        if (FIRST) *a.max_per_cell = most;
+        else if (most > *(volatile int32_t *)a.max_per_cell) atomicMax(a.max_per_cell, most);
+    }
+    for (int i = tid; i < ncell; i += kBBlock) {
+        const int32_t st = start[i];
+        a.offsets[g0 + i] = s0 + st;
+        a.counts[g0 + i] = start[i + 1] - st;
+    }
+    if (tid == 0 && b + 1 == a.nbuckets) a.offsets[a.nc] = a.n;
+
+    if (few && most <= kFastCell) {
+        // 4a. a small bucket: every cell's particles by arrival in one list, a
+        //     particle's rank the number of its cell's that come before it in
+        //     the bucket (cells hold few), then payload and (cell, index)
+        //     reordered through LDS and stored in order
+        uint16_t *list = reinterpret_cast<uint16_t *>(area);
+        float4 *lp = reinterpret_cast<float4 *>(area);
+        uint2 *lk = reinterpret_cast<uint2 *>(area);
+#pragma unroll
+        for (int r = 0; r < kFItems; ++r) {
+            const int32_t e = r * kBBlock + tid;
+            if (e < m) list[start[kv[r].x & lmask] + pos[r]] = (uint16_t)e;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kFItems; ++r) {
+            const int32_t e = r * kBBlock + tid;
+            if (e < m) {
+                const uint32_t c = kv[r].x & lmask;
+                const int32_t st = start[c], en = start[c + 1];
+                int32_t rank = 0;
+                for (int32_t q = st; q < en; ++q) rank += (int32_t)list[q] < e ? 1 : 0;
+                pos[r] = st + rank;
+            }
+        }
+        __syncthreads(); // the list makes room
+#pragma unroll
+        for (int r = 0; r < kFItems; ++r) {
+            if (r * kBBlock + tid < m) {
+                kv[r].x = to_cell_relative<false>(a, kv[r].x, p[r].x, p[r].y, p[r].z);
+                lp[pos[r]] = p[r];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kFItems; ++r) {
+            const int32_t q = r * kBBlock + tid;
+            if (q < m) a.xyzw[s0 + q] = lp[q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kFItems; ++r)
+            if (r * kBBlock + tid < m) lk[pos[r]] = kv[r];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kFItems; ++r) {
+            const int32_t q = r * kBBlock + tid;
+            if (q < m) {
+                const uint2 v = lk[q];
+                a.cell[s0 + q] = (int32_t)v.x;
+                a.perm[s0 + q] = (int32_t)v.y;
+            }
+        }
+        return;
+    }
+
+    // 4b. a large bucket: each wavefront ranks its part in order, 64 particles at
+    //     a time (ballots), and stores to the final arrays; no barrier after
+    //     the counts
+    if (few) count_parts();
+    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    for (int32_t c0 = e0; c0 < e1; c0 += 64 * kFItems) {
+#pragma unroll
+        for (int r = 0; r < kFItems; ++r) record(min(c0 + 64 * r + lane, e1 - 1), kv[r], p[r]);
+#pragma unroll
+        for (int r = 0; r < kFItems; ++r) {
+            const bool valid = c0 + 64 * r + lane < e1;
+            if (FIRST) kv[r].x = cell_key(p[r].x, p[r].y, p[r].z, a.g, a.err);
+            const uint32_t c = kv[r].x & lmask;
+            uint64_t peers = __ballot(valid);
+            for (int q = 0; q < lb; ++q) {
+                const uint64_t bal = __ballot((c >> q) & 1u);
+                peers &= ((c >> q) & 1u) ? bal : ~bal;
+            }
+            if (valid) {
+                const int32_t before = __popcll(peers & lt);
+                const int32_t base = cnt[c];
+                if (before == 0) cnt[c] = base + __popcll(peers);
+                const int32_t o = s0 + start[c] + base + before;
+                a.cell[o] = (int32_t)to_cell_relative<false>(a, kv[r].x, p[r].x, p[r].y, p[r].z);
+                a.perm[o] = (int32_t)kv[r].y;
+                a.xyzw[o] = p[r];
+            }
+        }
+    }
+}
+
 // The sorted coordinates as four arrays, from the records (in order).
 __global__ __launch_bounds__(kBlock) void k_split_records(int32_t n, const float4 *__restrict__ p, float *xs,
                                                           float *ys, float *zs, float *ws)
@@ -624,6 +878,44 @@ bool pi_grid_valid(const pi_grid *g)
     return true;
 }
 
+namespace {
+
+// How a binning of n particles into nc cells sorts: few go through the bucket
+// sort, alone or after one radix pass over the top eight key bits.  Measured
+// against the radix passes over all bits (kernels of one binning, µs; uniform
+// unless stated):
+//   n        cells       radix  bucket
+//   512      8^3            67       9  (no radix pass)
+//   4096     16^3           63      17  (no radix pass)
+//   4097     16^3           63      39
+//   32768    32^3           67      43
+//   131072   128^2 x 64    103      43
+//   262144   16^3           70      50
+//   262144   64^3           96      46  (8 blobs: 108 and 62)
+//   262144   64^3          180     205  (all in one layer of the cells)
+//   524288   64^3           94      49  (8 blobs: 108 and 83)
+//   524288   64^3          188     418  (all in one layer)
+// The line lies where the layer, whose few full buckets are a workgroup's work
+// each, begins to lose (all in a quarter of a layer, one bucket: 183 and 761 at
+// 262144).  A bucket sort after two passes, with 512 threads, gave 620 for 737
+// at 2^24 uniform in 256^3, but 1086 for 744 in 64 blobs there, and was left out.
+struct BucketPlan {
+    int passes; // radix passes before the bucket sort (0 or 1), -1: no bucket sort
+    int low_bits;
+};
+
+BucketPlan bucket_plan(int64_t n, int64_t nc)
+{
+    int bits = 0;
+    while (bits < 31 && ((int64_t)1 << bits) < nc) ++bits;
+    if (n <= kSortTile && bits <= kLowBits) return BucketPlan{0, bits};
+    if (n <= kBucketMax && bits > kRadixBits && bits <= kRadixBits + kLowBits)
+        return BucketPlan{1, bits - kRadixBits};
+    return BucketPlan{-1, 0};
+}
+
+} // namespace
+
 // Radix sort of n particles by global cell id, then counts and offsets.
 // nsys == 0: one system on grid g0; else d_sys describes nsys concatenated
 // systems with cells_total cells in all.
@@ -633,10 +925,14 @@ pi_status pi_bin_systems(pi_ctx *ctx, pi_cells *cells, const float *x, const flo
 {
     const bool batch = nsys > 0;
     if (n > 0) {
-        // 8-bit digits needed to sort keys 0 .. nc-1
-        int bits = 1;
-        while (bits < 31 && ((int64_t)1 << bits) < nc) ++bits;
-        const int passes = (bits + kRadixBits - 1) / kRadixBits;
+        const BucketPlan plan = batch ? BucketPlan{-1, 0} : bucket_plan(n, nc);
+        const bool buckets = plan.passes >= 0;
+        int passes = plan.passes;
+        if (!buckets) { // 8-bit digits needed to sort keys 0 .. nc-1
+            int bits = 1;
+            while (bits < 31 && ((int64_t)1 << bits) < nc) ++bits;
+            passes = (bits + kRadixBits - 1) / kRadixBits;
+        }
         const int32_t ntiles = (int32_t)((n + kSortTile - 1) / kSortTile);
         SortArgs a;
         memset(&a, 0, sizeof(a));
@@ -657,15 +953,21 @@ pi_status pi_bin_systems(pi_ctx *ctx, pi_cells *cells, const float *x, const flo
         a.cell = cells->cell;
         a.perm = cells->perm;
         a.xyzw = cells->xyzw;
-        // the last pass writes no records, so its output record buffer is
-        // free: in batch mode it takes the sorted global ids
+        a.counts = cells->counts;
+        a.offsets = cells->offsets;
+        a.max_per_cell = cells->max_per_cell;
+        a.nc = (int32_t)nc;
+        a.low_bits = plan.low_bits;
+        a.nbuckets = (int32_t)((nc + ((int64_t)1 << plan.low_bits) - 1) >> plan.low_bits);
+        // the last pass of a batch writes no records, so its output record
+        // buffer is free: it takes the sorted global ids
         uint32_t *ids = batch ? reinterpret_cast<uint32_t *>(cells->skv[(passes - 1) & 1])
                               : reinterpret_cast<uint32_t *>(cells->cell);
         a.ids = ids;
         for (int p = 0; p < passes; ++p) {
-            const bool first = p == 0, last = p == passes - 1;
+            const bool first = p == 0, last = p == passes - 1 && !buckets;
             const int src = (p + 1) & 1, dst = p & 1;
-            a.shift = p * kRadixBits;
+            a.shift = plan.low_bits + p * kRadixBits;
             a.kv_in = cells->skv[src];
             a.p_in = cells->sp[src];
             a.kv_out = last ? nullptr : cells->skv[dst];
@@ -691,13 +993,21 @@ pi_status pi_bin_systems(pi_ctx *ctx, pi_cells *cells, const float *x, const flo
                 PI_LAUNCH(ctx, nm, (k_radix_scatter<false, false, false>), grid, sb, 0, stream, a);
             }
         }
-        // the per-wavefront maxima go to the histogram buffer, free after
-        // the last pass (256 entries per 4096 particles, one per 256 needed)
-        const int64_t waves = (n + kRunIds - 1) / kRunIds;
-        PI_LAUNCH(ctx, "k_cell_ranges", k_cell_ranges, dim3(nblocks(waves * 64, kBlock)), dim3(kBlock), 0, stream,
-                  (int32_t)n, (int32_t)nc, (const uint32_t *)ids, cells->counts, cells->offsets, cells->hist);
-        PI_LAUNCH(ctx, "k_max_reduce", k_max_reduce, dim3(1), dim3(1024), 0, stream, (const int32_t *)cells->hist,
-                  (int32_t)waves, cells->max_per_cell);
+        if (buckets) {
+            const dim3 grid((unsigned)a.nbuckets), block(kBBlock);
+            a.kv_in = cells->skv[0];
+            a.p_in = cells->sp[0];
+            if (passes == 0) PI_LAUNCH(ctx, "k_bucket_sort", k_bucket_sort<true>, grid, block, 0, stream, a);
+            else PI_LAUNCH(ctx, "k_bucket_sort", k_bucket_sort<false>, grid, block, 0, stream, a);
+        } else {
+            // the per-wavefront maxima go to the histogram buffer, free after
+            // the last pass (256 entries per 4096 particles, one per 256 needed)
+            const int64_t waves = (n + kRunIds - 1) / kRunIds;
+            PI_LAUNCH(ctx, "k_cell_ranges", k_cell_ranges, dim3(nblocks(waves * 64, kBlock)), dim3(kBlock), 0, stream,
+                      (int32_t)n, (int32_t)nc, (const uint32_t *)ids, cells->counts, cells->offsets, cells->hist);
+            PI_LAUNCH(ctx, "k_max_reduce", k_max_reduce, dim3(1), dim3(1024), 0, stream, (const int32_t *)cells->hist,
+                      (int32_t)waves, cells->max_per_cell);
+        }
     } else {
         // no particles: every count and offset is zero, and M_C
         PI_LAUNCH(ctx, "k_fill_i32", k_fill_i32, dim3(nblocks((nc + 3) / 4, kBlock)), dim3(kBlock), 0, stream,
