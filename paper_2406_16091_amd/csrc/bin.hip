@@ -45,6 +45,7 @@ constexpr int kRadix = 1 << kRadixBits;
 #endif
 constexpr int kSBlock = PI_SCATTER_BLOCK;     // scatter threads per tile (256, 512 or 1024)
 constexpr int kSItems = kSortTile / kSBlock;  // keys per thread
+constexpr int kFewTiles = 16;                 // most tiles that sum the digit counts themselves
 static_assert(kSBlock >= kRadix && kSBlock <= 1024 && kSortTile % kSBlock == 0, "scatter block size");
 
 // p[0 .. n) = v, four entries per thread (p 16-byte aligned)
@@ -177,8 +178,9 @@ struct SortArgs {
     int32_t nc;       // cells
     int32_t low_bits; // bits of a key that the radix passes leave to it
     int32_t nbuckets;
-    const int32_t *gbase; // per digit: exclusive scan of its per-tile counts
-    const int32_t *dtot;  // per digit: total count
+    const int32_t *gbase; // per digit: exclusive scan of its per-tile counts (few_tiles: the counts)
+    int32_t few_tiles;
+    int32_t *dtot; // per digit: total count
     int32_t *hist;
     uint32_t *err;
 };
@@ -307,8 +309,19 @@ __global__ __launch_bounds__(kSBlock) __attribute__((amdgpu_waves_per_eu(1, 4)))
     for (int i = tid; i < W * kRadix; i += kSBlock) (&wcnt[0][0])[i] = 0;
     // this tile's digit offsets (threads 0..255), loaded with the tile
     const int d = tid & (kRadix - 1);
-    const int32_t dt = tid < kRadix ? a.dtot[d] : 0;
-    const int32_t gb = tid < kRadix ? a.gbase[(int64_t)d * a.ntiles + tile] : 0;
+    int32_t dt = 0, gb = 0;
+    if (tid < kRadix && a.few_tiles) { // the counts themselves, summed here
+#pragma unroll
+        for (int32_t t = 0; t < kFewTiles; ++t) {
+            const int32_t c = a.gbase[d * a.ntiles + min(t, a.ntiles - 1)];
+            dt += t < a.ntiles ? c : 0;
+            gb += t < tile ? c : 0;
+        }
+        if (tile == 0) a.dtot[d] = dt; // (for the bucket sort)
+    } else if (tid < kRadix) {
+        dt = a.dtot[d];
+        gb = a.gbase[(int64_t)d * a.ntiles + tile];
+    }
 
     // 0. the whole tile's keys and payload in registers: every global load
     //    of the tile is issued before the first barrier (indices past the
@@ -607,10 +620,11 @@ __global__ __launch_bounds__(1024) void k_max_reduce(const int32_t *__restrict__
 // caller's arrays, FIRST) and writes every final array of theirs: the particles
 // in order, counts, offsets and M_C.  A call of few particles is bound by its
 // launches and the latency of each (5 to 12 µs a kernel, a CU or a few busy), so
-// this replaces seven launches by one, or by four: 512 particles in 8^3 cells
-// took 67 µs in them and take 9, 32768 in 32^3 67 and 43.  One workgroup has a
-// CU to itself (at most 256 buckets): 1024 threads, the bucket in registers, and
-// LDS as large as ranking wants it.  Bound by the latency of its phases.
+// this replaces eight launches (two radix passes of three) by one, or by three or
+// four: 512 particles in 8^3 cells took 67 µs in them and take 9, 32768 in 32^3
+// 67 and 33.  A workgroup has a CU to itself (at most 256 buckets): 1024 threads,
+// the bucket in registers, and LDS as large as ranking wants it.  Bound by the
+// latency of its phases.
 constexpr int kBBlock = 1024;           // threads per bucket
 constexpr int kBWaves = kBBlock / 64;
 constexpr int kLowBits = 12;            // most bits of a key sorted here
@@ -887,8 +901,8 @@ namespace {
 //   n        cells       radix  bucket
 //   512      8^3            67       9  (no radix pass)
 //   4096     16^3           63      17  (no radix pass)
-//   4097     16^3           63      39
-//   32768    32^3           67      43
+//   4097     16^3           63      29
+//   32768    32^3           67      33
 //   131072   128^2 x 64    103      43
 //   262144   16^3           70      50
 //   262144   64^3           96      46  (8 blobs: 108 and 62)
@@ -958,6 +972,10 @@ pi_status pi_bin_systems(pi_ctx *ctx, pi_cells *cells, const float *x, const flo
         a.max_per_cell = cells->max_per_cell;
         a.nc = (int32_t)nc;
         a.low_bits = plan.low_bits;
+        // up to 16 tiles every tile sums the digit counts itself, a launch less
+        // (kernels of the binning of 65536 in 64 x 32^2 cells: 38 µs with the scan,
+        // 32 without; at 64 tiles the sums cost 10 µs, the launch 6)
+        a.few_tiles = buckets && ntiles <= kFewTiles;
         a.nbuckets = (int32_t)((nc + ((int64_t)1 << plan.low_bits) - 1) >> plan.low_bits);
         // the last pass of a batch writes no records, so its output record
         // buffer is free: it takes the sorted global ids
@@ -976,8 +994,9 @@ pi_status pi_bin_systems(pi_ctx *ctx, pi_cells *cells, const float *x, const flo
             if (first && batch) PI_LAUNCH(ctx, "k_radix_hist", (k_radix_hist<true, true>), grid, block, 0, stream, a);
             else if (first) PI_LAUNCH(ctx, "k_radix_hist", (k_radix_hist<true, false>), grid, block, 0, stream, a);
             else PI_LAUNCH(ctx, "k_radix_hist", (k_radix_hist<false, false>), grid, block, 0, stream, a);
-            PI_LAUNCH(ctx, "k_digit_scan", k_digit_scan, dim3(kRadix), dim3(kBlock), 0, stream, cells->hist, ntiles,
-                      cells->dtot);
+            if (!a.few_tiles)
+                PI_LAUNCH(ctx, "k_digit_scan", k_digit_scan, dim3(kRadix), dim3(kBlock), 0, stream, cells->hist,
+                          ntiles, cells->dtot);
             const dim3 sb(kSBlock);
             const char *nm = "k_radix_scatter";
             if (first && last) {

@@ -2406,14 +2406,20 @@ void pi_reduce_partials(pi_ctx *ctx, void *partials, unsigned nblk, pi_invariant
         PI_LAUNCH(ctx, "k_inv_zero", k_inv_zero, dim3(1), dim3(64), 0, stream, inv);
         return;
     }
-    // stage-1 records go after the sweep's records in the same buffer
-    const int32_t n1 = (int32_t)((nblk + kInvRun - 1) / kInvRun);
+    // up to kInvRun records are one run: stage 2 folds them itself, in the order
+    // in which stage 1 would (its one record then passed through unchanged), and
+    // a launch of a small call is saved (6 µs of the 50 that binning and sweep of
+    // 32768 particles in 32^3 cells take)
     InvPartial *parts = (InvPartial *)partials;
-    InvPartial *stage = parts + nblk;
-    PI_LAUNCH(ctx, "k_inv_stage1", k_inv_stage1, dim3(n1), dim3(kBlock), 0, stream, (const InvPartial *)parts,
-              (int32_t)nblk, stage);
-    PI_LAUNCH(ctx, "k_inv_stage2", k_inv_stage2, dim3(1), dim3(kBlock), 0, stream, (const InvPartial *)stage, n1,
-              inv);
+    int32_t n1 = (int32_t)nblk;
+    if (nblk > kInvRun) {
+        // stage-1 records go after the sweep's records in the same buffer
+        n1 = (int32_t)((nblk + kInvRun - 1) / kInvRun);
+        PI_LAUNCH(ctx, "k_inv_stage1", k_inv_stage1, dim3(n1), dim3(kBlock), 0, stream, (const InvPartial *)parts,
+                  (int32_t)nblk, parts + nblk);
+        parts += nblk;
+    }
+    PI_LAUNCH(ctx, "k_inv_stage2", k_inv_stage2, dim3(1), dim3(kBlock), 0, stream, (const InvPartial *)parts, n1, inv);
 }
 
 pi_status pi_interact_run(pi_ctx *ctx, const pi_cells *cells, const pi_interact_opts &o, float *rho, float *gx,

@@ -20,6 +20,8 @@ CASES = [
     (8192, (8, 8, 8), (1, 1, 1)),     # buckets of two cells
     (65536, (8, 8, 8), (1, 1, 1)),    # of 128 particles each
     (5000, (10, 11, 13), (1, 1, 1)),
+    (65536, (64, 64, 64), (1, 1, 1)),  # the most tiles that sum the digit counts themselves
+    (65537, (64, 64, 64), (1, 1, 1)),
     (262144, (64, 64, 64), (1, 1, 1)),  # the most for one pass: particles
     (262145, (64, 64, 64), (1, 1, 1)),
     (5000, (128, 128, 64), (1, 1, 1)),  # and cells
