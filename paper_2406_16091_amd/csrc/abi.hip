@@ -351,7 +351,7 @@ pi_status pi_ensure_capacity(pi_cells *c, int64_t n, int64_t n_cells, hipStream_
     const int64_t cap_n = grow_n ? grow(n < 64 ? 64 : n, c->cap_n) : c->cap_n;
     const int64_t cap_c = grow_c ? grow(n_cells < 64 ? 64 : n_cells, c->cap_cells) : c->cap_cells;
     const int64_t sort_tiles = (cap_n + 4095) / 4096 + 1;
-    const int64_t cap_hist = 256 * sort_tiles;
+    const int64_t cap_hist = 512 * sort_tiles;
     const int64_t cap_parts = 2 * (cap_c + cap_n / 64) + 64;
     BufRef b[40];
     const int nb = list_buffers(c, b);
@@ -365,7 +365,7 @@ pi_status pi_ensure_capacity(pi_cells *c, int64_t n, int64_t n_cells, hipStream_
         case BUF_CELLS1: count = cap_c + 1; redo = grow_c; break;
         case BUF_CELLS64: count = cap_c + 64; redo = grow_c; break;
         case BUF_PARTIALS: count = cap_parts; redo = grow_n || grow_c; break;
-        case BUF_RADIX: count = 256; redo = false; break;
+        case BUF_RADIX: count = 512; redo = false; break;
         case BUF_SCAN: count = 4 * (cap_c / 1024 + 2); redo = grow_c; break;
         }
         if (!redo && *b[i].ptr) continue;

@@ -6,9 +6,10 @@
 // reproducible.
 //
 // On MI355X the move is a least-significant-digit radix sort of the cell ids,
-// 8 bits per pass, which is stable by construction and keeps every HBM access
-// coalesced (the input order is a random permutation of the cells, so a
-// scatter by per-particle atomics costs a whole cache line per 4-byte access).
+// 8 bits per pass (9 where that saves a pass), which is stable by construction
+// and keeps every HBM access coalesced (the input order is a random permutation
+// of the cells, so a scatter by per-particle atomics costs a whole cache line
+// per 4-byte access).
 // Per pass, in launch order on the caller's stream:
 //   k_radix_hist     per 4096-key tile: LDS histogram of the pass's digit,
 //                    stored digit-major (digit * tiles + tile)
@@ -29,6 +30,8 @@
 // digit sorts the rest in LDS (k_bucket_sort, bucket_plan).
 #include <string.h>
 
+#include <type_traits>
+
 #include "pi_internal.h"
 
 namespace {
@@ -38,15 +41,16 @@ constexpr int kScanItems = 16;                 // histogram entries per thread a
 constexpr int kScanTile = kBlock * kScanItems; // 4096 entries per round
 constexpr int kSortItems = 16;
 constexpr int kSortTile = kBlock * kSortItems; // 4096 keys per sort tile
-constexpr int kRadixBits = 8;
+constexpr int kRadixBits = 8; // (of one digit, or 9)
 constexpr int kRadix = 1 << kRadixBits;
+constexpr int kWideBits = 9;
 #ifndef PI_SCATTER_BLOCK
 #define PI_SCATTER_BLOCK 512
 #endif
 constexpr int kSBlock = PI_SCATTER_BLOCK;     // scatter threads per tile (256, 512 or 1024)
 constexpr int kSItems = kSortTile / kSBlock;  // keys per thread
 constexpr int kFewTiles = 16;                 // most tiles that sum the digit counts themselves
-static_assert(kSBlock >= kRadix && kSBlock <= 1024 && kSortTile % kSBlock == 0, "scatter block size");
+static_assert(kSBlock >= 1 << kWideBits && kSBlock <= 1024 && kSortTile % kSBlock == 0, "scatter block size");
 
 // p[0 .. n) = v, four entries per thread (p 16-byte aligned)
 __global__ __launch_bounds__(kBlock) void k_fill_i32(int32_t *p, int64_t n, int32_t v)
@@ -208,12 +212,13 @@ __device__ __forceinline__ uint32_t key_at(const SortArgs &a, const TileSys &ts,
     return (uint32_t)s.cell_base + cell_key(x, y, z, s.g, a.err);
 }
 
-template <bool FIRST, bool BATCH>
+template <int BITS, bool FIRST, bool BATCH>
 __global__ __launch_bounds__(kBlock) void k_radix_hist(SortArgs a)
 {
-    __shared__ int32_t h[4][kRadix]; // one histogram per wavefront
+    constexpr int R = 1 << BITS;
+    __shared__ int32_t h[4][R]; // one histogram per wavefront
     const int wid = threadIdx.x >> 6;
-    for (int w = 0; w < 4; ++w) h[w][threadIdx.x] = 0;
+    for (int i = threadIdx.x; i < 4 * R; i += kBlock) (&h[0][0])[i] = 0;
     // all of the tile's loads first (indices past the end clamped; their
     // keys are not counted)
     // (each XCD takes a contiguous run of tiles: neighbouring tiles share
@@ -243,18 +248,19 @@ __global__ __launch_bounds__(kBlock) void k_radix_hist(SortArgs a)
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < kSortItems; ++q)
-        if (base + q * kBlock + threadIdx.x < a.n) atomicAdd(&h[wid][(key[q] >> a.shift) & (kRadix - 1)], 1);
+        if (base + q * kBlock + threadIdx.x < a.n) atomicAdd(&h[wid][(key[q] >> a.shift) & (R - 1)], 1);
     __syncthreads();
-    const int d = threadIdx.x;
-    a.hist[(int64_t)d * a.ntiles + tile] = (h[0][d] + h[1][d]) + (h[2][d] + h[3][d]);
+    for (int d = threadIdx.x; d < R; d += kBlock)
+        a.hist[(int64_t)d * a.ntiles + tile] = (h[0][d] + h[1][d]) + (h[2][d] + h[3][d]);
 }
 
 // Lanes of the wavefront whose digit equals this lane's (among `valid`).
+template <int BITS>
 __device__ __forceinline__ uint64_t match_digit(uint32_t d, uint64_t valid)
 {
     uint64_t m = valid;
 #pragma unroll
-    for (int b = 0; b < kRadixBits; ++b) {
+    for (int b = 0; b < BITS; ++b) {
         const uint64_t bal = __ballot((d >> b) & 1);
         m &= ((d >> b) & 1u) ? bal : ~bal;
     }
@@ -286,15 +292,18 @@ __device__ __forceinline__ uint32_t to_cell_relative(const SortArgs &a, uint32_t
 
 // (LDS allows two workgroups, i.e. 4 wavefronts per SIMD: registers are
 // budgeted for that, so the prefetched tile stays in registers)
-template <bool FIRST, bool LAST, bool BATCH>
+template <int BITS, bool FIRST, bool LAST, bool BATCH>
 __global__ __launch_bounds__(kSBlock) __attribute__((amdgpu_waves_per_eu(1, 4))) void k_radix_scatter(SortArgs a)
 {
-    constexpr int W = kSBlock / 64;      // wavefronts per block
-    __shared__ int32_t wcnt[W][kRadix];  // per-wave digit counters, then wave bases
-    __shared__ int32_t lstart[kRadix];   // tile-local start of each digit
-    __shared__ int32_t gdst[kRadix];     // global start of each digit's run
-    __shared__ int32_t scan_tmp[4];
-    __shared__ int32_t dscan_tmp[4];
+    constexpr int R = 1 << BITS;
+    constexpr int W = kSBlock / 64; // wavefronts per block
+    // (16 bits hold a tile's counts; with 512 digits, two workgroups per CU need that)
+    using Count = typename std::conditional<BITS == kRadixBits, int32_t, uint16_t>::type;
+    __shared__ Count wcnt[W][R];          // per-wave digit counters, then wave bases
+    __shared__ int32_t lstart[R];   // tile-local start of each digit
+    __shared__ int32_t gdst[R];     // global start of each digit's run
+    __shared__ int32_t scan_tmp[R / 64];
+    __shared__ int32_t dscan_tmp[R / 64];
     // reorder buffer: the (key, index) records (8 bytes per position; 16
     // in the last pass of a batch, which also carries the global id), then
     // the payload (16 bytes); plus a spare slot
@@ -306,11 +315,11 @@ __global__ __launch_bounds__(kSBlock) __attribute__((amdgpu_waves_per_eu(1, 4)))
     // per-tile digit offsets they read)
     const int32_t tile = (int32_t)xcd_remap(blockIdx.x, gridDim.x);
     const int64_t tile_base = (int64_t)tile * kSortTile;
-    for (int i = tid; i < W * kRadix; i += kSBlock) (&wcnt[0][0])[i] = 0;
-    // this tile's digit offsets (threads 0..255), loaded with the tile
-    const int d = tid & (kRadix - 1);
+    for (int i = tid; i < W * R; i += kSBlock) (&wcnt[0][0])[i] = 0;
+    // this tile's digit offsets (threads 0 .. R - 1), loaded with the tile
+    const int d = tid & (R - 1);
     int32_t dt = 0, gb = 0;
-    if (tid < kRadix && a.few_tiles) { // the counts themselves, summed here
+    if (tid < R && a.few_tiles) { // the counts themselves, summed here
 #pragma unroll
         for (int32_t t = 0; t < kFewTiles; ++t) {
             const int32_t c = a.gbase[d * a.ntiles + min(t, a.ntiles - 1)];
@@ -318,7 +327,7 @@ __global__ __launch_bounds__(kSBlock) __attribute__((amdgpu_waves_per_eu(1, 4)))
             gb += t < tile ? c : 0;
         }
         if (tile == 0) a.dtot[d] = dt; // (for the bucket sort)
-    } else if (tid < kRadix) {
+    } else if (tid < R) {
         dt = a.dtot[d];
         gb = a.gbase[(int64_t)d * a.ntiles + tile];
     }
@@ -366,43 +375,43 @@ __global__ __launch_bounds__(kSBlock) __attribute__((amdgpu_waves_per_eu(1, 4)))
 #pragma unroll
     for (int r = 0; r < kSItems; ++r) {
         const bool valid = elem(r) < a.n;
-        const uint32_t d = (key[r] >> a.shift) & (kRadix - 1);
+        const uint32_t d = (key[r] >> a.shift) & (R - 1);
         const uint64_t vmask = __ballot(valid);
-        const uint64_t peers = match_digit(d, vmask);
+        const uint64_t peers = match_digit<BITS>(d, vmask);
         int32_t rk = -1;
         if (valid) {
             const int32_t before = __popcll(peers & lt);
             const int32_t base = wcnt[wid][d];
             rk = base + before;
-            if (before == 0) wcnt[wid][d] = base + __popcll(peers);
+            if (before == 0) wcnt[wid][d] = (Count)(base + __popcll(peers));
         }
         pos[r] = rk; // rank within the wave for now, -1 past the end
     }
     __syncthreads();
 
-    // 2. per digit (threads 0..255): bases of the waves, tile total,
-    //    tile-local start (scan over the first four wavefronts), and where
+    // 2. per digit (threads 0 .. R - 1): bases of the waves, tile total,
+    //    tile-local start (scan over the first R / 64 wavefronts), and where
     //    the digit's run of this tile starts in the output: the totals of
     //    the smaller digits plus this digit's count in the tiles before
     int32_t tot = 0;
-    if (tid < kRadix) {
+    if (tid < R) {
         int32_t run = 0;
 #pragma unroll
         for (int k = 0; k < W; ++k) {
             const int32_t c = wcnt[k][d];
-            wcnt[k][d] = run;
+            wcnt[k][d] = (Count)run;
             run += c;
         }
         tot = run;
     }
     const int32_t inc = wave_incl_scan(tot);
     const int32_t dinc = wave_incl_scan(dt);
-    if (tid < kRadix && lane == 63) {
+    if (tid < R && lane == 63) {
         scan_tmp[wid] = inc;
         dscan_tmp[wid] = dinc;
     }
     __syncthreads();
-    if (tid < kRadix) {
+    if (tid < R) {
         int32_t wofs = 0, dofs = 0;
         for (int k = 0; k < wid; ++k) {
             wofs += scan_tmp[k];
@@ -419,7 +428,7 @@ __global__ __launch_bounds__(kSBlock) __attribute__((amdgpu_waves_per_eu(1, 4)))
     //    written but never read
 #pragma unroll
     for (int r = 0; r < kSItems; ++r) {
-        const uint32_t dg = (key[r] >> a.shift) & (kRadix - 1);
+        const uint32_t dg = (key[r] >> a.shift) & (R - 1);
         pos[r] = pos[r] >= 0 ? lstart[dg] + wcnt[wid][dg] + pos[r] : kSortTile;
     }
     const int32_t nvalid = (int32_t)min((int64_t)kSortTile, (int64_t)a.n - tile_base);
@@ -431,7 +440,7 @@ __global__ __launch_bounds__(kSBlock) __attribute__((amdgpu_waves_per_eu(1, 4)))
     //    destination is that digit's global start plus p's offset in the
     //    digit's tile-local run.
     auto dest = [&](int p, uint32_t k) {
-        const uint32_t dg = (k >> a.shift) & (kRadix - 1);
+        const uint32_t dg = (k >> a.shift) & (R - 1);
         return gdst[dg] + (p - lstart[dg]);
     };
     int32_t dst[kSItems];
@@ -930,6 +939,36 @@ BucketPlan bucket_plan(int64_t n, int64_t nc)
 
 } // namespace
 
+namespace {
+
+// One radix pass, digits of BITS bits.
+template <int BITS>
+void radix_pass(pi_ctx *ctx, const SortArgs &a, bool first, bool last, bool batch, hipStream_t stream)
+{
+    const dim3 grid(a.ntiles), block(kBlock), sb(kSBlock);
+    const char *nm = "k_radix_hist";
+    if (first && batch) PI_LAUNCH(ctx, nm, (k_radix_hist<BITS, true, true>), grid, block, 0, stream, a);
+    else if (first) PI_LAUNCH(ctx, nm, (k_radix_hist<BITS, true, false>), grid, block, 0, stream, a);
+    else PI_LAUNCH(ctx, nm, (k_radix_hist<BITS, false, false>), grid, block, 0, stream, a);
+    if (!a.few_tiles)
+        PI_LAUNCH(ctx, "k_digit_scan", k_digit_scan, dim3(1 << BITS), block, 0, stream, a.hist, a.ntiles, a.dtot);
+    nm = "k_radix_scatter";
+    if (first && last) {
+        if (batch) PI_LAUNCH(ctx, nm, (k_radix_scatter<BITS, true, true, true>), grid, sb, 0, stream, a);
+        else PI_LAUNCH(ctx, nm, (k_radix_scatter<BITS, true, true, false>), grid, sb, 0, stream, a);
+    } else if (first) {
+        if (batch) PI_LAUNCH(ctx, nm, (k_radix_scatter<BITS, true, false, true>), grid, sb, 0, stream, a);
+        else PI_LAUNCH(ctx, nm, (k_radix_scatter<BITS, true, false, false>), grid, sb, 0, stream, a);
+    } else if (last) {
+        if (batch) PI_LAUNCH(ctx, nm, (k_radix_scatter<BITS, false, true, true>), grid, sb, 0, stream, a);
+        else PI_LAUNCH(ctx, nm, (k_radix_scatter<BITS, false, true, false>), grid, sb, 0, stream, a);
+    } else {
+        PI_LAUNCH(ctx, nm, (k_radix_scatter<BITS, false, false, false>), grid, sb, 0, stream, a);
+    }
+}
+
+} // namespace
+
 // Radix sort of n particles by global cell id, then counts and offsets.
 // nsys == 0: one system on grid g0; else d_sys describes nsys concatenated
 // systems with cells_total cells in all.
@@ -942,10 +981,18 @@ pi_status pi_bin_systems(pi_ctx *ctx, pi_cells *cells, const float *x, const flo
         const BucketPlan plan = batch ? BucketPlan{-1, 0} : bucket_plan(n, nc);
         const bool buckets = plan.passes >= 0;
         int passes = plan.passes;
-        if (!buckets) { // 8-bit digits needed to sort keys 0 .. nc-1
+        int digit = kRadixBits;
+        if (!buckets) { // digits needed to sort keys 0 .. nc-1: of 9 bits where that saves a pass
+            // (a pass costs a fifth more with 512 digits, whose runs in a tile are half
+            // as long; binning in 64^3 cells, three passes of 8 bits and two of 9:
+            // 2^19 particles 93 and 75 µs, 2^22 196 and 152, 2^24 688 and 560)
             int bits = 1;
             while (bits < 31 && ((int64_t)1 << bits) < nc) ++bits;
             passes = (bits + kRadixBits - 1) / kRadixBits;
+            if ((bits + kWideBits - 1) / kWideBits < passes) {
+                digit = kWideBits;
+                passes = (bits + kWideBits - 1) / kWideBits;
+            }
         }
         const int32_t ntiles = (int32_t)((n + kSortTile - 1) / kSortTile);
         SortArgs a;
@@ -985,32 +1032,13 @@ pi_status pi_bin_systems(pi_ctx *ctx, pi_cells *cells, const float *x, const flo
         for (int p = 0; p < passes; ++p) {
             const bool first = p == 0, last = p == passes - 1 && !buckets;
             const int src = (p + 1) & 1, dst = p & 1;
-            a.shift = plan.low_bits + p * kRadixBits;
+            a.shift = plan.low_bits + p * digit;
             a.kv_in = cells->skv[src];
             a.p_in = cells->sp[src];
             a.kv_out = last ? nullptr : cells->skv[dst];
             a.p_out = last ? nullptr : cells->sp[dst];
-            const dim3 grid(ntiles), block(kBlock);
-            if (first && batch) PI_LAUNCH(ctx, "k_radix_hist", (k_radix_hist<true, true>), grid, block, 0, stream, a);
-            else if (first) PI_LAUNCH(ctx, "k_radix_hist", (k_radix_hist<true, false>), grid, block, 0, stream, a);
-            else PI_LAUNCH(ctx, "k_radix_hist", (k_radix_hist<false, false>), grid, block, 0, stream, a);
-            if (!a.few_tiles)
-                PI_LAUNCH(ctx, "k_digit_scan", k_digit_scan, dim3(kRadix), dim3(kBlock), 0, stream, cells->hist,
-                          ntiles, cells->dtot);
-            const dim3 sb(kSBlock);
-            const char *nm = "k_radix_scatter";
-            if (first && last) {
-                if (batch) PI_LAUNCH(ctx, nm, (k_radix_scatter<true, true, true>), grid, sb, 0, stream, a);
-                else PI_LAUNCH(ctx, nm, (k_radix_scatter<true, true, false>), grid, sb, 0, stream, a);
-            } else if (first) {
-                if (batch) PI_LAUNCH(ctx, nm, (k_radix_scatter<true, false, true>), grid, sb, 0, stream, a);
-                else PI_LAUNCH(ctx, nm, (k_radix_scatter<true, false, false>), grid, sb, 0, stream, a);
-            } else if (last) {
-                if (batch) PI_LAUNCH(ctx, nm, (k_radix_scatter<false, true, true>), grid, sb, 0, stream, a);
-                else PI_LAUNCH(ctx, nm, (k_radix_scatter<false, true, false>), grid, sb, 0, stream, a);
-            } else {
-                PI_LAUNCH(ctx, nm, (k_radix_scatter<false, false, false>), grid, sb, 0, stream, a);
-            }
+            if (digit == kRadixBits) radix_pass<kRadixBits>(ctx, a, first, last, batch, stream);
+            else radix_pass<kWideBits>(ctx, a, first, last, batch, stream);
         }
         if (buckets) {
             const dim3 grid((unsigned)a.nbuckets), block(kBBlock);

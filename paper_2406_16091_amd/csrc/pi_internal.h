@@ -70,7 +70,7 @@ struct pi_cells {
     pi_grid grid;
     int64_t cap_n;      // capacity in particles
     int64_t cap_cells;  // capacity in cells
-    int64_t cap_hist;   // radix histogram entries (256 per sort tile)
+    int64_t cap_hist;   // radix histogram entries (up to 512 digits per sort tile)
     hipStream_t last_stream;
     bool binned;
     // per cell
@@ -85,7 +85,7 @@ struct pi_cells {
     // radix-sort ping-pong buffers: key, original index, x, y, z, w
     uint2 *skv[2];       // radix ping-pong records (cell id, original index)
     float4 *sp[2];       // payload records (x, y, z, w)
-    int32_t *dtot;       // radix digit totals (256)
+    int32_t *dtot;       // radix digit totals (up to 512)
     // radix histograms (digit-major, 256 x sort tiles) and their scan scratch
     int32_t *hist;        // [cap_hist]
     // cell-scan scratch
