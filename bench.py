@@ -73,6 +73,8 @@ def algorithmic_bytes(name: str, n: int, nc: int, orig_order: bool) -> float:
         return 48.0 * n                               # records in and out (40 B on the first pass)
     if name == "k_cell_ranges":
         return 4.0 * n + 8.0 * nc                     # sorted ids in; counts and offsets out
+    if name == "k_bucket_sort":
+        return 48.0 * n + 8.0 * nc                    # records in; final arrays, counts and offsets out
     if name.startswith("k_sweep"):
         # sorted x, y, z, w in (16 B), rho, G and count out (20 B), one
         # offset per cell (4 B); the original-order scatter reads perm
@@ -491,7 +493,7 @@ def bench_step(system, steps: int = 20, warmup: int = 3):
     ds.close()
     per = {k: round(v[1] * 1e3 / steps, 2) for k, v in kt.items()}
     rebin = sum(v for k, v in per.items() if k.startswith(("k_step_", "k_scan_")))
-    full = sum(v for k, v in per.items() if k.startswith(("k_radix", "k_digit", "k_cell_ranges", "k_max")))
+    full = sum(v for k, v in per.items() if k.startswith(("k_radix", "k_digit", "k_bucket", "k_cell_ranges", "k_max")))
     return {"workload": "the headline system, stepped", "ms_per_step": round(ms, 4),
             "update_and_incremental_rebin_us": round(rebin, 2), "full_pi_bin_us": round(full, 2),
             "kernels_us": per}

@@ -86,7 +86,7 @@ struct pi_cells {
     uint2 *skv[2];       // radix ping-pong records (cell id, original index)
     float4 *sp[2];       // payload records (x, y, z, w)
     int32_t *dtot;       // radix digit totals (up to 512)
-    // radix histograms (digit-major, 256 x sort tiles) and their scan scratch
+    // radix histograms (digit-major, digits x sort tiles) and their scan scratch
     int32_t *hist;        // [cap_hist]
     // cell-scan scratch
     int32_t *max_per_cell; // [1]
