@@ -422,8 +422,9 @@ pi_status pi_batch_destroy(pi_batch *batch);
  * PI_ORDER_ORIGINAL output i belongs to input particle i, with
  * PI_ORDER_SORTED to sorted slot i (systems stay in order either way).  inv,
  * if not NULL, receives nsys records (device memory).  Same precision and
- * organisation options as pi_interact; AUTO picks one tile shape for the
- * batch from its mean occupancy.  Sum(n) and the total cell count must stay
+ * organisation options as pi_interact; AUTO picks per system: the tuner's
+ * cached choice for its class if there is one and it has 2^18 particles or
+ * more, else the static rule.  Sum(n) and the total cell count must stay
  * below 2^31.  Errors as pi_bin / pi_interact; device errors surface through
  * pi_batch_sync.
  */

@@ -3,7 +3,8 @@
 // concatenated; one radix sort orders them by global cell id (system cell
 // base + local cell), which keeps every system's particles contiguous and in
 // system order.  Each system gets its own sweep organisation (the tuner's
-// choice for its size and occupancy, or the caller's explicit one); systems
+// choice for its size and occupancy or the static rule, or the caller's explicit
+// one); systems
 // with the same organisation share one work-list launch, so a batch costs at
 // most one sweep launch per organisation.  The whole sequence is captured
 // once into a hipGraph per batch layout (systems, pointers, options) and
@@ -261,7 +262,7 @@ pi_status pi_batch_run_orgs(pi_ctx *ctx, pi_batch *b, int32_t nsys, const pi_sys
         const double ppc = (double)sys[s].n / (double)nc;
         int t = pi_pick_tile(o, ppc);
         if (t < 0) return PI_EINVAL;
-        if (o.sweep == PI_SWEEP_AUTO) t = pi_auto_tile(ctx, o.precision, sys[s].n, ppc);
+        if (o.sweep == PI_SWEEP_AUTO) t = pi_auto_tile(ctx, o.precision, sys[s].n, ppc, false);
         if (org && org[s] >= 0) {
             if (!pi_org_valid(org[s])) return PI_EINVAL;
             t = org[s];

@@ -269,7 +269,7 @@ KernelConst pi_make_kernel_const(float rc, float cell_w);
 bool pi_tile_shape(int tile_id, int *tx, int *ty, int *tz);
 int pi_pick_tile(const pi_interact_opts &o, double ppc);
 void pi_tile_opts(int tile_id, pi_interact_opts *out);
-int pi_auto_tile(pi_ctx *ctx, int precision, int64_t n, double ppc);
+int pi_auto_tile(pi_ctx *ctx, int precision, int64_t n, double ppc, bool alone);
 int64_t pi_batch_layout(int tile_id, SysDev *h_sys, int32_t nsys);
 int pi_batch_org(int tile_id);
 bool pi_org_valid(int id);

@@ -419,7 +419,9 @@ pi_status launch_batch(pi_server *s, Lane &ln, const std::vector<Ticket *> &ts)
     pi_interact_opts o1 = o;
     if (ln.alone && o1.sweep == PI_SWEEP_AUTO) {
         const double nc = (double)r0.grid.dims[0] * r0.grid.dims[1] * r0.grid.dims[2];
-        pi_tile_opts(clustered(ts[0]) ? kOrgStream : pi_auto_tile(s->ctx, r0.precision, r0.n, (double)r0.n / nc), &o1);
+        pi_tile_opts(clustered(ts[0]) ? kOrgStream
+                                      : pi_auto_tile(s->ctx, r0.precision, r0.n, (double)r0.n / nc, false),
+                     &o1);
     }
     std::vector<int32_t> org((size_t)m, -1);
     if (o.sweep == PI_SWEEP_AUTO)
