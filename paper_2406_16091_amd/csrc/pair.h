@@ -119,26 +119,6 @@ __device__ __forceinline__ float sq_dist(float dx, float dy, float dz)
     return __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
 }
 
-// c ? a : b with the lane mask of c in an SGPR pair.  Two selects in a row in
-// the short encoding, which reads the mask from VCC, cost about 30 cycles more
-// than the two selects (measured: 43 cycles for a compare and two selects,
-// 12 with the long encoding).
-__device__ __forceinline__ float lane_select(uint64_t c, float a, float b)
-{
-    float r;
-    asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(b), "v"(a), "s"(c));
-    return r;
-}
-
-// v + 1 in the lanes of c.
-__device__ __forceinline__ int32_t lane_add(uint64_t c, int32_t v)
-{
-    int32_t r;
-    uint64_t carry;
-    asm("v_addc_co_u32_e64 %0, %1, %2, 0, %3" : "=v"(r), "=s"(carry) : "v"(v), "s"(c));
-    return r;
-}
-
 // Kernel value W(r) and W'(r)/r of an accepted pair.  With SELECT both
 // pieces of the spline are evaluated and one is chosen, with the same
 // values as the branch: where a wavefront evaluates queued pairs together it
@@ -164,9 +144,9 @@ __device__ __forceinline__ void bspline_terms(float dx, float dy, float dz, floa
         const float omq2 = omq * omq;
         const float w_out = k.two_sigma * omq2 * omq;
         const float f_out = -k.six_sig_h * omq2 * __builtin_amdgcn_rsqf(t);
-        const uint64_t inner = __builtin_amdgcn_ballot_w64(t <= k.hh_quarter);
-        W = lane_select(inner, w_in, w_out);
-        Fr = lane_select(inner, f_in, f_out);
+        const bool inner = t <= k.hh_quarter;
+        W = inner ? w_in : w_out;
+        Fr = inner ? f_in : f_out;
         return;
     }
     if (t <= k.hh_quarter) {
@@ -282,18 +262,24 @@ struct Target {
     // The same for a wavefront that evaluates queued pairs together: every lane
     // runs, and a lane whose `ok` is false adds zeros, which change no sum (its
     // differences must be finite).  One straight piece of code: accumulators
-    // that a branch carries cost a register copy each per round.
+    // that a branch carries cost a register copy each per round.  The selects are
+    // the compiler's: it keeps two wait states between the compare that writes a
+    // lane mask and the select that reads it, which it would not around one
+    // written in inline assembly.  Sweep kernels with these, and with assembly
+    // that held the waits itself: 2^24 particles at 1 per cell (7x7x5) 0.80 and
+    // 0.80 ms, at 8 per cell 2.41 and 2.48, 2^21 at 64 per cell 1.97 and 2.03.
     __device__ __forceinline__ void pair_if(bool ok, float dx, float dy, float dz, float t, float wj,
                                             const KernelConst &k)
     {
         float W, Fr;
         bspline_terms<PREC, true>(dx, dy, dz, t, k, W, Fr);
-        // (the products, not a factor: either may be infinite)
-        const uint64_t in = __builtin_amdgcn_ballot_w64(ok);
-        const float a = lane_select(in, wj * W, 0.0f), f = lane_select(in, wj * Fr, 0.0f);
+        // (the products, not a factor: either may be infinite; and chosen as
+        // floats, not after the conversion, which the empty asm is for)
+        float a = ok ? wj * W : 0.0f, f = ok ? wj * Fr : 0.0f;
+        asm("" : "+v"(a), "+v"(f));
         // (adding zero would move a Kahan sum's excess into the sum)
         if (PREC != kPrecStep || ok) acc.add(a, f, dx, dy, dz);
-        count = lane_add(in, count);
+        count += ok ? 1 : 0;
         if (INV) ascale += -f * __builtin_amdgcn_sqrtf(t); // (Fr <= 0)
     }
 

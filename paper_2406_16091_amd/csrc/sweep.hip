@@ -244,6 +244,13 @@ __device__ __forceinline__ uint32_t first_bit(uint64_t m)
     return min(a, b + 32u);
 }
 
+// Has the compiler compute v here, in every lane, and not behind a branch around
+// the select that uses it.
+__device__ __forceinline__ void in_register(uint32_t &v)
+{
+    asm volatile("" : "+v"(v));
+}
+
 // ------------------------------------------------------------------ stream
 // Targets in cell-sorted order, one per lane, with sources streamed through LDS a
 // chunk of 64 at a time, so that any occupancy fits: the organisation for dense
@@ -348,9 +355,9 @@ __global__ __launch_bounds__(kBlock, 4) void k_sweep_stream(SweepArgs a)
             --cnt;
         }
         const bool live = m != 0;
-        const uint32_t e = __float_as_uint(lane_select(__builtin_amdgcn_ballot_w64(live),
-                                                       __uint_as_float(base + first_bit(m)),
-                                                       __uint_as_float(kNone)));
+        uint32_t e = base + first_bit(m);
+        in_register(e);
+        e = live ? e : kNone;
         m &= m - 1;
         const float4 q = rp[e];
         // (x_i - d W with d the source's cell against the target's, -1, 0 or 1:
@@ -360,7 +367,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_sweep_stream(SweepArgs a)
         const float t = sq_dist(ddx, ddy, ddz);
         const bool in = PREC == PI_PREC_PLAIN ? inside_cutoff<PREC>(ddx, ddy, ddz, t, a.k)
                                               : h2_above_d2<PREC>(ddx, ddy, ddz, a.k);
-        T.pair_if(live && in, ddx, ddy, ddz, t, q.w, a.k);
+        T.pair_if(live & in, ddx, ddy, ddz, t, q.w, a.k);
     };
 
     uint32_t seq = 0; // number of the next chunk
@@ -1097,15 +1104,15 @@ __global__ __launch_bounds__(kBlock, CAP <= 768 ? 6 : 4) void k_sweep_tile(Sweep
             }
             const bool live = m != 0;
             // (a lane without work evaluates its own target, all finite)
-            const uint32_t e = __float_as_uint(lane_select(__builtin_amdgcn_ballot_w64(live),
-                                                           __uint_as_float(base + first_bit(m)),
-                                                           __int_as_float(self)));
+            uint32_t e = base + first_bit(m);
+            in_register(e);
+            e = live ? e : (uint32_t)self;
             m &= m - 1;
             const float ddx = xt - soa[0][e], ddy = yt - soa[1][e], ddz = zt - soa[2][e];
             const float t = sq_dist(ddx, ddy, ddz);
             const bool in = PREC == PI_PREC_PLAIN ? inside_cutoff<PREC>(ddx, ddy, ddz, t, a.k)
                                                   : h2_above_d2<PREC>(ddx, ddy, ddz, a.k);
-            T.pair_if(live && in, ddx, ddy, ddz, t, soa[4][e], a.k);
+            T.pair_if(live & in, ddx, ddy, ddz, t, soa[4][e], a.k);
         };
         for (int32_t c = blo[0] >> 6; c < cend; ++c) {
             const int32_t c0 = c << 6;
