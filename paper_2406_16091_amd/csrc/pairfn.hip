@@ -549,18 +549,31 @@ int32_t pf_length(int t, int32_t want, double ppc, const PfArgs &a, int num_cu)
     return len;
 }
 
+// Whether the no-LDS walk goes cell by cell.  That issues more (a wavefront's loop
+// runs as long as its longest cell, three times a row), but its chain from one
+// candidate to the next is shorter and four loads are in flight, so it pays where a
+// launch leaves the SIMDs a few wavefronts each: Lennard-Jones by rows and by cells,
+// 10 per cell, 312 workgroups 57 and 38 us, 686 59 and 46, 952 62 and 56, 1403 74 and
+// 81, 10240 451 and 508; 3 per cell, 256 workgroups 26 and 21; the low-FLOP kernel
+// crosses at 850 workgroups.  The high-FLOP kernel's term hides the loads: 10 per
+// cell, 160 workgroups 96 and 98 us (compensated 116 and 104), 312 104 and 122, 1280
+// 202 and 234; 20 per cell, 64 workgroups 181 and 165.  From 64 per cell its cells are
+// long enough to even out (1024 workgroups 861 and 801, 16384 11624 and 10930).
+template <int KF>
+bool pf_cell_walk(const pi_ctx *ctx, const PfArgs &a, unsigned nblk)
+{
+    const double ppc = a.nc > 0 ? (double)a.n / (double)a.nc : 0.0;
+    if (KF == PI_PAIRFN_HIGHFLOP) return ppc >= (nblk <= (unsigned)ctx->num_cu ? 14.0 : 64.0);
+    return ppc >= 3.0 && nblk <= 3u * (unsigned)ctx->num_cu;
+}
+
 template <int KF, int PREC, bool INV>
 void pf_launch(pi_ctx *ctx, const PfOrg &g, const PfArgs &a, hipStream_t s, unsigned nblk)
 {
     if (g.t == 0) {
-        // Cell by cell from where its shorter inner loop outweighs the longer trip
-        // counts (row walk and cell walk, 32^3 cells): Lennard-Jones 1 per cell 16.9
-        // and 18.5 us, 3 per cell 26.8 and 24.6; high-FLOP 3 per cell 60.6 and 67.1, 6
-        // per cell 126.8 and 118, 10 per cell 289 and 236.
-        const double ppc = a.nc > 0 ? (double)a.n / (double)a.nc : 0.0;
-        if (ppc >= (KF == PI_PAIRFN_HIGHFLOP ? 6.0 : 3.0))
-            PI_LAUNCH(ctx, "k_pairfn_nolds", (k_pairfn_nolds<true, KF, PREC, INV>), dim3(nblk), dim3(kBlock), 0, s,
-                      a);
+        if (pf_cell_walk<KF>(ctx, a, nblk))
+            PI_LAUNCH(ctx, "k_pairfn_nolds_cells", (k_pairfn_nolds<true, KF, PREC, INV>), dim3(nblk), dim3(kBlock), 0,
+                      s, a);
         else
             PI_LAUNCH(ctx, "k_pairfn_nolds", (k_pairfn_nolds<false, KF, PREC, INV>), dim3(nblk), dim3(kBlock), 0, s,
                       a);
