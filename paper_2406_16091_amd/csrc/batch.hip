@@ -22,6 +22,7 @@ struct BatchGroup {
     int tile;
     int32_t first, count;
     int64_t blocks, part_base;
+    int64_t dense_blocks; // of the dense pass, among `blocks`
 };
 
 struct pi_batch {
@@ -169,7 +170,7 @@ pi_status launch_all(pi_batch *b, const float *x, const float *y, const float *z
             if (i < lanes) PI_CHECK_HIP(hipStreamWaitEvent(gs, b->binned, 0));
         }
         st = pi_sweep_batch(b->ctx, b->cells, g.count, b->d_sweep + g.first, b->d_kcs + g.first, g.blocks,
-                            g.part_base, g.tile, o, rho, gx, gy, gz, count, inv, gs);
+                            g.dense_blocks, g.part_base, g.tile, o, rho, gx, gy, gz, count, inv, gs);
         if (st != PI_OK) return st;
         if (fork && lane > 0 && i + lanes >= ng) PI_CHECK_HIP(hipEventRecord(b->done[lane - 1], gs));
     }
@@ -290,7 +291,7 @@ pi_status pi_batch_run_orgs(pi_ctx *ctx, pi_batch *b, int32_t nsys, const pi_sys
         g.tile = b->tile_of[order[i]];
         g.first = i;
         g.count = j - i;
-        g.blocks = pi_batch_layout(g.tile, b->h_sweep.data() + i, g.count);
+        g.blocks = pi_batch_layout(g.tile, b->h_sweep.data() + i, g.count, &g.dense_blocks);
         g.part_base = part_base;
         part_base += g.blocks;
         b->groups.push_back(g);

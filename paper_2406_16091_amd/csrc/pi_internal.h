@@ -256,6 +256,7 @@ struct SysDev {
     int32_t n;
     int32_t cell_base;
     int32_t block_base; // first workgroup of this system in a sweep launch
+    int32_t dense_base; // and in the dense pass of a tile sweep
     int32_t ntx, nty;   // tiles per axis in that launch
     int32_t orig;       // index of the system in the caller's list
     GridDev g;
@@ -270,7 +271,7 @@ bool pi_tile_shape(int tile_id, int *tx, int *ty, int *tz);
 int pi_pick_tile(const pi_interact_opts &o, double ppc);
 void pi_tile_opts(int tile_id, pi_interact_opts *out);
 int pi_auto_tile(pi_ctx *ctx, int precision, int64_t n, double ppc, bool alone);
-int64_t pi_batch_layout(int tile_id, SysDev *h_sys, int32_t nsys);
+int64_t pi_batch_layout(int tile_id, SysDev *h_sys, int32_t nsys, int64_t *dense_blocks);
 int pi_batch_org(int tile_id);
 bool pi_org_valid(int id);
 constexpr int kOrgStream = 9; // organisation id of the stream sweep
@@ -288,8 +289,9 @@ pi_status pi_batch_run_orgs(pi_ctx *ctx, pi_batch *b, int32_t nsys, const pi_sys
                             const pi_interact_opts *opts, float *rho, float *gx, float *gy, float *gz,
                             int32_t *count, pi_invariants *inv, pi_stream stream);
 pi_status pi_sweep_batch(pi_ctx *ctx, pi_cells *cells, int32_t nsys, const SysDev *d_sys, const KernelConst *d_kcs,
-                         int64_t total_blocks, int64_t part_base, int tile_id, const pi_interact_opts &o, float *rho,
-                         float *gx, float *gy, float *gz, int32_t *count, pi_invariants *inv, hipStream_t stream);
+                         int64_t total_blocks, int64_t dense_blocks, int64_t part_base, int tile_id,
+                         const pi_interact_opts &o, float *rho, float *gx, float *gy, float *gz, int32_t *count,
+                         pi_invariants *inv, hipStream_t stream);
 
 // The sweep of pi_interact (sweep.hip) on a binned system whose invariant
 // partial records live in `partials` (cap_partials records of 64 bytes).

@@ -49,16 +49,19 @@ struct SweepArgs {
     const SysDev *sys;
     const KernelConst *kcs;
     int32_t nsys;
+    int32_t dense_blocks; // workgroups of the dense pass of a tile sweep
 };
 
-// Batch mode: the system owning logical workgroup lb; narrows the sweep
-// arguments to that system (its grid, cell offsets and kernel constants).
+// Batch mode: the system owning logical workgroup lb (DENSE: of the dense pass);
+// narrows the sweep arguments to that system (its grid, cell offsets and kernel
+// constants).
+template <bool DENSE = false>
 __device__ __forceinline__ int enter_system(SweepArgs &a, uint32_t lb)
 {
     int lo = 0, hi = a.nsys; // sys[lo].block_base <= lb < sys[hi].block_base
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
-        if ((uint32_t)a.sys[mid].block_base <= lb) lo = mid; else hi = mid;
+        if ((uint32_t)(DENSE ? a.sys[mid].dense_base : a.sys[mid].block_base) <= lb) lo = mid; else hi = mid;
     }
     const SysDev &sd = a.sys[lo];
     a.nx = sd.g.nx;
@@ -277,38 +280,36 @@ __device__ __forceinline__ void in_register(uint32_t &v)
 // and copies than it saved (2.61).  Sweep times, no-LDS walk and this: clustered
 // 2^23 3.29 and 2.25 ms, 2^21 at 64 per cell 3.08 and 2.33 ms (plain sums 2.48
 // and 2.02), 24 per cell 1.65 and 1.15 ms; clustered 3e4 0.43 and 0.19 ms.
-template <int Q, int RING, int PREC, bool INV, bool BATCH>
-__global__ __launch_bounds__(kBlock, 4) void k_sweep_stream(SweepArgs a)
-{
+// Per wavefront: the ring of staged chunks (cell-relative position and weight, and
+// the cell along X from the group's first; the entry past it holds zeros, for lanes
+// without work), each chunk's row shift, the operand of the chunk being tested, and
+// each lane's masks.
+constexpr int kStreamQ = 2, kStreamRing = 4;
+
+template <int Q, int RING>
+struct StreamLds {
     static_assert((Q & (Q - 1)) == 0 && Q <= 4, "a lane's chunk numbers are four bytes of one word");
     static_assert((RING & (RING - 1)) == 0 && RING <= 64, "ring slots are the low bits of a chunk number");
-    constexpr int kWaves = kBlock / 64;
-    constexpr uint32_t kNone = RING * 64; // an entry of zeros, for lanes without work
-    // per wavefront: the ring of staged chunks (cell-relative position and
-    // weight, and the cell along X from the group's first), each chunk's row
-    // shift, the operand of the chunk being tested, and each lane's masks
-    __shared__ float4 ring_p[kWaves][RING * 64 + 1];
-    __shared__ float ring_cx[kWaves][RING * 64 + 1];
-    __shared__ float2 ring_row[kWaves][RING];
-    __shared__ uint32_t opnd[kWaves][4][68];
-    __shared__ uint2 words[kWaves][Q][64];
+    static constexpr int kWaves = kBlock / 64;
+    float4 p[kWaves][RING * 64 + 1];
+    float cx[kWaves][RING * 64 + 1];
+    float2 row[kWaves][RING];
+    uint32_t opnd[kWaves][4][68];
+    uint2 words[kWaves][Q][64];
+};
 
-    const uint32_t lb = xcd_remap(blockIdx.x, gridDim.x);
-    int32_t k, kend;
+// The wavefront's targets: sorted slot k of every lane (the lanes' slots ascend by
+// one), those with `active` set; wi is the target's weight.
+template <int Q, int RING, int PREC, bool INV>
+__device__ __forceinline__ void stream_targets(const SweepArgs &a, StreamLds<Q, RING> &lds, int32_t k, bool active,
+                                               Target<PREC, INV> &T, float &wi)
+{
+    constexpr uint32_t kNone = RING * 64;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (BATCH) {
-        const SysDev &sd = a.sys[enter_system(a, lb)];
-        k = (int32_t)sd.first + (int32_t)(lb - sd.block_base) * kBlock + tid;
-        kend = (int32_t)sd.first + sd.n;
-    } else {
-        k = (int32_t)(lb * kBlock) + tid;
-        kend = min(a.off[a.nc], a.n);
-    }
-    const bool active = k < kend;
     const float W = a.k.w, iw = a.k.inv_w;
     const float reach2 = a.k.reach2;
-    float xi = 0.f, yi = 0.f, zi = 0.f, wi = 0.f;
+    float xi = 0.f, yi = 0.f, zi = 0.f;
     int32_t ix = 0, row = -1;
     if (active) {
         const int32_t c = a.cell[k];
@@ -320,19 +321,18 @@ __global__ __launch_bounds__(kBlock, 4) void k_sweep_stream(SweepArgs a)
         zi = pk.z;
         wi = pk.w;
     }
-    float4 *rp = ring_p[wave];
-    float *rcx = ring_cx[wave];
-    uint2 *myq = &words[wave][0][lane];
+    float4 *rp = lds.p[wave];
+    float *rcx = lds.cx[wave];
+    uint2 *myq = &lds.words[wave][0][lane];
     if (lane == 0) {
         rp[kNone] = make_float4(0.f, 0.f, 0.f, 0.f);
         rcx[kNone] = 0.f;
     }
     const int n = lane & 15, kk = lane >> 4;
-    const uint32_t *acomp = &opnd[wave][kk][16 * (n >> 2) + (n & 3)];
+    const uint32_t *acomp = &lds.opnd[wave][kk][16 * (n >> 2) + (n & 3)];
     const float gyl = yi * yi, gyr = (W - yi) * (W - yi);
     const float gzl = zi * zi, gzr = (W - zi) * (W - zi);
 
-    Target<PREC, INV> T;
     uint64_t m = 0;          // the mask being evaluated, ...
     uint32_t base = 0;       // ... its first entry of the ring, ...
     float ty = 0.f, tz = 0.f; // ... and the target in the frame of its row
@@ -346,7 +346,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_sweep_stream(SweepArgs a)
             m = (uint64_t)w2.x | ((uint64_t)w2.y << 32);
             seq_m = ids & 255u;
             const uint32_t slot = ids & (RING - 1);
-            const float2 sh = ring_row[wave][slot];
+            const float2 sh = lds.row[wave][slot];
             base = slot << 6;
             ty = __builtin_fmaf(-sh.x, W, yi);
             tz = __builtin_fmaf(-sh.y, W, zi);
@@ -477,14 +477,14 @@ __global__ __launch_bounds__(kBlock, 4) void k_sweep_stream(SweepArgs a)
             const float fcx = (float)(cx - cA);
             rp[slot * 64 + lane] = q;
             rcx[slot * 64 + lane] = fcx;
-            if (lane == 0) ring_row[wave][slot] = make_float2((float)dy, (float)dz);
+            if (lane == 0) lds.row[wave][slot] = make_float2((float)dy, (float)dz);
             {
                 const float sx = __builtin_fmaf(q.x, iw, fcx - mid), sy = __builtin_fmaf(q.y, iw, (float)dy - 0.5f),
                             sz = __builtin_fmaf(q.z, iw, (float)dz - 0.5f);
-                opnd[wave][0][lane] = split_f16(sx);
-                opnd[wave][1][lane] = split_f16(sy);
-                opnd[wave][2][lane] = split_f16(sz);
-                opnd[wave][3][lane] = split_f16(sq_dist(sx, sy, sz));
+                lds.opnd[wave][0][lane] = split_f16(sx);
+                lds.opnd[wave][1][lane] = split_f16(sy);
+                lds.opnd[wave][2][lane] = split_f16(sz);
+                lds.opnd[wave][3][lane] = split_f16(sq_dist(sx, sy, sz));
             }
             __builtin_amdgcn_wave_barrier();
             const int32_t cfirst = __builtin_amdgcn_readlane(cx, 0), clast = __builtin_amdgcn_readlane(cx, len - 1);
@@ -531,6 +531,26 @@ __global__ __launch_bounds__(kBlock, 4) void k_sweep_stream(SweepArgs a)
             do round(); while (__any((m != 0) | (cnt > 0)));
         }
     }
+}
+
+template <int PREC, bool INV, bool BATCH>
+__global__ __launch_bounds__(kBlock, 4) void k_sweep_stream(SweepArgs a)
+{
+    __shared__ StreamLds<kStreamQ, kStreamRing> lds;
+    const uint32_t lb = xcd_remap(blockIdx.x, gridDim.x);
+    int32_t k, kend;
+    if (BATCH) {
+        const SysDev &sd = a.sys[enter_system(a, lb)];
+        k = (int32_t)sd.first + (int32_t)(lb - sd.block_base) * kBlock + (int32_t)threadIdx.x;
+        kend = (int32_t)sd.first + sd.n;
+    } else {
+        k = (int32_t)(lb * kBlock + threadIdx.x);
+        kend = min(a.off[a.nc], a.n);
+    }
+    const bool active = k < kend;
+    Target<PREC, INV> T;
+    float wi = 0.f;
+    stream_targets(a, lds, k, active, T, wi);
     if (active) write_target(a, k, T);
     if (INV) {
         long long cn = 0;
@@ -558,47 +578,8 @@ __global__ __launch_bounds__(kBlock, 4) void k_sweep_stream(SweepArgs a)
 // organisations).
 //
 // A tile whose halo holds more than CAP particles is flagged and left to the
-// dense pass, which walks each of its targets from global memory with the
-// row walk of the no-LDS sweep (each neighbour X-row's up to three cells as
-// one range, cells surely beyond the cutoff trimmed; same sources, same
-// order, same roundings, so the same results).
-template <int PREC, bool INV>
-__device__ __forceinline__ void walk_rows_global(const SweepArgs &a, int32_t k, int32_t ix, int32_t iy, int32_t iz,
-                                                 float xi, float yi, float zi, Target<PREC, INV> &T)
-{
-    const float W = a.k.w;
-    const float reach2 = a.k.reach2;
-    const float xm = xi - (float)(-1) * W, xp = xi - (float)(1) * W;
-    const float gyl = yi * yi, gyr = (W - yi) * (W - yi);
-    const float gzl = zi * zi, gzr = (W - zi) * (W - zi);
-    const float tl = ix > 0 ? reach2 - xi * xi : -1.0f;
-    const float tr = ix + 1 < a.nx ? reach2 - (W - xi) * (W - xi) : -1.0f;
-    for (int dz = -1; dz <= 1; ++dz) {
-        const int32_t cz = iz + dz;
-        if (cz < 0 || cz >= a.nz) continue;
-        const float tz = zi - (float)dz * W;
-        const float gz = dz < 0 ? gzl : (dz > 0 ? gzr : 0.f);
-        for (int dy = -1; dy <= 1; ++dy) {
-            const int32_t cy = iy + dy;
-            if (cy < 0 || cy >= a.ny) continue;
-            const float gyz = (dy < 0 ? gyl : (dy > 0 ? gyr : 0.f)) + gz;
-            if (gyz >= reach2) continue;
-            const float ty = yi - (float)dy * W;
-            const int64_t rb = (int64_t)a.nx * (cy + (int64_t)a.ny * cz) + ix;
-            const int32_t b1 = a.off[rb], b2 = a.off[rb + 1];
-            const int32_t j0 = gyz < tl ? a.off[rb - 1] : b1;
-            const int32_t j3 = gyz < tr ? a.off[rb + 2] : b2;
-            for (int32_t j = j0; j < j3; ++j) {
-                const float tx = j < b1 ? xm : (j < b2 ? xi : xp);
-                const float4 s = a.p4[j];
-                const float ddx = tx - s.x, ddy = ty - s.y, ddz = tz - s.z;
-                const float t = sq_dist(ddx, ddy, ddz);
-                if (t < a.k.hi && j != k && inside_cutoff<PREC>(ddx, ddy, ddz, t, a.k))
-                    T.accept(ddx, ddy, ddz, t, s.w, a.k);
-            }
-        }
-    }
-}
+// dense pass, which takes its targets by the stream's walk (same sources, same
+// order, same results).
 
 // X-pencils (k_sweep_pencil).  The (up to) three cells a target needs from one
 // X-row form a single range: 9 row segments per target instead of 27 cells.
@@ -1004,12 +985,15 @@ __global__ __launch_bounds__(kBlock, CAP <= 768 ? 6 : 4) void k_sweep_tile(Sweep
     long long icnt = 0;
     double inx = 0, iny = 0, inz = 0, isc = 0, irs = 0;
 
-    if (tid == 0) a.tflag[lb] = total > CAP ? 1 : 0;
-    if (total > CAP) {
-        // halo too large for LDS: the dense pass (k_sweep_dense, or
-        // k_sweep_dense_batch for a batch) takes this tile's targets, one
-        // thread each across the system, so a dense region is not left to
-        // one workgroup
+    // halo too large for LDS, or so many targets in a few cells that this workgroup
+    // would still be at them when the others are done: the dense pass (k_sweep_dense,
+    // or k_sweep_dense_batch for a batch) takes this tile's targets, one thread each
+    // across the system.  (Two rounds of targets are a full halo's in the shapes that
+    // the static rule picks; 2^13 particles of which nine in ten lie in 8 blobs,
+    // 8 per cell on average: sweep 867 us without the second limit, 641 with it.)
+    const bool overflow = total > CAP || ntarget > 2 * kBlock;
+    if (tid == 0) a.tflag[lb] = overflow ? 1 : 0;
+    if (overflow) {
         if (!BATCH && tid == 0) *a.ovf = a.epoch;
         if (INV) reduce_invariants(a, lb, 0, 0.0, 0.0, 0.0, 0.0, 0.0);
         return;
@@ -1584,17 +1568,52 @@ __global__ __launch_bounds__(kCellBlock) void k_sweep_cell(SweepArgs a, int32_t 
     if (INV) wave_reduce_partial(a.partials + lb, icnt, inx, iny, inz, isc, irs);
 }
 
-// The dense pass of a single-system tile sweep: the targets of every tile
-// whose halo overflowed the LDS area, each walked from global memory by one
-// thread (the same walk and order as the tiles, so the same results).  A
-// persistent grid strides over the particles; when the overflow word does
-// not hold this launch's epoch, no tile overflowed and each workgroup only
-// writes an empty partial record.  Tile shape (tx, ty, tz) and tile counts
-// are those of the tile launch.
+// Invariant sums of a lane over the targets it took.
+struct DenseSums {
+    long long cnt = 0;
+    double nx = 0, ny = 0, nz = 0, sc = 0, rs = 0;
+};
+
+// Sorted slot k of every lane, if its tile is flagged, by the stream's walk.
 template <int PREC, bool INV>
-__global__ __launch_bounds__(kBlock) void k_sweep_dense(SweepArgs a, int32_t tx, int32_t ty, int32_t tz,
-                                                        int32_t ntx, int32_t nty, uint32_t rec0)
+__device__ __forceinline__ void dense_targets(const SweepArgs &a, StreamLds<kStreamQ, kStreamRing> &lds, int32_t k,
+                                              int32_t kend, const uint8_t *flags, int32_t tx, int32_t ty, int32_t tz,
+                                              int32_t ntx, int32_t nty, DenseSums &sums)
 {
+    bool active = k < kend;
+    if (active) {
+        const int32_t c = a.cell[k];
+        const int32_t ix = c % a.nx, iy = (c / a.nx) % a.ny, iz = c / (a.nx * a.ny);
+        active = flags[ix / tx + ntx * (iy / ty + nty * (iz / tz))] != 0;
+    }
+    if (!__any(active)) return;
+    Target<PREC, INV> T;
+    float wi = 0.f;
+    stream_targets(a, lds, k, active, T, wi);
+    if (!active) return;
+    write_target(a, k, T);
+    if (INV) {
+        long long c1;
+        double a1, a2, a3, a4, a5;
+        target_invariants(T, wi, c1, a1, a2, a3, a4, a5);
+        sums.cnt += c1; sums.nx += a1; sums.ny += a2; sums.nz += a3; sums.sc += a4; sums.rs += a5;
+    }
+}
+
+// The dense pass of a single-system tile sweep: the targets of every tile
+// whose halo overflowed the LDS area, by the stream's walk (its outputs are the
+// no-LDS walk's bit for bit).  A persistent grid strides over the particles; when
+// the overflow word does not hold this launch's epoch, no tile overflowed and
+// each workgroup only writes an empty partial record.  Tile shape (tx, ty, tz) and
+// tile counts are those of the tile launch.  (With a thread per target that walked
+// the rows from global memory, as the no-LDS walk does, the sweep of 2^20 particles
+// of which nine in ten lie in 64 blobs, 8 per cell on average, took 2.10 ms; with
+// this it takes 1.04, and the no-LDS walk alone 1.44.)
+template <int PREC, bool INV>
+__global__ __launch_bounds__(kBlock, 4) void k_sweep_dense(SweepArgs a, int32_t tx, int32_t ty, int32_t tz,
+                                                           int32_t ntx, int32_t nty, uint32_t rec0)
+{
+    __shared__ StreamLds<kStreamQ, kStreamRing> lds;
     __shared__ uint32_t any;
     if (threadIdx.x == 0) any = *(volatile uint32_t *)a.ovf == a.epoch ? 1u : 0u;
     __syncthreads();
@@ -1609,73 +1628,40 @@ __global__ __launch_bounds__(kBlock) void k_sweep_dense(SweepArgs a, int32_t tx,
         }
         return;
     }
-    long long icnt = 0;
-    double inx = 0, iny = 0, inz = 0, isc = 0, irs = 0;
-    {
-        const int32_t kend = min(a.off[a.nc], a.n);
-        for (int32_t k = (int32_t)(blockIdx.x * kBlock + threadIdx.x); k < kend; k += (int32_t)(gridDim.x * kBlock)) {
-            const int32_t c = a.cell[k];
-            const int32_t ix = c % a.nx, iy = (c / a.nx) % a.ny, iz = c / (a.nx * a.ny);
-            const int32_t tile = ix / tx + ntx * (iy / ty + nty * (iz / tz));
-            if (!a.tflag[tile]) continue;
-            Target<PREC, INV> T;
-            const float4 pk = a.p4[k];
-            walk_rows_global(a, k, ix, iy, iz, pk.x, pk.y, pk.z, T);
-            write_target(a, k, T);
-            if (INV) {
-                long long c1;
-                double a1, a2, a3, a4, a5;
-                target_invariants(T, pk.w, c1, a1, a2, a3, a4, a5);
-                icnt += c1; inx += a1; iny += a2; inz += a3; isc += a4; irs += a5;
-            }
-        }
-    }
-    if (INV) reduce_invariants(a, rec0 + blockIdx.x, icnt, inx, iny, inz, isc, irs);
+    DenseSums sums;
+    const int32_t kend = min(a.off[a.nc], a.n);
+    for (int32_t k0 = (int32_t)blockIdx.x * kBlock; k0 < kend; k0 += (int32_t)gridDim.x * kBlock)
+        dense_targets<PREC, INV>(a, lds, k0 + (int32_t)threadIdx.x, kend, a.tflag, tx, ty, tz, ntx, nty, sums);
+    if (INV) reduce_invariants(a, rec0 + blockIdx.x, sums.cnt, sums.nx, sums.ny, sums.nz, sums.sc, sums.rs);
 }
 
-// The dense pass of a batch tile sweep.  Each system's workgroups in the
-// launch are its tiles followed by its dense workgroups (the batch layout);
-// a dense workgroup first checks whether any tile of its system overflowed
-// (the flags the tile launch just wrote) and, if so, strides over the
-// system's particles and walks from global memory the targets of flagged
-// tiles.  Its invariant partial record stays in the system's range.
+// The dense pass of a batch tile sweep, one launch of all systems' dense workgroups
+// (the tiles' flags and every partial record are laid out as each system's tiles
+// followed by its dense workgroups).  A dense workgroup first checks whether any
+// tile of its system overflowed (the flags the tile launch just wrote) and, if so,
+// strides over the system's particles and takes the targets of flagged tiles.
 template <int PREC, bool INV>
-__global__ __launch_bounds__(kBlock) void k_sweep_dense_batch(SweepArgs a, int32_t tx, int32_t ty, int32_t tz,
-                                                              int32_t total_blocks)
+__global__ __launch_bounds__(kBlock, 4) void k_sweep_dense_batch(SweepArgs a, int32_t tx, int32_t ty, int32_t tz)
 {
-    const uint32_t lb = blockIdx.x;
-    const int s = enter_system(a, lb);
+    __shared__ StreamLds<kStreamQ, kStreamRing> lds;
+    const int s = enter_system<true>(a, blockIdx.x);
     const SysDev &sd = a.sys[s];
     const int32_t ntx = sd.ntx, nty = sd.nty, ntz = (a.nz + tz - 1) / tz;
     const int32_t ntiles = ntx * nty * ntz;
-    const int32_t d = (int32_t)(lb - (uint32_t)sd.block_base) - ntiles;
-    if (d < 0) return; // a tile's workgroup
-    const int32_t nd = (s + 1 < a.nsys ? a.sys[s + 1].block_base : total_blocks) - sd.block_base - ntiles;
+    const int32_t d = (int32_t)blockIdx.x - sd.dense_base;
+    const int32_t nd = (s + 1 < a.nsys ? a.sys[s + 1].dense_base : a.dense_blocks) - sd.dense_base;
+    const uint32_t lb = (uint32_t)(sd.block_base + ntiles + d);
     const uint8_t *flags = a.tflag + sd.block_base;
     int any = 0;
     for (int32_t t = (int32_t)threadIdx.x; t < ntiles && !any; t += kBlock) any = flags[t];
     any = __syncthreads_or(any);
-    long long icnt = 0;
-    double inx = 0, iny = 0, inz = 0, isc = 0, irs = 0;
+    DenseSums sums;
     if (any) {
         const int32_t kend = (int32_t)sd.first + sd.n;
-        for (int32_t k = (int32_t)sd.first + d * kBlock + (int32_t)threadIdx.x; k < kend; k += nd * kBlock) {
-            const int32_t c = a.cell[k];
-            const int32_t ix = c % a.nx, iy = (c / a.nx) % a.ny, iz = c / (a.nx * a.ny);
-            if (!flags[ix / tx + ntx * (iy / ty + nty * (iz / tz))]) continue;
-            Target<PREC, INV> T;
-            const float4 pk = a.p4[k];
-            walk_rows_global(a, k, ix, iy, iz, pk.x, pk.y, pk.z, T);
-            write_target(a, k, T);
-            if (INV) {
-                long long c1;
-                double a1, a2, a3, a4, a5;
-                target_invariants(T, pk.w, c1, a1, a2, a3, a4, a5);
-                icnt += c1; inx += a1; iny += a2; inz += a3; isc += a4; irs += a5;
-            }
-        }
+        for (int32_t k0 = (int32_t)sd.first + d * kBlock; k0 < kend; k0 += nd * kBlock)
+            dense_targets<PREC, INV>(a, lds, k0 + (int32_t)threadIdx.x, kend, flags, tx, ty, tz, ntx, nty, sums);
     }
-    if (INV) reduce_invariants(a, lb, icnt, inx, iny, inz, isc, irs);
+    if (INV) reduce_invariants(a, lb, sums.cnt, sums.nx, sums.ny, sums.nz, sums.sc, sums.rs);
 }
 
 // FP64 reduction of the per-workgroup partials in two fixed-order stages
@@ -1921,8 +1907,8 @@ void launch_tile(pi_ctx *ctx, const char *name, const SweepArgs &a, hipStream_t 
         else
             PI_LAUNCH(ctx, name, (k_sweep_tile<TX, TY, TZ, CAP, PREC, INV, BATCH>), dim3(nblk), dim3(kBlock), 0, s, a,
                       ntx, nty);
-        PI_LAUNCH(ctx, "k_sweep_dense_batch", (k_sweep_dense_batch<PREC, INV>), dim3(nblk), dim3(kBlock), 0, s, a, TX,
-                  TY, TZ, (int32_t)nblk);
+        PI_LAUNCH(ctx, "k_sweep_dense_batch", (k_sweep_dense_batch<PREC, INV>), dim3((unsigned)a.dense_blocks),
+                  dim3(kBlock), 0, s, a, TX, TY, TZ);
         return;
     }
     SweepArgs b = a;
@@ -2007,7 +1993,7 @@ void launch_sweep(pi_ctx *ctx, int tile_id, const SweepArgs &a, hipStream_t s, u
             nblk = (unsigned)((a.n + kBlock - 1) / kBlock);
             if (nblk == 0) nblk = 1;
         }
-        PI_LAUNCH(ctx, "k_sweep_stream", (k_sweep_stream<2, 4, PREC, INV, BATCH>), dim3(nblk), dim3(kBlock), 0, s,
+        PI_LAUNCH(ctx, "k_sweep_stream", (k_sweep_stream<PREC, INV, BATCH>), dim3(nblk), dim3(kBlock), 0, s,
                   a);
         break;
     default:
@@ -2164,37 +2150,41 @@ int pi_batch_org(int tile)
 
 // Batch sweep: h_sys gets each system's block_base / ntx / nty for tile_id
 // (the caller uploads the table to d_sys before launching).  Returns the
-// total workgroup count.
-int64_t pi_batch_layout(int tile_id, SysDev *h_sys, int32_t nsys)
+// total workgroup count, and the dense pass's in *dense_blocks.
+int64_t pi_batch_layout(int tile_id, SysDev *h_sys, int32_t nsys, int64_t *dense_blocks)
 {
     int tx = 0, ty = 0, tz = 0;
     const bool tiled = tile_id > 0 && pi_tile_shape(tile_id, &tx, &ty, &tz);
     const bool cell = tiled && tile_cfg(tile_id).sweep == PI_SWEEP_CELL;
     if (cell) ty = tz = 1; // runs of tx cells
-    int64_t base = 0;
+    int64_t base = 0, dense = 0;
     for (int32_t s = 0; s < nsys; ++s) {
         SysDev &d = h_sys[s];
         d.block_base = (int32_t)base;
+        d.dense_base = (int32_t)dense;
         if (tiled) {
             d.ntx = (d.g.nx + tx - 1) / tx;
             d.nty = (d.g.ny + ty - 1) / ty;
             const int32_t ntz = (d.g.nz + tz - 1) / tz;
             base += (int64_t)d.ntx * d.nty * ntz;
             // the dense workgroups of an LDS tiling (none for the cell-SM)
-            if (!cell) base += batch_dense_blocks(d.n);
+            if (!cell) dense += batch_dense_blocks(d.n);
         } else {
             d.ntx = d.nty = 0;
             base += (d.n + kBlock - 1) / kBlock;
         }
+        base += dense - d.dense_base;
     }
+    *dense_blocks = dense;
     return base;
 }
 
 // One sweep launch over the systems of table d_sys[0 .. nsys) (all with tile
 // tile_id); their workgroup partials go to records part_base + block.
 pi_status pi_sweep_batch(pi_ctx *ctx, pi_cells *cells, int32_t nsys, const SysDev *d_sys, const KernelConst *d_kcs,
-                         int64_t total_blocks, int64_t part_base, int tile_id, const pi_interact_opts &o, float *rho,
-                         float *gx, float *gy, float *gz, int32_t *count, pi_invariants *inv, hipStream_t stream)
+                         int64_t total_blocks, int64_t dense_blocks, int64_t part_base, int tile_id,
+                         const pi_interact_opts &o, float *rho, float *gx, float *gy, float *gz, int32_t *count,
+                         pi_invariants *inv, hipStream_t stream)
 {
     if (part_base + total_blocks > cells->cap_partials) return PI_ENOMEM;
     SweepArgs a;
@@ -2215,6 +2205,7 @@ pi_status pi_sweep_batch(pi_ctx *ctx, pi_cells *cells, int32_t nsys, const SysDe
     a.sys = d_sys;
     a.kcs = d_kcs;
     a.nsys = nsys;
+    a.dense_blocks = (int32_t)dense_blocks;
     unsigned nblk = (unsigned)total_blocks;
     if (nblk > 0) launch_sweep_prec<true>(ctx, o.precision, true, tile_id, a, stream, nblk);
     if (inv)
