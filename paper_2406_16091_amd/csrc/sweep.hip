@@ -2217,11 +2217,19 @@ pi_status pi_sweep_batch(pi_ctx *ctx, pi_cells *cells, int32_t nsys, const SysDe
 
 namespace {
 
+// The precision a class is timed under: a time step's is that of the sweep whose
+// option it takes, so a class that pi_interact or pi_tuner_choice timed serves
+// pi_step too, also under capture (a set of trials is 0.1 s at 2^24 particles).
+int tune_precision(int prec)
+{
+    return prec == kPrecStep ? PI_PREC_COMPENSATED : prec;
+}
+
 uint64_t tune_key(int prec, int64_t n, double ppc, bool batch)
 {
     const int kn = n > 1 ? (int)floor(2.0 * log2((double)n)) : 0;
     const int kp = (int)fmin(1023.0, floor(4.0 * ppc + 0.5));
-    return (uint64_t)prec + 4ull * (uint64_t)kn + 256ull * (uint64_t)kp + (batch ? (1ull << 30) : 0ull);
+    return (uint64_t)tune_precision(prec) + 4ull * (uint64_t)kn + 256ull * (uint64_t)kp + (batch ? (1ull << 30) : 0ull);
 }
 
 // Time every compiled organisation on this system (the fastest of up to
