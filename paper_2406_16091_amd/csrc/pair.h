@@ -23,15 +23,17 @@ struct KernelConst {
 };
 
 // The arithmetic of a time step with PI_PREC_COMPENSATED: h^2 - r^2 by FP32
-// error-free transforms and Kahan-compensated FP32 sums, as the first time
-// steps of this library had them.  A last bit of G that differs moves some
+// error-free transforms and Kahan-compensated FP32 sums; with PI_PREC_FP64ACC the same
+// h^2 - r^2 and FP64 sums of FP32 terms; both as the first time steps of this
+// library had them.  A last bit of G that differs moves some
 // particles to the next point of the position lattice, and the trajectory leaves
 // its earlier course from there (with the FP64 forms below, G differed by up to
 // 1.5e-3 of its mean size after eight steps of 2^24 particles): the time steps
 // keep their arithmetic, so that a simulation can be taken up and checked against
 // earlier runs bit for bit.  In the sub-box tiles at 1 per cell it costs nothing:
 // four steps and a read-back take 8.11 ms either way.
-constexpr int kPrecStep = 3;
+constexpr int kPrecStep = 3, kPrecStep64 = 4;
+constexpr bool step_precision(int prec) { return prec >= kPrecStep; }
 
 // h^2 - (dx^2 + dy^2 + dz^2) in FP64, which the vector units issue at the rate
 // of (non-packed) FP32: the square of a float is exact in double (48
@@ -83,14 +85,14 @@ __device__ __forceinline__ float h2_minus_d2_fp32(float dx, float dy, float dz, 
 template <int PREC>
 __device__ __forceinline__ bool h2_above_d2(float dx, float dy, float dz, const KernelConst &k)
 {
-    if (PREC == kPrecStep) return h2_minus_d2_fp32(dx, dy, dz, k) > 0.0f;
+    if (step_precision(PREC)) return h2_minus_d2_fp32(dx, dy, dz, k) > 0.0f;
     return h2_minus_d2(dx, dy, dz, k) > 0.0;
 }
 
 template <int PREC>
 __device__ __forceinline__ float h2_minus_d2_term(float dx, float dy, float dz, const KernelConst &k)
 {
-    if (PREC == kPrecStep) return h2_minus_d2_fp32(dx, dy, dz, k);
+    if (step_precision(PREC)) return h2_minus_d2_fp32(dx, dy, dz, k);
     return (float)h2_minus_d2(dx, dy, dz, k);
 }
 
@@ -243,6 +245,22 @@ struct Acc<kPrecStep> {
     __device__ __forceinline__ float r_gx() const { return s1 - c1; }
     __device__ __forceinline__ float r_gy() const { return s2 - c2; }
     __device__ __forceinline__ float r_gz() const { return s3 - c3; }
+};
+
+template <>
+struct Acc<kPrecStep64> {
+    double rho = 0.0, gx = 0.0, gy = 0.0, gz = 0.0;
+    __device__ __forceinline__ void add(float a, float f, float dx, float dy, float dz)
+    {
+        rho += (double)a;
+        gx += (double)(f * dx);
+        gy += (double)(f * dy);
+        gz += (double)(f * dz);
+    }
+    __device__ __forceinline__ float r_rho() const { return (float)rho; }
+    __device__ __forceinline__ float r_gx() const { return (float)gx; }
+    __device__ __forceinline__ float r_gy() const { return (float)gy; }
+    __device__ __forceinline__ float r_gz() const { return (float)gz; }
 };
 
 // Everything a target keeps while it walks its 27 cells.

@@ -525,6 +525,7 @@ extern "C" pi_status pi_step(pi_ctx *ctx, pi_cells *cells, const pi_step_opts *o
     pi_status st = pi_check_interact_opts(io, n, cells->grho, cells->ggx, cells->ggy, cells->ggz, nullptr, inv);
     if (st != PI_OK) return st;
     if (io.precision == PI_PREC_COMPENSATED) io.precision = kPrecStep;
+    else if (io.precision == PI_PREC_FP64ACC) io.precision = kPrecStep64;
     st = pi_interact_run(ctx, cells, io, cells->grho, cells->ggx, cells->ggy, cells->ggz, nullptr, inv, s,
                          cells->partials, cells->cap_partials, false);
     if (st != PI_OK) return st;

@@ -2021,6 +2021,12 @@ void launch_sweep_prec(pi_ctx *ctx, int prec, bool inv, int tile_id, const Sweep
             else launch_sweep<kPrecStep, false, false>(ctx, tile_id, a, s, nblk);
         }
         break;
+    case kPrecStep64: // (as kPrecStep)
+        if constexpr (!BATCH) {
+            if (inv) launch_sweep<kPrecStep64, true, false>(ctx, tile_id, a, s, nblk);
+            else launch_sweep<kPrecStep64, false, false>(ctx, tile_id, a, s, nblk);
+        }
+        break;
     // (PI_PREC_FP64ACC is the same arithmetic as PI_PREC_COMPENSATED)
     default:
         if (inv) launch_sweep<PI_PREC_COMPENSATED, true, BATCH>(ctx, tile_id, a, s, nblk);
@@ -2222,7 +2228,7 @@ namespace {
 // pi_step too, also under capture (a set of trials is 0.1 s at 2^24 particles).
 int tune_precision(int prec)
 {
-    return prec == kPrecStep ? PI_PREC_COMPENSATED : prec;
+    return prec == kPrecStep ? PI_PREC_COMPENSATED : (prec == kPrecStep64 ? PI_PREC_FP64ACC : prec);
 }
 
 uint64_t tune_key(int prec, int64_t n, double ppc, bool batch)

@@ -19,10 +19,13 @@ SYSTEMS = {
 }
 PINNED = {
     ("1ppc", "compensated"): "0967a52d1dbfbe00932f46a4064b4f0c",
+    ("1ppc", "fp64acc"): "6fd0a14c7a417bfb1499553160aa7653",
     ("1ppc", "plain"): "49e43c581ec078d6cafd392ea9a28892",
     ("8ppc", "compensated"): "c09d7e3d2e6dd24f297fe7da2b3c804d",
+    ("8ppc", "fp64acc"): "58194cd7c01fbb4e10076e2d98d41b0c",
     ("8ppc", "plain"): "1ad6b1c065accf0cb452ad0f54bfddcd",
     ("blobs", "compensated"): "ea0100796a1f331d14960c356d2e9be3",
+    ("blobs", "fp64acc"): "18bc795a82f7d15347c2fbdeb047592d",
     ("blobs", "plain"): "a329fe8827aa0c8e77e8dde7f146b224",
 }
 ORGANISATIONS = [("auto", (0, 0, 0)), ("nolds", (0, 0, 0)), ("stream", (0, 0, 0)), ("pencil", (30, 1, 1)),
