@@ -137,10 +137,13 @@ pi_status pi_cells_get_view(pi_cells *cells, pi_cells_view *out);
 /* Accumulation precision of the sweep. */
 #define PI_PREC_COMPENSATED 0 /* FP32 terms with h^2 - r^2 formed in FP64 for
                                  q > 1/2, sums in FP64 (they hold more than
-                                 compensated FP32 sums, and cost less) */
+                                 compensated FP32 sums, and cost less); in
+                                 pi_step h^2 - r^2 by FP32 error-free transforms
+                                 and Kahan-compensated FP32 sums */
 #define PI_PREC_PLAIN       1 /* FP32 terms (1 - q from q), plain FP32 sums */
 #define PI_PREC_FP64ACC     2 /* the terms of PI_PREC_COMPENSATED, FP64 sums: the
-                                 same arithmetic */
+                                 same arithmetic, but in pi_step, which has FP64
+                                 sums of its FP32 terms */
 
 /* Organisation of the sweep. */
 #define PI_SWEEP_AUTO   0 /* chosen by the library's tuner */
@@ -320,7 +323,10 @@ pi_status pi_interact_pairfn(pi_ctx *ctx, const pi_cells *cells, const pi_pairfn
  * and w_i taken as the mass, the force on i is -kappa w_i G_i (G as
  * pi_interact computes it), and one pi_step is:
  *   1. the sweep of pi_interact (opts->precision, opts->sweep) at the
- *      current positions;
+ *      current positions, in FP32 arithmetic of its own with PI_PREC_COMPENSATED
+ *      and PI_PREC_FP64ACC (see there), so that a trajectory repeats bit for bit
+ *      what earlier versions gave: rho and G may differ from pi_interact's in
+ *      their last bits;
  *   2. symplectic Euler, per axis: v <- v - dt kappa G; x <- x + dt v, with
  *      the displacement cut to half a cell width (PI_ESTEP is then latched
  *      and returned by the next pi_sync: reduce dt), reflection at the box
