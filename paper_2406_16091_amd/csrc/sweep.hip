@@ -2223,12 +2223,13 @@ pi_status pi_sweep_batch(pi_ctx *ctx, pi_cells *cells, int32_t nsys, const SysDe
 
 namespace {
 
-// The precision a class is timed under: a time step's is that of the sweep whose
-// option it takes, so a class that pi_interact or pi_tuner_choice timed serves
-// pi_step too, also under capture (a set of trials is 0.1 s at 2^24 particles).
+// The precision a class is timed under: one for all that sum in more than plain FP32,
+// whose sweeps are the same arithmetic or, in a time step, near it in cost.  A class
+// that one call timed serves the others, also under capture (a set of trials is 0.1
+// s at 2^24 particles).
 int tune_precision(int prec)
 {
-    return prec == kPrecStep ? PI_PREC_COMPENSATED : (prec == kPrecStep64 ? PI_PREC_FP64ACC : prec);
+    return prec == PI_PREC_PLAIN ? PI_PREC_PLAIN : PI_PREC_COMPENSATED;
 }
 
 uint64_t tune_key(int prec, int64_t n, double ppc, bool batch)

@@ -56,3 +56,18 @@ def test_a_tuned_sweep_serves_the_time_steps():
     ds.sync()
     assert _returns_at_once(ds, step(ds))
     ds.close()
+
+
+def test_a_tuned_sweep_serves_the_other_name_of_its_arithmetic():
+    from paper_2406_16091_amd import device
+
+    def sweep(ds):
+        return lambda: ds.interact(precision="fp64acc")
+
+    _warm(sweep)
+    ds = device.DeviceSystem(_system(53, 3))
+    ds.bin()
+    ds.interact()
+    ds.sync()
+    assert _returns_at_once(ds, sweep(ds))
+    ds.close()
