@@ -627,7 +627,8 @@ __global__ __launch_bounds__(1024) void k_max_reduce(const int32_t *__restrict__
 // Bucket sort: a workgroup takes the 2^low_bits consecutive cells whose ids
 // share their top bits (after a radix pass over those; or all cells and the
 // caller's arrays, FIRST) and writes every final array of theirs: the particles
-// in order, counts, offsets and M_C.  A call of few particles is bound by its
+// in order, counts, offsets and M_C; a bucket of more than kFast particles is shared
+// by several.  A call of few particles is bound by its
 // launches and the latency of each (5 to 12 µs a kernel, a CU or a few busy), so
 // this replaces eight launches (two radix passes of three) by one, or by three or
 // four: 512 particles in 8^3 cells took 67 µs in them and take 9, 32768 in 32^3
@@ -642,6 +643,7 @@ constexpr int kFast = kFItems * kBBlock; // a small bucket: at most this many pa
 constexpr int kFastCell = 64;            // and this many in its fullest cell
 constexpr int kBucketCounters = 1 << 15; // counters of a large bucket's wavefronts
 constexpr int64_t kBucketMax = 64 * kSortTile; // most particles sorted by buckets
+static_assert(kSortTile <= kFast, "all particles of a binning without radix passes are one small bucket");
 
 template <bool FIRST>
 __global__ __launch_bounds__(kBBlock) void k_bucket_sort(SortArgs a)
@@ -657,16 +659,36 @@ __global__ __launch_bounds__(kBBlock) void k_bucket_sort(SortArgs a)
     __shared__ int32_t ends[2];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int32_t b = (int32_t)blockIdx.x;
     const int lb = a.low_bits;
-    const int64_t g0 = (int64_t)b << lb;
-    const int32_t ncell = (int32_t)min((int64_t)1 << lb, (int64_t)a.nc - g0);
     const uint32_t lmask = (1u << lb) - 1u;
 
-    // 1. the bucket's range, from the totals of the digits
+    // 1. the workgroup's bucket b and share of it, from the totals of the digits: a
+    //    bucket of more than kFast particles is cut into shares of that many, the
+    //    first of them the bucket's own workgroup's, the others the workgroups'
+    //    after the last bucket's, in order
+    int32_t b = (int32_t)blockIdx.x, share = 0;
     if (!FIRST) {
         static_assert(kRadix <= kBBlock, "a thread per digit");
         const int32_t v = tid < kRadix ? a.dtot[tid] : 0;
+        if (__builtin_expect(b >= a.nbuckets, 0)) {
+            const int32_t more = v > kFast ? (v - 1) / kFast : 0;
+            const int32_t minc = wave_incl_scan(more);
+            if (lane == 63) wsum[wid] = minc;
+            if (tid == 0) ends[0] = -1;
+            __syncthreads();
+            int32_t first = minc - more;
+            for (int w = 0; w < wid; ++w) first += wsum[w];
+            const int32_t x = b - a.nbuckets;
+            if (x >= first && x < first + more) {
+                ends[0] = tid;
+                ends[1] = x - first + 1;
+            }
+            __syncthreads();
+            b = ends[0];
+            share = ends[1];
+            if (b < 0) return; // (one workgroup in 4096 particles is there for the shares; most have none)
+            __syncthreads(); // wsum and ends are rewritten
+        }
         const int32_t inc = wave_incl_scan(v);
         if (lane == 63) wsum[wid] = inc;
         __syncthreads();
@@ -677,6 +699,8 @@ __global__ __launch_bounds__(kBBlock) void k_bucket_sort(SortArgs a)
             ends[1] = before + v;
         }
     }
+    const int64_t g0 = (int64_t)b << lb;
+    const int32_t ncell = (int32_t)min((int64_t)1 << lb, (int64_t)a.nc - g0);
     for (int i = tid; i < ncell; i += kBBlock) start[i] = 0;
     __syncthreads();
     const int32_t s0 = FIRST ? 0 : ends[0];
@@ -695,18 +719,55 @@ __global__ __launch_bounds__(kBBlock) void k_bucket_sort(SortArgs a)
 
     // 2. particles per cell.  A bucket of at most kFast particles keeps them in
     //    registers, and the counter's value is a particle's arrival in its
-    //    cell; in a larger one each wavefront counts a contiguous part.
-    const bool few = m <= kFast;
+    //    cell; of a larger one each wavefront counts a contiguous part of the share
+    //    [r0, r1), and all count the particles before and after it.
+    const bool few = FIRST || m <= kFast;
+    const int32_t r0 = FIRST ? 0 : share * kFast, r1 = min(m, r0 + kFast);
     uint2 kv[kFItems];
     float4 p[kFItems];
     int32_t pos[kFItems];
-    const int sets = min(kBWaves, kBucketCounters >> lb);
-    const int32_t part = (m + 64 * sets - 1) / (64 * sets) * 64;
-    const int32_t e0 = wid * part, e1 = wid < sets ? min(e0 + part, m) : e0;
+    const int sets = min(kBWaves, (kBucketCounters >> lb) - (few ? 0 : 1));
+    const int32_t part = (r1 - r0 + 64 * sets - 1) / (64 * sets) * 64;
+    const int32_t e0 = r0 + wid * part, e1 = wid < sets ? min(e0 + part, r1) : e0;
     int32_t *cnt = reinterpret_cast<int32_t *>(area) + (wid < sets ? wid << lb : 0);
-    auto count_parts = [&]() { // and, from every cell's counts, where the parts start in the cell
+    int32_t *before = reinterpret_cast<int32_t *>(area) + (kBucketCounters - (1 << lb)); // (not few)
+    // the particles [q0, q1) of the bucket counted in `to`, 64 of one cell at once (a
+    // bucket's particles may all lie in one)
+    auto count64 = [&](int32_t *to, uint32_t k) {
+        const uint32_t c = k & lmask;
+        if (__ballot(c != (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)c)) == 0) {
+            if (lane == 0) atomicAdd(&to[c], 64);
+        } else {
+            atomicAdd(&to[c], 1);
+        }
+    };
+    auto count_all = [&](int32_t *to, int32_t q0, int32_t q1) {
+        constexpr int U = 16;
+        const uint2 *kv_in = a.kv_in + s0;
+        int32_t q = q0 + 64 * wid;
+        for (; q + (U - 1) * kBBlock + 64 <= q1; q += U * kBBlock) {
+            uint32_t k[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) k[u] = (kv_in + q + u * kBBlock)[lane].x;
+#pragma unroll
+            for (int u = 0; u < U; ++u) count64(to, k[u]);
+        }
+        for (; q < q1; q += kBBlock) {
+            if (q + 64 <= q1) count64(to, kv_in[q + lane].x);
+            else if (q + lane < q1) atomicAdd(&to[kv_in[q + lane].x & lmask], 1);
+        }
+    };
+    // and, from every cell's counts, where the parts start in the cell (whole: the
+    // share is the bucket)
+    auto count_parts = [&](auto whole) {
         for (int i = tid; i < sets << lb; i += kBBlock) area[i] = 0;
+        if (!whole)
+            for (int i = tid; i < ncell; i += kBBlock) before[i] = 0;
         __syncthreads();
+        if (!whole) {
+            count_all(before, 0, r0);
+            count_all(start, r1, m);
+        }
         for (int32_t e = e0 + lane; e < e1; e += 64) {
             uint32_t k;
             if (FIRST) k = cell_key(a.x[e], a.y[e], a.z[e], a.g, a.err);
@@ -715,17 +776,17 @@ __global__ __launch_bounds__(kBBlock) void k_bucket_sort(SortArgs a)
         }
         __syncthreads();
         for (int i = tid; i < ncell; i += kBBlock) {
-            int32_t run = 0;
+            int32_t run = whole ? 0 : before[i];
             for (int w = 0; w < sets; ++w) {
                 const int32_t c = (int32_t)area[(w << lb) + i];
                 area[(w << lb) + i] = (uint32_t)run;
                 run += c;
             }
-            if (!few) start[i] = run;
+            if (!whole) start[i] += run;
         }
         __syncthreads();
     };
-    if (few) {
+    if (__builtin_expect(few, 1)) {
 #pragma unroll
         for (int r = 0; r < kFItems; ++r) {
             if (r * kBBlock >= m) break;
@@ -739,7 +800,7 @@ __global__ __launch_bounds__(kBBlock) void k_bucket_sort(SortArgs a)
         }
         __syncthreads();
     } else {
-        count_parts();
+        count_parts(std::false_type());
     }
 
     // 3. exclusive scan over the cells (four consecutive ones per thread), the
@@ -772,16 +833,18 @@ __global__ __launch_bounds__(kBBlock) void k_bucket_sort(SortArgs a)
     }
     __syncthreads();
     for (int w = 0; w < kBWaves; ++w) most = max(most, wmost[w]);
-    if (tid == 0) { // (few buckets raise M_C)
+    if (tid == 0 && share == 0) { // (few buckets raise M_C)
         if (FIRST) *a.max_per_cell = most;
         else if (most > *(volatile int32_t *)a.max_per_cell) atomicMax(a.max_per_cell, most);
     }
-    for (int i = tid; i < ncell; i += kBBlock) {
-        const int32_t st = start[i];
-        a.offsets[g0 + i] = s0 + st;
-        a.counts[g0 + i] = start[i + 1] - st;
+    if (share == 0) {
+        for (int i = tid; i < ncell; i += kBBlock) {
+            const int32_t st = start[i];
+            a.offsets[g0 + i] = s0 + st;
+            a.counts[g0 + i] = start[i + 1] - st;
+        }
+        if (tid == 0 && b + 1 == a.nbuckets) a.offsets[a.nc] = a.n;
     }
-    if (tid == 0 && b + 1 == a.nbuckets) a.offsets[a.nc] = a.n;
 
     if (few && most <= kFastCell) {
         // 4a. a small bucket: every cell's particles by arrival in one list, a
@@ -839,10 +902,10 @@ __global__ __launch_bounds__(kBBlock) void k_bucket_sort(SortArgs a)
         return;
     }
 
-    // 4b. a large bucket: each wavefront ranks its part in order, 64 particles at
-    //     a time (ballots), and stores to the final arrays; no barrier after
-    //     the counts
-    if (few) count_parts();
+    // 4b. a share of a large bucket, or a full cell: each wavefront ranks its part in
+    //     order, 64 particles at a time (ballots), and stores to the final arrays; no
+    //     barrier after the counts
+    if (few) count_parts(std::true_type());
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     for (int32_t c0 = e0; c0 < e1; c0 += 64 * kFItems) {
 #pragma unroll
@@ -915,12 +978,17 @@ namespace {
 //   131072   128^2 x 64    103      43
 //   262144   16^3           70      50
 //   262144   64^3           96      46  (8 blobs: 108 and 62)
-//   262144   64^3          180     205  (all in one layer of the cells)
+//   262144   64^3          176      54  (all in one layer of the cells)
+//   262144   64^3          178      78  (in a quarter of a layer, one bucket; one cell: 177 and 80)
+//   262144   32^3           58      61  (one bucket; one cell: 58 and 79, eight cells: 58 and 90)
+//   131072   32^3           57      51  (one bucket; one cell: 58 and 61, eight cells: 57 and 63)
 //   524288   64^3           94      49  (8 blobs: 108 and 83)
-//   524288   64^3          188     418  (all in one layer)
-// The line lies where the layer, whose few full buckets are a workgroup's work
-// each, begins to lose (all in a quarter of a layer, one bucket: 183 and 761 at
-// 262144).  A bucket sort after two passes, with 512 threads, gave 620 for 737
+// A bucket of more than kFast particles is shared by a workgroup for every kFast of
+// them, each of which reads all of the bucket's keys (one workgroup for the whole
+// bucket: 204 us for the layer, 762 and 520 for the bucket and the cell); that grows
+// with the square of a bucket, so the line lies where one bucket, or the few cells of
+// one, begins to lose to two radix passes, while uniform particles gain up to it.
+// A bucket sort after two passes, with 512 threads, gave 620 for 737
 // at 2^24 uniform in 256^3, but 1086 for 744 in 64 blobs there, and was left out.
 struct BucketPlan {
     int passes; // radix passes before the bucket sort (0 or 1), -1: no bucket sort
@@ -1041,7 +1109,10 @@ pi_status pi_bin_systems(pi_ctx *ctx, pi_cells *cells, const float *x, const flo
             else radix_pass<kWideBits>(ctx, a, first, last, batch, stream);
         }
         if (buckets) {
-            const dim3 grid((unsigned)a.nbuckets), block(kBBlock);
+            // (passes > 0: a workgroup per bucket, and one per kFast particles for the
+            // further shares of larger buckets)
+            const unsigned shares = passes > 0 ? (unsigned)((n + kFast - 1) / kFast) : 0u;
+            const dim3 grid((unsigned)a.nbuckets + shares), block(kBBlock);
             a.kv_in = cells->skv[0];
             a.p_in = cells->sp[0];
             if (passes == 0) PI_LAUNCH(ctx, "k_bucket_sort", k_bucket_sort<true>, grid, block, 0, stream, a);
