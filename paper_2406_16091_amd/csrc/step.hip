@@ -478,6 +478,13 @@ __global__ __launch_bounds__(kBlock) void k_unpack_records(int32_t n, const floa
     if (d) d[i] = r.w;
 }
 
+// Whether work queued on s is being captured (also if that cannot be told).
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
+}
+
 inline unsigned nblocks(int64_t n, int b) { return (unsigned)std::max<int64_t>(1, (n + b - 1) / b); }
 
 } // namespace
@@ -608,10 +615,13 @@ extern "C" pi_status pi_state_get(pi_ctx *ctx, pi_cells *cells, float *x, float 
     const dim3 grid(nblocks(n, kBlock)), block(kBlock);
     // The records go to the binning's ping-pong buffers, free between binnings.
     // That needs the stream of the object's last call: a read-back that runs
-    // beside others on another stream scatters straight to its own outputs.
+    // beside others on another stream scatters straight to its own outputs, and so
+    // does one on the per-thread stream, whose handle is another stream in every
+    // thread, and one under capture, whose graph may be launched beside other
+    // read-backs.
     // Below 2^18 particles the outputs stay in the caches and the two launches of
     // the direct scatter are faster than five.
-    if (s == cells->last_stream && n >= kRecordsMin) {
+    if (n >= kRecordsMin && s == cells->last_stream && s != hipStreamPerThread && !capturing(s)) {
         if (px || pv) {
             PI_LAUNCH(ctx, "k_state_records", k_state_records, grid, block, 0, s, (int32_t)n, grid_dev(cells->grid),
                       cells->perm, cells->cell, cells->xyzw, cells->vel, px ? cells->sp[0] : nullptr,
