@@ -284,7 +284,7 @@ pi_status pi_batch_run_orgs(pi_ctx *ctx, pi_batch *b, int32_t nsys, const pi_sys
         int32_t j = i;
         while (j < nsys && b->tile_of[order[j]] == b->tile_of[order[i]]) {
             b->h_sweep[j] = b->h_sys[order[j]];
-            kcs[j] = pi_make_kernel_const(sys[order[j]].grid.rc, sys[order[j]].grid.cell_w);
+            kcs[j] = pi_make_kernel_const(sys[order[j]].grid);
             ++j;
         }
         BatchGroup g;

@@ -266,7 +266,7 @@ bool pi_grid_valid(const pi_grid *g);
 
 struct KernelConst;
 struct pi_interact_opts;
-KernelConst pi_make_kernel_const(float rc, float cell_w);
+KernelConst pi_make_kernel_const(const pi_grid &grid);
 bool pi_tile_shape(int tile_id, int *tx, int *ty, int *tz);
 int pi_pick_tile(const pi_interact_opts &o, double ppc);
 void pi_tile_opts(int tile_id, pi_interact_opts *out);

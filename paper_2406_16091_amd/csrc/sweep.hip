@@ -1791,16 +1791,20 @@ __global__ void k_inv_zero(pi_invariants *__restrict__ out)
 
 } // namespace
 
-KernelConst pi_make_kernel_const(float rc, float cell_w)
+KernelConst pi_make_kernel_const(const pi_grid &grid)
 {
     KernelConst k;
-    const float h = rc;
+    const float h = grid.rc, cell_w = grid.cell_w;
     const double hd = (double)h;
     const double r2 = hd * hd; // exact
     const double u = ldexp(1.0, -24);
     k.lo = nextafterf((float)(r2 * (1.0 - 4.0 * u)), 0.0f);
     k.hi = nextafterf((float)(r2 * (1.0 + 4.0 * u)), INFINITY);
-    k.reach2 = nextafterf((float)(r2 * (1.0 + 16.0 * u)), INFINITY);
+    // (a particle lies at most n u cell widths below the low face of its cell on an
+    // axis of n cells: the rounding of (x - o) / w; twice that covers three axes)
+    const int32_t n = std::max(grid.dims[0], std::max(grid.dims[1], grid.dims[2]));
+    const double reach = hd + 2.0 * u * (double)n * (double)cell_w;
+    k.reach2 = nextafterf((float)(reach * reach * (1.0 + 16.0 * u)), INFINITY);
     k.hh64 = r2;
     k.hh = h * h;
     k.eh = fmaf(h, h, -k.hh);
@@ -2380,7 +2384,7 @@ extern "C" pi_status pi_tuner_choice(pi_ctx *ctx, const pi_cells *cells, int32_t
         a.nx = cells->grid.dims[0];
         a.ny = cells->grid.dims[1];
         a.nz = cells->grid.dims[2];
-        a.k = pi_make_kernel_const(cells->grid.rc, cells->grid.cell_w);
+        a.k = pi_make_kernel_const(cells->grid);
         a.tflag = cells->tflag;
         a.ovf = cells->d_err + 32;
         a.host_epoch = &const_cast<pi_cells *>(cells)->sweep_epoch;
@@ -2465,7 +2469,7 @@ pi_status pi_interact_run(pi_ctx *ctx, const pi_cells *cells, const pi_interact_
     a.gz = gz;
     a.count = count;
     a.partials = (InvPartial *)partials;
-    a.k = pi_make_kernel_const(cells->grid.rc, cells->grid.cell_w);
+    a.k = pi_make_kernel_const(cells->grid);
 
     if (n == 0) {
         if (inv) PI_LAUNCH(ctx, "k_inv_zero", k_inv_zero, dim3(1), dim3(64), 0, stream, inv);
