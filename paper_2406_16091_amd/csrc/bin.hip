@@ -182,6 +182,7 @@ struct SortArgs {
     int32_t nc;       // cells
     int32_t low_bits; // bits of a key that the radix passes leave to it
     int32_t nbuckets;
+    int32_t share; // most particles of a bucket that a workgroup sorts
     const int32_t *gbase; // per digit: exclusive scan of its per-tile counts (few_tiles: the counts)
     int32_t few_tiles;
     int32_t *dtot; // per digit: total count
@@ -628,7 +629,7 @@ __global__ __launch_bounds__(1024) void k_max_reduce(const int32_t *__restrict__
 // share their top bits (after a radix pass over those; or all cells and the
 // caller's arrays, FIRST) and writes every final array of theirs: the particles
 // in order, counts, offsets and M_C; a bucket of more than kFast particles is shared
-// by several.  A call of few particles is bound by its
+// by several (SortArgs::share).  A call of few particles is bound by its
 // launches and the latency of each (5 to 12 µs a kernel, a CU or a few busy), so
 // this replaces eight launches (two radix passes of three) by one, or by three or
 // four: 512 particles in 8^3 cells took 67 µs in them and take 9, 32768 in 32^3
@@ -640,6 +641,7 @@ constexpr int kBWaves = kBBlock / 64;
 constexpr int kLowBits = 12;            // most bits of a key sorted here
 constexpr int kFItems = 4;
 constexpr int kFast = kFItems * kBBlock; // a small bucket: at most this many particles,
+constexpr int64_t kWideShares = 1 << 15; // particles up to which a bucket's shares are of 4 kFast
 constexpr int kFastCell = 64;            // and this many in its fullest cell
 constexpr int kBucketCounters = 1 << 15; // counters of a large bucket's wavefronts
 constexpr int64_t kBucketMax = 64 * kSortTile; // most particles sorted by buckets
@@ -663,7 +665,7 @@ __global__ __launch_bounds__(kBBlock) void k_bucket_sort(SortArgs a)
     const uint32_t lmask = (1u << lb) - 1u;
 
     // 1. the workgroup's bucket b and share of it, from the totals of the digits: a
-    //    bucket of more than kFast particles is cut into shares of that many, the
+    //    bucket of more than a.share particles is cut into shares of that many, the
     //    first of them the bucket's own workgroup's, the others the workgroups'
     //    after the last bucket's, in order
     int32_t b = (int32_t)blockIdx.x, share = 0;
@@ -671,7 +673,7 @@ __global__ __launch_bounds__(kBBlock) void k_bucket_sort(SortArgs a)
         static_assert(kRadix <= kBBlock, "a thread per digit");
         const int32_t v = tid < kRadix ? a.dtot[tid] : 0;
         if (__builtin_expect(b >= a.nbuckets, 0)) {
-            const int32_t more = v > kFast ? (v - 1) / kFast : 0;
+            const int32_t more = v > a.share ? (v - 1) / a.share : 0;
             const int32_t minc = wave_incl_scan(more);
             if (lane == 63) wsum[wid] = minc;
             if (tid == 0) ends[0] = -1;
@@ -686,7 +688,7 @@ __global__ __launch_bounds__(kBBlock) void k_bucket_sort(SortArgs a)
             __syncthreads();
             b = ends[0];
             share = ends[1];
-            if (b < 0) return; // (one workgroup in 4096 particles is there for the shares; most have none)
+            if (b < 0) return; // (there are as many as any distribution asks for; most have none)
             __syncthreads(); // wsum and ends are rewritten
         }
         const int32_t inc = wave_incl_scan(v);
@@ -722,7 +724,7 @@ __global__ __launch_bounds__(kBBlock) void k_bucket_sort(SortArgs a)
     //    cell; of a larger one each wavefront counts a contiguous part of the share
     //    [r0, r1), and all count the particles before and after it.
     const bool few = FIRST || m <= kFast;
-    const int32_t r0 = FIRST ? 0 : share * kFast, r1 = min(m, r0 + kFast);
+    const int32_t r0 = FIRST ? 0 : share * a.share, r1 = FIRST ? m : min(m, r0 + a.share);
     uint2 kv[kFItems];
     float4 p[kFItems];
     int32_t pos[kFItems];
@@ -983,8 +985,8 @@ namespace {
 //   262144   32^3           58      61  (one bucket; one cell: 58 and 79, eight cells: 58 and 90)
 //   131072   32^3           57      51  (one bucket; one cell: 58 and 61, eight cells: 57 and 63)
 //   524288   64^3           94      49  (8 blobs: 108 and 83)
-// A bucket of more than kFast particles is shared by a workgroup for every kFast of
-// them, each of which reads all of the bucket's keys (one workgroup for the whole
+// A bucket of more than kFast particles (four times as many up to 2^15 in all) is
+// shared by a workgroup for every kFast of them, each of which reads all of the bucket's keys (one workgroup for the whole
 // bucket: 204 us for the layer, 762 and 520 for the bucket and the cell); that grows
 // with the square of a bucket, so the line lies where one bucket, or the few cells of
 // one, begins to lose to two radix passes, while uniform particles gain up to it.
@@ -1109,9 +1111,11 @@ pi_status pi_bin_systems(pi_ctx *ctx, pi_cells *cells, const float *x, const flo
             else radix_pass<kWideBits>(ctx, a, first, last, batch, stream);
         }
         if (buckets) {
-            // (passes > 0: a workgroup per bucket, and one per kFast particles for the
-            // further shares of larger buckets)
-            const unsigned shares = passes > 0 ? (unsigned)((n + kFast - 1) / kFast) : 0u;
+            // (passes > 0: a workgroup per bucket, and the further shares of larger
+            // buckets.  A workgroup that has none costs 0.07 us until the launch fills
+            // the GPU: fewer, larger shares for few particles)
+            a.share = n <= kWideShares ? 4 * kFast : kFast;
+            const unsigned shares = passes > 0 ? (unsigned)((n + a.share - 1) / a.share) : 0u;
             const dim3 grid((unsigned)a.nbuckets + shares), block(kBBlock);
             a.kv_in = cells->skv[0];
             a.p_in = cells->sp[0];

@@ -1,5 +1,5 @@
 """Binning of few particles that lie in few buckets of cells: a bucket of more than
-4096 is shared by several workgroups.  Every array bit for bit the oracle's, and no
+4096 (16384 of at most 32768 in all) is shared by several workgroups.  Every array bit for bit the oracle's, and no
 such system much slower than by the radix passes that one particle more would take."""
 import time
 
@@ -40,11 +40,14 @@ CASES = [
     (262143, G32, [(1.0, (0, 0, 0), (32, 4, 1))]),
     (200001, G32, [(0.7, (1, 1, 1), (2, 2, 2))]),
     (65537, (31, 33, 29), [(1.0, (30, 32, 28), (1, 1, 1))]),
-    (4097, G32, [(1.0, (0, 0, 0), (32, 4, 1))]),        # one over a share, and two and three shares
+    (4097, G32, [(1.0, (0, 0, 0), (32, 4, 1))]),        # one over a small bucket
     (8192, G32, [(1.0, (0, 0, 0), (32, 4, 1))]),
     (8193, G32, [(1.0, (0, 0, 0), (1, 1, 1))]),
     (12288, G20, [(1.0, (0, 0, 0), (128, 32, 1))]),
     (12289, G20, [(1.0, (0, 0, 0), (2, 2, 1))]),
+    (32768, G32, [(1.0, (0, 0, 0), (32, 4, 1))]),       # two shares of 2^14, and shares of 2^12
+    (32768, G20, [(0.6, (127, 127, 63), (1, 1, 1))]),
+    (32769, G32, [(1.0, (0, 0, 0), (32, 4, 1))]),
 ]
 
 
