@@ -22,7 +22,6 @@ struct BatchGroup {
     int tile;
     int32_t first, count;
     int64_t blocks, part_base;
-    int64_t dense_blocks; // of the dense pass, among `blocks`
 };
 
 struct pi_batch {
@@ -31,6 +30,7 @@ struct pi_batch {
     SysDev *d_sys;              // binning table, caller's order
     SysDev *d_sweep;            // sweep table, grouped by organisation
     KernelConst *d_kcs;         // kernel constants, sweep-table order
+    uint32_t *d_ovf;            // per system, sweep-table order: whether a tile overflowed
     int32_t *d_hint;            // coarse cell-to-system index (binning)
     int64_t cap_hint;
     int32_t cap_sys;
@@ -40,7 +40,8 @@ struct pi_batch {
     std::vector<int64_t> cell_base; // host copy, nsys entries
     std::vector<int> tile_of;       // organisation of each system (caller's order)
     std::vector<BatchGroup> groups;
-    int64_t total_blocks;
+    int64_t sweep_blocks;           // workgroups of all sweep launches: their partial records come first,
+    int64_t dense_blocks;           // then those of the dense pass
     // graph cache (or, with `direct`, the layout the tables hold)
     std::vector<unsigned char> sig;
     hipGraph_t graph;
@@ -100,6 +101,7 @@ extern "C" pi_status pi_batch_destroy(pi_batch *b)
     if (b->d_sys) (void)hipFree(b->d_sys);
     if (b->d_sweep) (void)hipFree(b->d_sweep);
     if (b->d_kcs) (void)hipFree(b->d_kcs);
+    if (b->d_ovf) (void)hipFree(b->d_ovf);
     if (b->d_hint) (void)hipFree(b->d_hint);
     for (hipStream_t st : b->side) (void)hipStreamDestroy(st);
     for (hipEvent_t e : b->done) (void)hipEventDestroy(e);
@@ -147,7 +149,7 @@ pi_status launch_all(pi_batch *b, const float *x, const float *y, const float *z
     GridDev g0;
     memset(&g0, 0, sizeof(g0));
     pi_status st = pi_bin_systems(b->ctx, b->cells, x, y, z, w, n_total, cells_total, b->nsys, b->d_sys, b->d_hint,
-                                  g0, stream);
+                                  b->d_ovf, g0, stream);
     if (st != PI_OK) return st;
     // The groups write disjoint outputs and partial records, so on a real
     // stream they run side by side: in up to kLanes chains, the first on
@@ -169,14 +171,15 @@ pi_status launch_all(pi_batch *b, const float *x, const float *y, const float *z
             gs = b->side[lane - 1];
             if (i < lanes) PI_CHECK_HIP(hipStreamWaitEvent(gs, b->binned, 0));
         }
-        st = pi_sweep_batch(b->ctx, b->cells, g.count, b->d_sweep + g.first, b->d_kcs + g.first, g.blocks,
-                            g.dense_blocks, g.part_base, g.tile, o, rho, gx, gy, gz, count, inv, gs);
+        st = pi_sweep_batch(b->ctx, b->cells, g.count, b->d_sweep + g.first, b->d_kcs + g.first,
+                            b->d_ovf + g.first, g.blocks, g.part_base, g.tile, o, rho, gx, gy, gz, count, gs);
         if (st != PI_OK) return st;
         if (fork && lane > 0 && i + lanes >= ng) PI_CHECK_HIP(hipEventRecord(b->done[lane - 1], gs));
     }
     if (fork)
         for (size_t i = 1; i < lanes; ++i) PI_CHECK_HIP(hipStreamWaitEvent(stream, b->done[i - 1], 0));
-    return PI_OK;
+    return pi_sweep_batch_end(b->ctx, b->cells, b->nsys, b->d_sweep, b->d_kcs, b->d_ovf, b->sweep_blocks,
+                              b->dense_blocks, o, rho, gx, gy, gz, count, inv, stream);
 }
 
 } // namespace
@@ -280,6 +283,7 @@ pi_status pi_batch_run_orgs(pi_ctx *ctx, pi_batch *b, int32_t nsys, const pi_sys
     std::vector<KernelConst> kcs((size_t)nsys);
     b->groups.clear();
     int64_t part_base = 0;
+    b->dense_blocks = 0;
     for (int32_t i = 0; i < nsys;) {
         int32_t j = i;
         while (j < nsys && b->tile_of[order[j]] == b->tile_of[order[i]]) {
@@ -291,26 +295,30 @@ pi_status pi_batch_run_orgs(pi_ctx *ctx, pi_batch *b, int32_t nsys, const pi_sys
         g.tile = b->tile_of[order[i]];
         g.first = i;
         g.count = j - i;
-        g.blocks = pi_batch_layout(g.tile, b->h_sweep.data() + i, g.count, &g.dense_blocks);
         g.part_base = part_base;
+        g.blocks = pi_batch_layout(g.tile, b->h_sweep.data() + i, g.count, part_base, &b->dense_blocks);
         part_base += g.blocks;
         b->groups.push_back(g);
         i = j;
     }
-    b->total_blocks = part_base;
+    b->sweep_blocks = part_base;
+    const int64_t total_blocks = b->sweep_blocks + b->dense_blocks;
     b->nsys = nsys;
     if (nsys > b->cap_sys) {
         PI_CHECK_HIP(hipStreamSynchronize(stream));
         if (b->d_sys) (void)hipFree(b->d_sys);
         if (b->d_sweep) (void)hipFree(b->d_sweep);
         if (b->d_kcs) (void)hipFree(b->d_kcs);
+        if (b->d_ovf) (void)hipFree(b->d_ovf);
+        b->d_ovf = nullptr;
         b->d_sys = nullptr;
         b->d_sweep = nullptr;
         b->d_kcs = nullptr;
         b->cap_sys = 0;
         if (hipMalloc((void **)&b->d_sys, sizeof(SysDev) * (size_t)nsys) != hipSuccess ||
             hipMalloc((void **)&b->d_sweep, sizeof(SysDev) * (size_t)nsys) != hipSuccess ||
-            hipMalloc((void **)&b->d_kcs, sizeof(KernelConst) * (size_t)nsys) != hipSuccess)
+            hipMalloc((void **)&b->d_kcs, sizeof(KernelConst) * (size_t)nsys) != hipSuccess ||
+            hipMalloc((void **)&b->d_ovf, sizeof(uint32_t) * (size_t)nsys) != hipSuccess)
             return PI_ENOMEM;
         b->cap_sys = nsys;
     }
@@ -337,23 +345,23 @@ pi_status pi_batch_run_orgs(pi_ctx *ctx, pi_batch *b, int32_t nsys, const pi_sys
         pi_cells_forget(c);
         return st;
     }
-    if (b->total_blocks > c->cap_tflag) {
+    if (total_blocks > c->cap_tflag) {
         // one overflow flag per workgroup of the sweep launches
         PI_CHECK_HIP(hipStreamSynchronize(stream));
         if (c->tflag) (void)hipFree(c->tflag);
         c->tflag = nullptr;
         c->cap_tflag = 0;
-        if (hipMalloc((void **)&c->tflag, (size_t)b->total_blocks) != hipSuccess) {
+        if (hipMalloc((void **)&c->tflag, (size_t)total_blocks) != hipSuccess) {
             pi_cells_forget(c);
             return PI_ENOMEM;
         }
-        c->cap_tflag = b->total_blocks;
+        c->cap_tflag = total_blocks;
     }
-    if (b->total_blocks + 64 > c->cap_partials) {
+    if (total_blocks + 64 > c->cap_partials) {
         PI_CHECK_HIP(hipStreamSynchronize(stream));
         if (c->partials) (void)hipFree(c->partials);
         c->partials = nullptr;
-        const int64_t need = b->total_blocks + 64;
+        const int64_t need = total_blocks + 64;
         if (hipMalloc(&c->partials, (size_t)need * 64) != hipSuccess) {
             c->cap_partials = 0;
             pi_cells_forget(c);

@@ -161,6 +161,7 @@ struct SortArgs {
     const SysDev *sys; // batch mode: system table (nsys entries), else null
     int32_t nsys;
     const int32_t *cell_hint; // batch mode: coarse cell-to-system index
+    uint32_t *sys_ovf;        // batch mode: the systems' overflow words, cleared for the sweep
     // the first pass reads the caller's arrays
     const float *x, *y, *z, *w;
     // later passes read the previous pass's records: (cell id, original
@@ -225,6 +226,8 @@ __global__ __launch_bounds__(kBlock) void k_radix_hist(SortArgs a)
     // (each XCD takes a contiguous run of tiles: neighbouring tiles share
     // its L2, which merges their partial-line writes of a histogram column)
     if (FIRST && !BATCH && blockIdx.x == 0 && threadIdx.x == 0) *a.max_per_cell = 0; // (the bucket sort raises it)
+    if (FIRST && BATCH && blockIdx.x == 0)
+        for (int i = threadIdx.x; i < a.nsys; i += kBlock) a.sys_ovf[i] = 0;
     const int32_t tile = (int32_t)xcd_remap(blockIdx.x, gridDim.x);
     const int64_t base = (int64_t)tile * kSortTile;
     const int64_t last = (int64_t)a.n - 1;
@@ -1044,7 +1047,7 @@ void radix_pass(pi_ctx *ctx, const SortArgs &a, bool first, bool last, bool batc
 // systems with cells_total cells in all.
 pi_status pi_bin_systems(pi_ctx *ctx, pi_cells *cells, const float *x, const float *y, const float *z,
                          const float *w, int64_t n, int64_t nc, int32_t nsys, const SysDev *d_sys,
-                         const int32_t *d_cell_hint, const GridDev &g0, hipStream_t stream)
+                         const int32_t *d_cell_hint, uint32_t *d_ovf, const GridDev &g0, hipStream_t stream)
 {
     const bool batch = nsys > 0;
     if (n > 0) {
@@ -1072,6 +1075,7 @@ pi_status pi_bin_systems(pi_ctx *ctx, pi_cells *cells, const float *x, const flo
         a.g = g0;
         a.sys = d_sys;
         a.cell_hint = d_cell_hint;
+        a.sys_ovf = d_ovf;
         a.nsys = nsys;
         a.x = x;
         a.y = y;
@@ -1166,7 +1170,7 @@ extern "C" pi_status pi_bin(pi_ctx *ctx, pi_cells *cells, const float *x, const 
     cells->last_stream = stream;
 
     const GridDev g = grid_dev(*grid);
-    st = pi_bin_systems(ctx, cells, x, y, z, w, n, nc, 0, nullptr, nullptr, g, stream);
+    st = pi_bin_systems(ctx, cells, x, y, z, w, n, nc, 0, nullptr, nullptr, nullptr, g, stream);
     if (st != PI_OK) {
         pi_cells_forget(cells);
         return st;

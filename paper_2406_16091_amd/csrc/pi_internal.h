@@ -255,9 +255,11 @@ struct SysDev {
     int64_t first;
     int32_t n;
     int32_t cell_base;
-    int32_t block_base; // first workgroup of this system in a sweep launch
-    int32_t dense_base; // and in the dense pass of a tile sweep
-    int32_t ntx, nty;   // tiles per axis in that launch
+    int32_t block_base; // first workgroup of this system in its organisation's sweep launch
+    int32_t dense_base; // and in the batch's dense pass
+    int32_t rec_base;   // first of its workgroups' partial records and tile flags
+    int32_t ntx, nty;   // tiles per axis in the sweep launch (0: no tiles)
+    int32_t tx, ty, tz; // and their shape
     int32_t orig;       // index of the system in the caller's list
     GridDev g;
 };
@@ -271,7 +273,7 @@ bool pi_tile_shape(int tile_id, int *tx, int *ty, int *tz);
 int pi_pick_tile(const pi_interact_opts &o, double ppc);
 void pi_tile_opts(int tile_id, pi_interact_opts *out);
 int pi_auto_tile(pi_ctx *ctx, int precision, int64_t n, double ppc, bool alone);
-int64_t pi_batch_layout(int tile_id, SysDev *h_sys, int32_t nsys, int64_t *dense_blocks);
+int64_t pi_batch_layout(int tile_id, SysDev *h_sys, int32_t nsys, int64_t rec_base, int64_t *dense_blocks);
 int pi_batch_org(int tile_id);
 bool pi_org_valid(int id);
 constexpr int kOrgStream = 9; // organisation id of the stream sweep
@@ -289,9 +291,15 @@ pi_status pi_batch_run_orgs(pi_ctx *ctx, pi_batch *b, int32_t nsys, const pi_sys
                             const pi_interact_opts *opts, float *rho, float *gx, float *gy, float *gz,
                             int32_t *count, pi_invariants *inv, pi_stream stream);
 pi_status pi_sweep_batch(pi_ctx *ctx, pi_cells *cells, int32_t nsys, const SysDev *d_sys, const KernelConst *d_kcs,
-                         int64_t total_blocks, int64_t dense_blocks, int64_t part_base, int tile_id,
+                         uint32_t *d_ovf, int64_t total_blocks, int64_t part_base, int tile_id,
                          const pi_interact_opts &o, float *rho, float *gx, float *gy, float *gz, int32_t *count,
-                         pi_invariants *inv, hipStream_t stream);
+                         hipStream_t stream);
+// The rest of a batch's sweep, once all its organisations' launches are done: the
+// dense pass of every tiled system and the invariants.
+pi_status pi_sweep_batch_end(pi_ctx *ctx, pi_cells *cells, int32_t nsys, const SysDev *d_sys, const KernelConst *d_kcs,
+                             uint32_t *d_ovf, int64_t sweep_blocks, int64_t dense_blocks, const pi_interact_opts &o,
+                             float *rho, float *gx, float *gy, float *gz, int32_t *count, pi_invariants *inv,
+                             hipStream_t stream);
 
 // The sweep of pi_interact (sweep.hip) on a binned system whose invariant
 // partial records live in `partials` (cap_partials records of 64 bytes).
@@ -318,6 +326,8 @@ pi_status pi_split_records(pi_ctx *ctx, pi_cells *cells);
 // between entries c >> shift and (c >> shift) + 1.
 constexpr int kCellHintShift = 10;
 
+// d_ovf (batch): nsys words that the binning clears, for the sweep's overflows.
 pi_status pi_bin_systems(pi_ctx *ctx, pi_cells *cells, const float *x, const float *y, const float *z,
                          const float *w, int64_t n_total, int64_t cells_total, int32_t nsys,
-                         const SysDev *d_sys, const int32_t *d_cell_hint, const GridDev &g0, hipStream_t stream);
+                         const SysDev *d_sys, const int32_t *d_cell_hint, uint32_t *d_ovf, const GridDev &g0,
+                         hipStream_t stream);

@@ -33,10 +33,11 @@ struct SweepArgs {
     float *rho, *gx, *gy, *gz;
     int32_t *count;
     InvPartial *partials;
-    // single-system tiles: per tile, 1 if its halo overflowed the LDS area
+    // tiles: per tile, 1 if its halo overflowed the LDS area
     // and its targets are left to the dense pass; a word that a launch whose
     // tiles overflowed sets to its epoch (a number the host gives each tile
-    // launch on a cell object, from the counter at host_epoch)
+    // launch on a cell object, from the counter at host_epoch; in a batch a word
+    // per system, set to 1)
     uint8_t *tflag;
     uint32_t *ovf;
     uint32_t epoch;
@@ -49,27 +50,41 @@ struct SweepArgs {
     const SysDev *sys;
     const KernelConst *kcs;
     int32_t nsys;
-    int32_t dense_blocks; // workgroups of the dense pass of a tile sweep
 };
 
-// Batch mode: the system owning logical workgroup lb (DENSE: of the dense pass);
-// narrows the sweep arguments to that system (its grid, cell offsets and kernel
-// constants).
-template <bool DENSE = false>
-__device__ __forceinline__ int enter_system(SweepArgs &a, uint32_t lb)
+// Batch mode: narrows the sweep arguments to system s (its grid, cell offsets and
+// kernel constants).
+__device__ __forceinline__ void narrow_to_system(SweepArgs &a, int s)
 {
-    int lo = 0, hi = a.nsys; // sys[lo].block_base <= lb < sys[hi].block_base
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if ((uint32_t)(DENSE ? a.sys[mid].dense_base : a.sys[mid].block_base) <= lb) lo = mid; else hi = mid;
-    }
-    const SysDev &sd = a.sys[lo];
+    const SysDev &sd = a.sys[s];
     a.nx = sd.g.nx;
     a.ny = sd.g.ny;
     a.nz = sd.g.nz;
     a.nc = (int64_t)sd.g.nx * sd.g.ny * sd.g.nz;
     a.off += sd.cell_base;
-    a.k = a.kcs[lo];
+    a.k = a.kcs[s];
+}
+
+// The system owning logical workgroup lb of the sweep; narrows the arguments to it.
+__device__ __forceinline__ int enter_system(SweepArgs &a, uint32_t lb)
+{
+    int lo = 0, hi = a.nsys; // sys[lo].block_base <= lb < sys[hi].block_base
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if ((uint32_t)a.sys[mid].block_base <= lb) lo = mid; else hi = mid;
+    }
+    narrow_to_system(a, lo);
+    return lo;
+}
+
+// The system owning share i of the batch's dense pass.
+__device__ __forceinline__ int dense_system(const SweepArgs &a, uint32_t i)
+{
+    int lo = 0, hi = a.nsys; // sys[lo].dense_base <= i < sys[hi].dense_base
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if ((uint32_t)a.sys[mid].dense_base <= i) lo = mid; else hi = mid;
+    }
     return lo;
 }
 
@@ -624,13 +639,13 @@ __global__ __launch_bounds__(kBlock) void k_sweep_pencil(SweepArgs a, int32_t nt
 
     const uint32_t lb = xcd_remap(blockIdx.x, gridDim.x);
     uint32_t tl = lb; // tile index within its system
+    int own = 0;      // the system
     if (BATCH) {
-        const SysDev &sd = a.sys[enter_system(a, lb)];
+        own = enter_system(a, lb);
+        const SysDev &sd = a.sys[own];
         tl = lb - (uint32_t)sd.block_base;
         ntx = sd.ntx;
         nty = sd.nty;
-        // the system's workgroups past its tiles belong to its dense pass
-        if (tl >= (uint32_t)(ntx * nty * ((a.nz + TZ - 1) / TZ))) return;
     }
     const int32_t bx = (int32_t)(tl % (uint32_t)ntx);
     const int32_t by = (int32_t)((tl / (uint32_t)ntx) % (uint32_t)nty);
@@ -694,7 +709,7 @@ __global__ __launch_bounds__(kBlock) void k_sweep_pencil(SweepArgs a, int32_t nt
         // k_sweep_dense_batch for a batch) takes this tile's targets, one
         // thread each across the system, so a dense region is not left to
         // one workgroup
-        if (!BATCH && tid == 0) *a.ovf = a.epoch;
+        if (tid == 0) a.ovf[own] = a.epoch;
         if (INV) reduce_invariants(a, lb, 0, 0.0, 0.0, 0.0, 0.0, 0.0);
         return;
     }
@@ -922,13 +937,13 @@ __global__ __launch_bounds__(kBlock, CAP <= 768 ? 6 : 4) void k_sweep_tile(Sweep
 
     const uint32_t lb = xcd_remap(blockIdx.x, gridDim.x);
     uint32_t tl = lb; // tile index within its system
+    int own = 0;      // the system
     if (BATCH) {
-        const SysDev &sd = a.sys[enter_system(a, lb)];
+        own = enter_system(a, lb);
+        const SysDev &sd = a.sys[own];
         tl = lb - (uint32_t)sd.block_base;
         ntx = sd.ntx;
         nty = sd.nty;
-        // the system's workgroups past its tiles belong to its dense pass
-        if (tl >= (uint32_t)(ntx * nty * ((a.nz + TZ - 1) / TZ))) return;
     }
     const int32_t bx = (int32_t)(tl % (uint32_t)ntx);
     const int32_t by = (int32_t)((tl / (uint32_t)ntx) % (uint32_t)nty);
@@ -994,7 +1009,7 @@ __global__ __launch_bounds__(kBlock, CAP <= 768 ? 6 : 4) void k_sweep_tile(Sweep
     const bool overflow = total > CAP || ntarget > 2 * kBlock;
     if (tid == 0) a.tflag[lb] = overflow ? 1 : 0;
     if (overflow) {
-        if (!BATCH && tid == 0) *a.ovf = a.epoch;
+        if (tid == 0) a.ovf[own] = a.epoch;
         if (INV) reduce_invariants(a, lb, 0, 0.0, 0.0, 0.0, 0.0, 0.0);
         return;
     }
@@ -1182,13 +1197,13 @@ __global__ __launch_bounds__(kBlock) void k_sweep_pencilreg(SweepArgs a, int32_t
 
     const uint32_t lb = xcd_remap(blockIdx.x, gridDim.x);
     uint32_t tl = lb;
+    int own = 0;
     if (BATCH) {
-        const SysDev &sd = a.sys[enter_system(a, lb)];
+        own = enter_system(a, lb);
+        const SysDev &sd = a.sys[own];
         tl = lb - (uint32_t)sd.block_base;
         ntx = sd.ntx;
         nty = sd.nty;
-        // the system's workgroups past its tiles belong to its dense pass
-        if (tl >= (uint32_t)(ntx * nty * ((a.nz + TZ - 1) / TZ))) return;
     }
     const int32_t bx = (int32_t)(tl % (uint32_t)ntx);
     const int32_t by = (int32_t)((tl / (uint32_t)ntx) % (uint32_t)nty);
@@ -1239,7 +1254,7 @@ __global__ __launch_bounds__(kBlock) void k_sweep_pencilreg(SweepArgs a, int32_t
     double inx = 0, iny = 0, inz = 0, isc = 0, irs = 0;
     if (tid == 0) a.tflag[lb] = overflow ? 1 : 0;
     if (overflow) {
-        if (!BATCH && tid == 0) *a.ovf = a.epoch;
+        if (tid == 0) a.ovf[own] = a.epoch;
         if (INV) reduce_invariants(a, lb, 0, 0.0, 0.0, 0.0, 0.0, 0.0);
         return;
     }
@@ -1635,33 +1650,45 @@ __global__ __launch_bounds__(kBlock, 4) void k_sweep_dense(SweepArgs a, int32_t 
     if (INV) reduce_invariants(a, rec0 + blockIdx.x, sums.cnt, sums.nx, sums.ny, sums.nz, sums.sc, sums.rs);
 }
 
-// The dense pass of a batch tile sweep, one launch of all systems' dense workgroups
-// (the tiles' flags and every partial record are laid out as each system's tiles
-// followed by its dense workgroups).  A dense workgroup first checks whether any
-// tile of its system overflowed (the flags the tile launch just wrote) and, if so,
-// strides over the system's particles and takes the targets of flagged tiles.
+// The dense pass of a batch, one launch for all its tiled systems (a pass behind each
+// organisation's sweep is a chain of latencies where few targets are left: 16 systems
+// of up to 2e4 particles in blobs, 8 to 14 per cell, on the null stream 3.1 ms with
+// four passes, 1.8 with one).  A persistent grid takes the systems' shares (a share
+// strides over its system's particles); it looks 256 of them up at once, since most
+// are of systems in which no tile overflowed and then have nothing to do nor a
+// record to write (a workgroup for each of the 41,000 shares of 512 systems: 182 us,
+// 28 this way).
 template <int PREC, bool INV>
-__global__ __launch_bounds__(kBlock, 4) void k_sweep_dense_batch(SweepArgs a, int32_t tx, int32_t ty, int32_t tz)
+__global__ __launch_bounds__(kBlock, 4) void k_sweep_dense_batch(SweepArgs b, int32_t shares)
 {
     __shared__ StreamLds<kStreamQ, kStreamRing> lds;
-    const int s = enter_system<true>(a, blockIdx.x);
-    const SysDev &sd = a.sys[s];
-    const int32_t ntx = sd.ntx, nty = sd.nty, ntz = (a.nz + tz - 1) / tz;
-    const int32_t ntiles = ntx * nty * ntz;
-    const int32_t d = (int32_t)blockIdx.x - sd.dense_base;
-    const int32_t nd = (s + 1 < a.nsys ? a.sys[s + 1].dense_base : a.dense_blocks) - sd.dense_base;
-    const uint32_t lb = (uint32_t)(sd.block_base + ntiles + d);
-    const uint8_t *flags = a.tflag + sd.block_base;
-    int any = 0;
-    for (int32_t t = (int32_t)threadIdx.x; t < ntiles && !any; t += kBlock) any = flags[t];
-    any = __syncthreads_or(any);
-    DenseSums sums;
-    if (any) {
-        const int32_t kend = (int32_t)sd.first + sd.n;
-        for (int32_t k0 = (int32_t)sd.first + d * kBlock; k0 < kend; k0 += nd * kBlock)
-            dense_targets<PREC, INV>(a, lds, k0 + (int32_t)threadIdx.x, kend, flags, tx, ty, tz, ntx, nty, sums);
+    __shared__ int32_t todo[kBlock];
+    __shared__ int32_t count;
+    for (int64_t i0 = blockIdx.x; i0 < shares; i0 += (int64_t)gridDim.x * kBlock) {
+        const int64_t mine = i0 + (int64_t)threadIdx.x * gridDim.x;
+        if (threadIdx.x == 0) count = 0;
+        __syncthreads();
+        if (mine < shares && b.ovf[dense_system(b, (uint32_t)mine)]) todo[atomicAdd(&count, 1)] = (int32_t)mine;
+        __syncthreads();
+        const int32_t n = count;
+        __syncthreads(); // (count is written again if there is nothing to do)
+        for (int32_t q = 0; q < n; ++q) {
+            const int32_t share = todo[q];
+            SweepArgs a = b;
+            const int s = dense_system(b, (uint32_t)share);
+            narrow_to_system(a, s);
+            const SysDev &sd = a.sys[s];
+            const int32_t nd = (s + 1 < a.nsys ? a.sys[s + 1].dense_base : shares) - sd.dense_base;
+            const int32_t kend = (int32_t)sd.first + sd.n;
+            DenseSums sums;
+            for (int32_t k0 = (int32_t)sd.first + (share - sd.dense_base) * kBlock; k0 < kend; k0 += nd * kBlock)
+                dense_targets<PREC, INV>(a, lds, k0 + (int32_t)threadIdx.x, kend, a.tflag + sd.rec_base, sd.tx, sd.ty,
+                                         sd.tz, sd.ntx, sd.nty, sums);
+            if (INV)
+                reduce_invariants(a, (uint32_t)share, sums.cnt, sums.nx, sums.ny, sums.nz, sums.sc, sums.rs);
+            __syncthreads(); // the reduction's and the list's LDS are written again
+        }
     }
-    if (INV) reduce_invariants(a, lb, sums.cnt, sums.nx, sums.ny, sums.nz, sums.sc, sums.rs);
 }
 
 // FP64 reduction of the per-workgroup partials in two fixed-order stages
@@ -1742,22 +1769,27 @@ __global__ __launch_bounds__(kBlock) void k_inv_stage2(const InvPartial *__restr
     }
 }
 
-// Batch mode: invariants of table entry s from its workgroups' partials
-// [block_base[s], block_base[s+1]) (one workgroup per system, fixed order),
-// written to the system's place in the caller's list.
+// Batch mode: invariants of table entry s from the partial records of its sweep
+// workgroups and, from `dense` on, its shares of the dense pass (one workgroup per system,
+// fixed order), written to the system's place in the caller's list.
 __global__ __launch_bounds__(kBlock) void k_inv_systems(const InvPartial *__restrict__ parts,
-                                                        const SysDev *__restrict__ sys, int32_t nsys,
-                                                        int32_t total_blocks, pi_invariants *__restrict__ out)
+                                                        const InvPartial *__restrict__ dense,
+                                                        const SysDev *__restrict__ sys,
+                                                        const uint32_t *__restrict__ ovf, int32_t nsys,
+                                                        int32_t sweep_blocks, int32_t dense_blocks,
+                                                        pi_invariants *__restrict__ out)
 {
     __shared__ double red[kBlock][5];
     __shared__ long long redc[kBlock];
     const int s = blockIdx.x;
-    const int32_t b0 = sys[s].block_base;
-    const int32_t b1 = s + 1 < nsys ? sys[s + 1].block_base : total_blocks;
+    const bool last = s + 1 == nsys;
+    const int32_t b0 = sys[s].rec_base, d0 = sys[s].dense_base;
+    const int32_t n = (last ? sweep_blocks : sys[s + 1].rec_base) - b0;
+    const int32_t nd = ovf[s] ? (last ? dense_blocks : sys[s + 1].dense_base) - d0 : 0; // (else not written)
     long long c = 0;
     double v[5] = {0, 0, 0, 0, 0};
-    for (int32_t i = b0 + (int32_t)threadIdx.x; i < b1; i += kBlock) {
-        const InvPartial p = parts[i];
+    for (int32_t i = (int32_t)threadIdx.x; i < n + nd; i += kBlock) {
+        const InvPartial p = i < n ? parts[b0 + i] : dense[d0 + i - n];
         c += p.pairs;
         v[0] += p.net[0];
         v[1] += p.net[1];
@@ -1878,9 +1910,14 @@ unsigned dense_blocks(int64_t n)
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>(b, 1024));
 }
 
-// Dense workgroups of one system of a batch tile sweep: one per 512
-// particles, at most 1024 (a workgroup of a system without an overflowing
-// tile only reads the system's tile flags).
+// Most workgroups of a batch's dense pass: several times what the GPU holds at once, so
+// that shares of unequal work even out (64 systems of up to 2e5 particles in blobs, 8
+// to 14 per cell: 11.7 ms with 1024, 9.1 with this), and few enough to be soon through
+// where there is nothing to do.
+constexpr int64_t kBatchDenseGrid = 8192;
+
+// Shares of one system of a batch tile sweep in the dense pass: one per 512
+// particles, at most 1024.
 int64_t batch_dense_blocks(int64_t n)
 {
     return std::max<int64_t>(1, std::min<int64_t>((n + 511) / 512, 1024));
@@ -1901,7 +1938,6 @@ void launch_tile(pi_ctx *ctx, const char *name, const SweepArgs &a, hipStream_t 
         nblk = (unsigned)((int64_t)ntx * nty * ntz);
     }
     if (BATCH) {
-        // (nblk counts every system's tiles and dense workgroups)
         if constexpr (REG)
             PI_LAUNCH(ctx, name, (k_sweep_pencilreg<TX, TY, TZ, CAP, PREC, INV, BATCH>), dim3(nblk), dim3(kBlock), 0,
                       s, a, ntx, nty);
@@ -1911,9 +1947,7 @@ void launch_tile(pi_ctx *ctx, const char *name, const SweepArgs &a, hipStream_t 
         else
             PI_LAUNCH(ctx, name, (k_sweep_tile<TX, TY, TZ, CAP, PREC, INV, BATCH>), dim3(nblk), dim3(kBlock), 0, s, a,
                       ntx, nty);
-        PI_LAUNCH(ctx, "k_sweep_dense_batch", (k_sweep_dense_batch<PREC, INV>), dim3((unsigned)a.dense_blocks),
-                  dim3(kBlock), 0, s, a, TX, TY, TZ);
-        return;
+        return; // (the dense pass comes after all organisations' launches)
     }
     SweepArgs b = a;
     b.epoch = ++*a.host_epoch;
@@ -2158,45 +2192,45 @@ int pi_batch_org(int tile)
     return tile;
 }
 
-// Batch sweep: h_sys gets each system's block_base / ntx / nty for tile_id
-// (the caller uploads the table to d_sys before launching).  Returns the
-// total workgroup count, and the dense pass's in *dense_blocks.
-int64_t pi_batch_layout(int tile_id, SysDev *h_sys, int32_t nsys, int64_t *dense_blocks)
+// Batch sweep: h_sys gets each system's workgroups and tiles for tile_id (the caller
+// uploads the table to d_sys before launching); their records begin at rec_base.
+// Returns the workgroups of the sweep launch and adds those of the dense pass to
+// *dense_blocks.
+int64_t pi_batch_layout(int tile_id, SysDev *h_sys, int32_t nsys, int64_t rec_base, int64_t *dense_blocks)
 {
     int tx = 0, ty = 0, tz = 0;
     const bool tiled = tile_id > 0 && pi_tile_shape(tile_id, &tx, &ty, &tz);
     const bool cell = tiled && tile_cfg(tile_id).sweep == PI_SWEEP_CELL;
     if (cell) ty = tz = 1; // runs of tx cells
-    int64_t base = 0, dense = 0;
+    int64_t base = 0;
     for (int32_t s = 0; s < nsys; ++s) {
         SysDev &d = h_sys[s];
         d.block_base = (int32_t)base;
-        d.dense_base = (int32_t)dense;
+        d.rec_base = (int32_t)(rec_base + base);
+        d.dense_base = (int32_t)*dense_blocks;
+        d.tx = tx;
+        d.ty = ty;
+        d.tz = tz;
         if (tiled) {
             d.ntx = (d.g.nx + tx - 1) / tx;
             d.nty = (d.g.ny + ty - 1) / ty;
             const int32_t ntz = (d.g.nz + tz - 1) / tz;
             base += (int64_t)d.ntx * d.nty * ntz;
             // the dense workgroups of an LDS tiling (none for the cell-SM)
-            if (!cell) dense += batch_dense_blocks(d.n);
+            if (!cell) *dense_blocks += batch_dense_blocks(d.n);
         } else {
             d.ntx = d.nty = 0;
             base += (d.n + kBlock - 1) / kBlock;
         }
-        base += dense - d.dense_base;
     }
-    *dense_blocks = dense;
     return base;
 }
 
-// One sweep launch over the systems of table d_sys[0 .. nsys) (all with tile
-// tile_id); their workgroup partials go to records part_base + block.
-pi_status pi_sweep_batch(pi_ctx *ctx, pi_cells *cells, int32_t nsys, const SysDev *d_sys, const KernelConst *d_kcs,
-                         int64_t total_blocks, int64_t dense_blocks, int64_t part_base, int tile_id,
-                         const pi_interact_opts &o, float *rho, float *gx, float *gy, float *gz, int32_t *count,
-                         pi_invariants *inv, hipStream_t stream)
+namespace {
+
+SweepArgs batch_args(const pi_cells *cells, int32_t nsys, const SysDev *d_sys, const KernelConst *d_kcs,
+                     uint32_t *d_ovf, const pi_interact_opts &o, float *rho, float *gx, float *gy, float *gz, int32_t *count)
 {
-    if (part_base + total_blocks > cells->cap_partials) return PI_ENOMEM;
     SweepArgs a;
     memset(&a, 0, sizeof(a));
     a.off = cells->offsets;
@@ -2210,17 +2244,56 @@ pi_status pi_sweep_batch(pi_ctx *ctx, pi_cells *cells, int32_t nsys, const SysDe
     a.gy = gy;
     a.gz = gz;
     a.count = count;
-    a.partials = (InvPartial *)cells->partials + part_base;
-    a.tflag = cells->tflag + part_base; // (one flag per workgroup of the group)
+    a.tflag = cells->tflag;
+    a.ovf = d_ovf;
+    a.epoch = 1;
     a.sys = d_sys;
     a.kcs = d_kcs;
     a.nsys = nsys;
-    a.dense_blocks = (int32_t)dense_blocks;
+    return a;
+}
+
+} // namespace
+
+// One sweep launch over the systems of table d_sys[0 .. nsys) (all with tile
+// tile_id); their workgroup partials go to records part_base + block.
+pi_status pi_sweep_batch(pi_ctx *ctx, pi_cells *cells, int32_t nsys, const SysDev *d_sys, const KernelConst *d_kcs,
+                         uint32_t *d_ovf, int64_t total_blocks, int64_t part_base, int tile_id,
+                         const pi_interact_opts &o, float *rho, float *gx, float *gy, float *gz, int32_t *count,
+                         hipStream_t stream)
+{
+    if (part_base + total_blocks > cells->cap_partials) return PI_ENOMEM;
+    SweepArgs a = batch_args(cells, nsys, d_sys, d_kcs, d_ovf, o, rho, gx, gy, gz, count);
+    a.partials = (InvPartial *)cells->partials + part_base;
+    a.tflag += part_base; // (one flag per workgroup of the group)
     unsigned nblk = (unsigned)total_blocks;
     if (nblk > 0) launch_sweep_prec<true>(ctx, o.precision, true, tile_id, a, stream, nblk);
+    PI_CHECK_HIP(hipGetLastError());
+    return PI_OK;
+}
+
+pi_status pi_sweep_batch_end(pi_ctx *ctx, pi_cells *cells, int32_t nsys, const SysDev *d_sys, const KernelConst *d_kcs,
+                             uint32_t *d_ovf, int64_t sweep_blocks, int64_t dense_blocks, const pi_interact_opts &o,
+                             float *rho, float *gx, float *gy, float *gz, int32_t *count, pi_invariants *inv,
+                             hipStream_t stream)
+{
+    if (sweep_blocks + dense_blocks > cells->cap_partials) return PI_ENOMEM;
+    const InvPartial *parts = (const InvPartial *)cells->partials;
+    if (dense_blocks > 0) {
+        SweepArgs a = batch_args(cells, nsys, d_sys, d_kcs, d_ovf, o, rho, gx, gy, gz, count);
+        a.partials = (InvPartial *)cells->partials + sweep_blocks;
+        const dim3 grid((unsigned)std::min<int64_t>(dense_blocks, kBatchDenseGrid)), block(kBlock);
+        const int32_t shares = (int32_t)dense_blocks;
+        if (o.precision == PI_PREC_PLAIN)
+            PI_LAUNCH(ctx, "k_sweep_dense_batch", (k_sweep_dense_batch<PI_PREC_PLAIN, true>), grid, block, 0, stream, a,
+                      shares);
+        else
+            PI_LAUNCH(ctx, "k_sweep_dense_batch", (k_sweep_dense_batch<PI_PREC_COMPENSATED, true>), grid, block, 0,
+                      stream, a, shares);
+    }
     if (inv)
-        PI_LAUNCH(ctx, "k_inv_systems", k_inv_systems, dim3(nsys), dim3(kBlock), 0, stream,
-                  (const InvPartial *)a.partials, d_sys, nsys, (int32_t)total_blocks, inv);
+        PI_LAUNCH(ctx, "k_inv_systems", k_inv_systems, dim3(nsys), dim3(kBlock), 0, stream, parts,
+                  parts + sweep_blocks, d_sys, (const uint32_t *)d_ovf, nsys, (int32_t)sweep_blocks, (int32_t)dense_blocks, inv);
     PI_CHECK_HIP(hipGetLastError());
     return PI_OK;
 }
