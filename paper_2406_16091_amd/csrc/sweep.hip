@@ -2416,9 +2416,15 @@ pi_status tuned_tile(pi_ctx *ctx, const SweepArgs &a, int prec, int64_t n, doubl
 // others (a batch, the server) take the choice only from 2^18 particles: the
 // trials run a system alone, a smaller one leaves part of the GPU idle, and they
 // then favour many small workgroups where a batch wants the least work (512
-// systems after trials of each: 3.8 ms by the choices, 3.3 by this rule).
+// systems after trials of each: 3.8 ms by the choices, 3.3 by this rule).  Below
+// 2^15 particles they take the stream from 6 per cell: the tiles' gain is small there,
+// every tile shape among the systems is a launch of its own, and a tile around a
+// dense core is a long chain in one workgroup (16 systems of up to 2e4 particles, 8 to
+// 14 per cell, tiles and stream: uniform 130 and 131 us, 239 and 204 on the null stream;
+// in 8 blobs 1157 and 624, 1795 and 695; no LDS 900 and 948).
 int pi_auto_tile(pi_ctx *ctx, int precision, int64_t n, double ppc, bool alone)
 {
+    if (!alone && n < ((int64_t)1 << 15) && ppc >= 6.0) return kOrgStream;
     pi_tuner *t = ctx->tuner;
     if (t && t->mode == PI_TUNE_TIMED && (alone || n >= ((int64_t)1 << 18))) {
         std::lock_guard<std::mutex> g(t->mu);

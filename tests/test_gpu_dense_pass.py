@@ -59,34 +59,57 @@ def test_dense_tiles_equal_the_no_lds_walk(precision, tile):
     db.close()
 
 
-def test_clustered_systems_are_no_slower_than_the_no_lds_walk():
-    import torch
-    from paper_2406_16091_amd import device, pi
-
-    rng = np.random.default_rng(3)
-    side, n = 51, 1 << 20
-    centre = rng.random((64, 3)) * side
-    p = centre[rng.integers(0, 64, n)] + 0.05 * side * rng.standard_normal((n, 3))
+def _blobs(n, side, count, seed):
+    """Nine in ten particles in `count` blobs of a twentieth of the side, the rest uniform."""
+    rng = np.random.default_rng(seed)
+    centre = rng.random((count, 3)) * side
+    p = centre[rng.integers(0, count, n)] + 0.05 * side * rng.standard_normal((n, 3))
     p = np.where(rng.random((n, 1)) < 0.1, rng.random((n, 3)) * side, p)
     p = np.floor(np.clip(p, 0, side - 2.0 ** -10) * 1024) / 1024
-    s = synth.System("blobs", *(np.ascontiguousarray(p[:, a], np.float32) for a in range(3)), synth._weights(rng, n),
-                     (0.0, 0.0, 0.0), (side,) * 3, 1.0, 1.0)
+    return synth.System("blobs", *(np.ascontiguousarray(p[:, a], np.float32) for a in range(3)), synth._weights(rng, n),
+                        (0.0, 0.0, 0.0), (side,) * 3, 1.0, 1.0)
+
+
+def _best(run):
+    import torch
+    t = []
+    for _ in range(8):
+        t0 = time.perf_counter()
+        run()
+        torch.cuda.synchronize()
+        t.append(time.perf_counter() - t0)
+    return min(t)
+
+
+def test_batches_of_clustered_systems_are_no_slower_than_the_no_lds_walk():
+    """On the null stream, which runs a batch's launches one after another."""
+    from paper_2406_16091_amd import device
+
+    rng = np.random.default_rng(5)
+    sizes = [int(1000 * 20 ** rng.random()) for _ in range(16)]
+    systems = [_blobs(n, max(3, round((n / rng.uniform(8, 14)) ** (1 / 3))), 8, 40 + i) for i, n in enumerate(sizes)]
+    db = device.DeviceBatch(systems)
+    time_of, out = {}, {}
+    for sweep in ("auto", "nolds"):
+        time_of[sweep] = _best(lambda: db.run(sweep=sweep, stream=0))
+        db.sync()
+        out[sweep] = db.results()
+    for a, b in zip(out["auto"], out["nolds"]):
+        for k in OUT:
+            assert np.array_equal(a[k], b[k]), k
+    assert time_of["auto"] < 1.15 * time_of["nolds"], time_of
+    db.close()
+
+
+def test_clustered_systems_are_no_slower_than_the_no_lds_walk():
+    from paper_2406_16091_amd import device, pi
+
     ctx = device.Context(0)  # a context of its own, in static mode
     pi.pi_tuner_mode(ctx.handle, pi.PI_TUNE_STATIC)
-    ds = device.DeviceSystem(s, ctx=ctx)
+    ds = device.DeviceSystem(_blobs(1 << 20, 51, 64, 3), ctx=ctx)
     ds.bin()
     ds.sync()
-
-    def best(sweep):
-        t = []
-        for _ in range(8):
-            t0 = time.perf_counter()
-            ds.interact(sweep=sweep)
-            torch.cuda.synchronize()
-            t.append(time.perf_counter() - t0)
-        return min(t)
-
-    auto, walk = best("auto"), best("nolds")
+    auto, walk = (_best(lambda: ds.interact(sweep=sweep)) for sweep in ("auto", "nolds"))
     assert auto < 1.15 * walk, (auto, walk)
     ds.close()
     pi.pi_ctx_destroy(ctx.handle)
