@@ -1,0 +1,85 @@
+"""Batch objects that come and go: a destroyed one leaves its side streams to the
+context's next one.  More at once than are kept, in one thread and another and on
+streams of their own, each gives what one alone gives."""
+import threading
+
+import numpy as np
+import pytest
+
+from paper_2406_16091_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+OUT = ("rho", "gx", "gy", "gz", "count")
+
+
+def _systems():
+    """Occupancies of five organisations, so five sweep groups in four chains."""
+    rng = np.random.default_rng(8)
+    return [synth.box_system(int(per * side ** 3), side, seed=60 + i, lattice_log2=18)
+            for i, (per, side) in enumerate(zip((0.9, 1.8, 3.0, 4.0, 5.0, 12.0), rng.integers(9, 14, 6)))]
+
+
+def _check(db, ref):
+    for got, want in zip(db.results(), ref):
+        for k in OUT:
+            assert np.array_equal(got[k], want[k]), k
+
+
+def test_batch_objects_come_and_go():
+    import torch
+    from paper_2406_16091_amd import device
+
+    systems = _systems()
+    db = device.DeviceBatch(systems)
+    db.run(sweep="nolds", stream=0)
+    db.sync()
+    ref = db.results()
+    db.close()
+    for _ in range(2):
+        live = []
+        for _ in range(20):  # (16 sets are kept)
+            s = torch.cuda.Stream()
+            db = device.DeviceBatch(systems)
+            s.wait_stream(torch.cuda.current_stream())
+            db.run(stream=s)
+            live.append((db, s))
+        for db, s in live:
+            s.synchronize()
+            _check(db, ref)
+            db.close()
+
+
+def test_batch_objects_of_one_thread_after_another():
+    """Made and run in one thread, destroyed in the next."""
+    import torch
+    from paper_2406_16091_amd import device
+
+    systems = _systems()
+    db = device.DeviceBatch(systems)
+    db.run(sweep="nolds", stream=0)
+    db.sync()
+    ref = db.results()
+    failed, last = [], [db]
+
+    def work():
+        try:
+            torch.cuda.set_device(0)
+            last.pop().close()
+            s = torch.cuda.Stream()
+            db = device.DeviceBatch(systems)
+            torch.cuda.synchronize()
+            for _ in range(3):
+                db.run(stream=s)
+            db.sync(s)
+            _check(db, ref)
+            last.append(db)
+        except Exception as e:  # noqa: BLE001
+            failed.append(e)
+
+    for _ in range(6):
+        t = threading.Thread(target=work)
+        t.start()
+        t.join()
+    assert not failed, failed
+    last.pop().close()
