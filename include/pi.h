@@ -430,7 +430,7 @@ pi_status pi_batch_destroy(pi_batch *batch);
  * if not NULL, receives nsys records (device memory).  Same precision and
  * organisation options as pi_interact; AUTO picks per system: the tuner's
  * cached choice for its class if there is one and it has 2^18 particles or
- * more, else the static rule.  Sum(n) and the total cell count must stay
+ * more, the stream below 2^15 particles from 6 per cell, else the static rule.  Sum(n) and the total cell count must stay
  * below 2^31.  Errors as pi_bin / pi_interact; device errors surface through
  * pi_batch_sync.
  */

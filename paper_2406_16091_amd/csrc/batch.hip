@@ -2,13 +2,12 @@
 // of Sec. 2 applied to a set of systems at once).  The systems' particles are
 // concatenated; one radix sort orders them by global cell id (system cell
 // base + local cell), which keeps every system's particles contiguous and in
-// system order.  Each system gets its own sweep organisation (the tuner's
-// choice for its size and occupancy or the static rule, or the caller's explicit
-// one); systems
-// with the same organisation share one work-list launch, so a batch costs at
-// most one sweep launch per organisation.  The whole sequence is captured
-// once into a hipGraph per batch layout (systems, pointers, options) and
-// replayed afterwards with a single launch.
+// system order.  Each system gets its own sweep organisation (the tuner's choice
+// for its size and occupancy or the static rule, or the caller's explicit one);
+// systems with the same organisation share one work-list launch, so a batch costs
+// one sweep launch per organisation, and one dense pass and one reduction of the
+// invariants for all.  The whole sequence is captured once into a hipGraph per batch
+// layout (systems, pointers, options) and replayed afterwards with a single launch.
 #include <stdlib.h>
 #include <string.h>
 

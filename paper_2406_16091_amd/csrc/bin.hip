@@ -47,7 +47,7 @@ constexpr int kWideBits = 9;
 #ifndef PI_SCATTER_BLOCK
 #define PI_SCATTER_BLOCK 512
 #endif
-constexpr int kSBlock = PI_SCATTER_BLOCK;     // scatter threads per tile (256, 512 or 1024)
+constexpr int kSBlock = PI_SCATTER_BLOCK;     // scatter threads per tile (512 or 1024: one per digit at least)
 constexpr int kSItems = kSortTile / kSBlock;  // keys per thread
 constexpr int kFewTiles = 16;                 // most tiles that sum the digit counts themselves
 static_assert(kSBlock >= 1 << kWideBits && kSBlock <= 1024 && kSortTile % kSBlock == 0, "scatter block size");
@@ -1127,7 +1127,7 @@ pi_status pi_bin_systems(pi_ctx *ctx, pi_cells *cells, const float *x, const flo
             else PI_LAUNCH(ctx, "k_bucket_sort", k_bucket_sort<false>, grid, block, 0, stream, a);
         } else {
             // the per-wavefront maxima go to the histogram buffer, free after
-            // the last pass (256 entries per 4096 particles, one per 256 needed)
+            // the last pass (512 entries per 4096 particles, one per 256 needed)
             const int64_t waves = (n + kRunIds - 1) / kRunIds;
             PI_LAUNCH(ctx, "k_cell_ranges", k_cell_ranges, dim3(nblocks(waves * 64, kBlock)), dim3(kBlock), 0, stream,
                       (int32_t)n, (int32_t)nc, (const uint32_t *)ids, cells->counts, cells->offsets, cells->hist);

@@ -31,8 +31,8 @@ struct KernelConst {
 // its earlier course from there (with the FP64 forms below, G differed by up to
 // 1.5e-3 of its mean size after eight steps of 2^24 particles): the time steps
 // keep their arithmetic, so that a simulation can be taken up and checked against
-// earlier runs bit for bit.  In the sub-box tiles at 1 per cell it costs nothing:
-// four steps and a read-back take 8.11 ms either way.
+// earlier runs bit for bit.  In the sub-box tiles at 1 per cell it costs little: 0.79 ms
+// of a step of 2^24 particles, 0.78 with the FP64 forms.
 constexpr int kPrecStep = 3, kPrecStep64 = 4;
 constexpr bool step_precision(int prec) { return prec >= kPrecStep; }
 

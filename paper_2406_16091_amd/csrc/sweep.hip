@@ -285,22 +285,23 @@ __device__ __forceinline__ void in_register(uint32_t &v)
 // order, so the outputs are bitwise those of the no-LDS walk, also off the
 // lattice.  A ring slot is reused once no lane has a mask of its chunk left.
 //
-// What bounds it is VALU issue, at about 80 instructions per round, and the
+// What bounds it is VALU issue, at about 65 instructions per round, and the
 // number of rounds: with a ring of four chunks the lanes stay within four chunks
 // of each other, and at 64 per cell a wavefront takes about 480 rounds for 268
 // pairs per lane.  A longer ring takes fewer rounds but leaves too few wavefronts
 // per SIMD to hide the LDS latency (RING, Q = 4, 2: 29 KB, five workgroups per
-// CU): 64 per cell 2.34 ms with (4, 2), 2.47 with (4, 4), 2.93 with (2, 2), 2.98
-// with (8, 4); loading each lane's next pair a round ahead cost more registers
-// and copies than it saved (2.61).  Sweep times, no-LDS walk and this: clustered
-// 2^23 3.29 and 2.25 ms, 2^21 at 64 per cell 3.08 and 2.33 ms (plain sums 2.48
-// and 2.02), 24 per cell 1.65 and 1.15 ms; clustered 3e4 0.43 and 0.19 ms.
+// CU): 64 per cell, as this was chosen, 2.34 ms with (4, 2), 2.47 with (4, 4), 2.93
+// with (2, 2), 2.98 with (8, 4); loading each lane's next pair a round ahead cost more
+// registers and copies than it saved (2.61).  Sweep times, no-LDS walk and this:
+// clustered 2^23 4.04 and 2.58 ms, 2^21 at 64 per cell 3.14 and 2.20 ms (plain sums
+// 2.47 and 1.93), 24 per cell in 48^3 cells 1.70 and 1.10 ms; clustered 3e4 0.40 and
+// 0.19 ms.
+constexpr int kStreamQ = 2, kStreamRing = 4;
+
 // Per wavefront: the ring of staged chunks (cell-relative position and weight, and
 // the cell along X from the group's first; the entry past it holds zeros, for lanes
 // without work), each chunk's row shift, the operand of the chunk being tested, and
 // each lane's masks.
-constexpr int kStreamQ = 2, kStreamRing = 4;
-
 template <int Q, int RING>
 struct StreamLds {
     static_assert((Q & (Q - 1)) == 0 && Q <= 4, "a lane's chunk numbers are four bytes of one word");
@@ -904,8 +905,8 @@ __global__ __launch_bounds__(kBlock) void k_sweep_pencil(SweepArgs a, int32_t nt
 // the pairs do not).  A round is straight code; lanes without work add zeros.
 //
 // Measured (sweep kernel): 2^24 particles at 1 per cell 1.17 ms with per-lane
-// tests and pair queues, 0.76 ms with this (6x6x6); at 8 per cell 4.35 ms with
-// the no-LDS walk, 2.5 ms with this (3x3x3).  What bounds it is VALU issue: at 1
+// tests and pair queues, 0.78 ms with this (6x6x6; 7x7x5 0.79); at 8 per cell 4.37 ms
+// with the no-LDS walk, 2.41 ms with this (3x3x3).  What bounds it is VALU issue: at 1
 // per cell about 6,000 cycles per wavefront, 45% in the evaluation rounds (9.7
 // of them, 4.2 pairs per lane), 35% in the chunks, 20% in the set-up.  Matrix
 // and vector instructions of different wavefronts overlap only in part here, so
@@ -2096,10 +2097,10 @@ bool halo_fits(int id, double ppc)
 // 5x4x4 to 3.3, 5x4x3 to 4.1, 4x4x3 to 5.3, 4x3x3 to 6.8, 3x3x3 to 9.6, 3x3x2 to
 // 12, 3x2x2 to 15, then the stream.  Sweep times on uniform systems of 80^3 or
 // 48^3 cells, the rule's pick against the no-LDS walk and the next best tile:
-// 2 per cell 83 us (no LDS 119, 5x4x4 94), 3 139 (212, 4x4x4 151), 4 212 (328,
-// 4x4x4 224), 6 108 (174, 4x4x2 110), 8 153 (265, 4x4x2 175), 12 296 (510,
-// 3x2x2 360); the stream against no LDS at 24 per cell 1154 us (1651), 32 1924
-// (2743).
+// 2 per cell 88 us (no LDS 121, 5x4x4 97), 3 148 (222, 4x4x4 157), 4 222 (346,
+// 4x4x4 229), 6 114 (181, 4x4x2 115), 8 157 (279, 4x4x2 177), 12 302 (535,
+// 3x2x2 357); the stream against no LDS at 24 per cell 1098 us (1695), 32 1827
+// (2784).
 const int kStaticTiles[] = {5, 18, 19, 20, 21, 22, 23, 24, 25};
 
 int pick_tile_default(double ppc)
@@ -2316,12 +2317,11 @@ uint64_t tune_key(int prec, int64_t n, double ppc, bool batch)
     return (uint64_t)tune_precision(prec) + 4ull * (uint64_t)kn + 256ull * (uint64_t)kp + (batch ? (1ull << 30) : 0ull);
 }
 
-// Time every compiled organisation on this system (the fastest of up to
-// three runs after a first one, with
-// the invariant partials when the call computes them, since they change the
-// ranking: at 1 per cell the 7x7x5 tile is 5% faster than 6x6x6 without
-// them and 5% slower with them) and return the fastest; the outputs and
-// partial records in `a` are overwritten.  The static default is timed first and a later organisation
+// Time every compiled organisation on this system (the fastest of up to three runs
+// after a first one, with the invariant partials when the call computes them, since
+// they change the ranking: 2^24 at 1 per cell, 6x6x6 and 7x7x5, 776 and 785 us with
+// them, 746 and 733 without) and return the fastest; the outputs and partial records
+// in `a` are overwritten.  The static default is timed first and a later organisation
 // displaces the current best only when it is faster by more than 5%, so that
 // near-ties (within run-to-run noise) resolve the same way every time.
 // Organisations that cannot win at mean occupancy ppc and are not timed: the
