@@ -201,11 +201,9 @@ extern "C" pi_status pi_ctx_create(int32_t device, pi_ctx **out)
     c->timing_on = 0;
     c->timing = new (std::nothrow) pi_timing();
     c->tuner = new (std::nothrow) pi_tuner();
-    c->sides = new (std::nothrow) pi_side_pool();
-    if (!c->timing || !c->tuner || !c->sides) {
+    if (!c->timing || !c->tuner) {
         delete c->timing;
         delete c->tuner;
-        delete c->sides;
         free(c);
         return PI_ENOMEM;
     }
@@ -213,7 +211,6 @@ extern "C" pi_status pi_ctx_create(int32_t device, pi_ctx **out)
     if (ss != PI_OK) {
         delete c->timing;
         delete c->tuner;
-        delete c->sides;
         free(c);
         return ss;
     }
@@ -236,9 +233,6 @@ extern "C" pi_status pi_ctx_destroy(pi_ctx *ctx)
         delete ctx->timing;
     }
     delete ctx->tuner;
-    if (ctx->sides)
-        for (int i = 0; i < ctx->sides->count; ++i) pi_side_destroy(ctx->sides->idle[i]);
-    delete ctx->sides;
     free(ctx);
     return PI_OK;
 }

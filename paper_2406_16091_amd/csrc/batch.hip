@@ -8,7 +8,6 @@
 // one sweep launch per organisation, and one dense pass and one reduction of the
 // invariants for all.  The whole sequence is captured once into a hipGraph per batch
 // layout (systems, pointers, options) and replayed afterwards with a single launch.
-#include <stdlib.h>
 #include <string.h>
 
 #include <algorithm>
@@ -49,7 +48,11 @@ struct pi_batch {
     bool direct;       // launch the sequence directly instead of capturing it
     bool layout_valid; // direct: the tables hold the layout of `sig`
     hipStream_t graph_stream;
-    pi_side *side;     // for the fork of the sweep groups (null until needed)
+    // side streams and events that fork the sweep groups off the binning
+    // and join them back (default priority, created on first use)
+    std::vector<hipStream_t> side;
+    std::vector<hipEvent_t> done;
+    hipEvent_t binned;
 };
 
 extern "C" pi_status pi_batch_create(pi_ctx *ctx, pi_batch **out)
@@ -89,16 +92,6 @@ pi_cells *pi_batch_cells(pi_batch *b)
     return b->cells;
 }
 
-void pi_side_destroy(pi_side *s)
-{
-    for (int i = 0; i < kSideMax; ++i) {
-        if (s->stream[i]) (void)hipStreamDestroy(s->stream[i]);
-        if (s->done[i]) (void)hipEventDestroy(s->done[i]);
-    }
-    if (s->binned) (void)hipEventDestroy(s->binned);
-    free(s);
-}
-
 extern "C" pi_status pi_batch_destroy(pi_batch *b)
 {
     if (!b) return PI_EINVAL;
@@ -109,13 +102,10 @@ extern "C" pi_status pi_batch_destroy(pi_batch *b)
     if (b->d_kcs) (void)hipFree(b->d_kcs);
     if (b->d_ovf) (void)hipFree(b->d_ovf);
     if (b->d_hint) (void)hipFree(b->d_hint);
-    pi_cells_destroy(b->cells); // (waits for the object's stream, into which the side streams are joined)
-    if (b->side) {
-        pi_side_pool *pool = b->ctx->sides;
-        std::lock_guard<std::mutex> g(pool->mu);
-        if (pool->count < kSideIdle) pool->idle[pool->count++] = b->side;
-        else pi_side_destroy(b->side);
-    }
+    for (hipStream_t st : b->side) (void)hipStreamDestroy(st);
+    for (hipEvent_t e : b->done) (void)hipEventDestroy(e);
+    if (b->binned) (void)hipEventDestroy(b->binned);
+    pi_cells_destroy(b->cells);
     delete b;
     return PI_OK;
 }
@@ -133,28 +123,20 @@ void append(std::vector<unsigned char> &v, const void *p, size_t n)
 // to 0.3 ms (512 systems in six groups: first run 5.7 ms with a stream per group
 // and 5.2 with four chains, the next ones 3.23 and 3.21).
 constexpr size_t kLanes = 4;
-static_assert(kLanes <= kSideMax + 1, "a side stream for every chain but the first");
 
-// The batch's side streams and events for the fork of launch_all (taken or created
-// outside any graph capture).
+// Side streams and events for the fork of launch_all (created outside any
+// graph capture).
 pi_status ensure_side(pi_batch *b)
 {
-    const int need = (int)std::min(b->groups.size(), kLanes) - 1;
-    if (need < 1) return PI_OK;
-    if (!b->side) {
-        pi_side_pool *pool = b->ctx->sides;
-        std::lock_guard<std::mutex> g(pool->mu);
-        if (pool->count > 0) b->side = pool->idle[--pool->count];
-    }
-    if (!b->side) b->side = (pi_side *)calloc(1, sizeof(pi_side));
-    pi_side *s = b->side;
-    if (!s) return PI_ENOMEM;
-    if (!s->binned) PI_CHECK_HIP(hipEventCreateWithFlags(&s->binned, hipEventDisableTiming));
-    while (s->count < need) {
-        const int i = s->count;
-        if (!s->done[i]) PI_CHECK_HIP(hipEventCreateWithFlags(&s->done[i], hipEventDisableTiming));
-        PI_CHECK_HIP(hipStreamCreateWithFlags(&s->stream[i], hipStreamNonBlocking));
-        ++s->count;
+    const size_t ng = std::min(b->groups.size(), kLanes);
+    if (!b->binned) PI_CHECK_HIP(hipEventCreateWithFlags(&b->binned, hipEventDisableTiming));
+    while (b->side.size() + 1 < ng) {
+        hipStream_t sst = nullptr;
+        PI_CHECK_HIP(hipStreamCreateWithFlags(&sst, hipStreamNonBlocking));
+        b->side.push_back(sst);
+        hipEvent_t ev = nullptr;
+        PI_CHECK_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+        b->done.push_back(ev);
     }
     return PI_OK;
 }
@@ -177,24 +159,24 @@ pi_status launch_all(pi_batch *b, const float *x, const float *y, const float *z
     const size_t lanes = std::min(ng, kLanes);
     const bool fork = stream != nullptr && ng > 1;
     if (fork) {
-        if (!b->side || b->side->count + 1 < (int)lanes) return PI_EINVAL; // ensure_side() not called
-        PI_CHECK_HIP(hipEventRecord(b->side->binned, stream));
+        if (!b->binned || b->side.size() < lanes - 1) return PI_EINVAL; // ensure_side() not called
+        PI_CHECK_HIP(hipEventRecord(b->binned, stream));
     }
     for (size_t i = 0; i < ng; ++i) {
         const BatchGroup &g = b->groups[i];
         hipStream_t gs = stream;
         const size_t lane = i % lanes;
         if (fork && lane > 0) {
-            gs = b->side->stream[lane - 1];
-            if (i < lanes) PI_CHECK_HIP(hipStreamWaitEvent(gs, b->side->binned, 0));
+            gs = b->side[lane - 1];
+            if (i < lanes) PI_CHECK_HIP(hipStreamWaitEvent(gs, b->binned, 0));
         }
         st = pi_sweep_batch(b->ctx, b->cells, g.count, b->d_sweep + g.first, b->d_kcs + g.first,
                             b->d_ovf + g.first, g.blocks, g.part_base, g.tile, o, rho, gx, gy, gz, count, gs);
         if (st != PI_OK) return st;
-        if (fork && lane > 0 && i + lanes >= ng) PI_CHECK_HIP(hipEventRecord(b->side->done[lane - 1], gs));
+        if (fork && lane > 0 && i + lanes >= ng) PI_CHECK_HIP(hipEventRecord(b->done[lane - 1], gs));
     }
     if (fork)
-        for (size_t i = 1; i < lanes; ++i) PI_CHECK_HIP(hipStreamWaitEvent(stream, b->side->done[i - 1], 0));
+        for (size_t i = 1; i < lanes; ++i) PI_CHECK_HIP(hipStreamWaitEvent(stream, b->done[i - 1], 0));
     return pi_sweep_batch_end(b->ctx, b->cells, b->nsys, b->d_sweep, b->d_kcs, b->d_ovf, b->sweep_blocks,
                               b->dense_blocks, o, rho, gx, gy, gz, count, inv, stream);
 }

@@ -32,26 +32,6 @@ struct pi_tuner {
     int mode = 1;                   // PI_TUNE_STATIC / PI_TUNE_TIMED
 };
 
-// Side streams and events that fork a batch's sweep groups off its binning and join
-// them back (default priority, created on first use).  A batch object keeps a set
-// while it lives; destroyed, it leaves the set to the context's next one (a stream
-// with its event costs 0.2 to 0.3 ms).
-constexpr int kSideMax = 3;
-struct pi_side {
-    int count;
-    hipStream_t stream[kSideMax];
-    hipEvent_t done[kSideMax];
-    hipEvent_t binned;
-};
-
-constexpr int kSideIdle = 16; // most sets kept for later objects
-struct pi_side_pool {
-    std::mutex mu;
-    int count = 0;
-    pi_side *idle[kSideIdle];
-};
-void pi_side_destroy(pi_side *s);
-
 struct pi_ctx {
     int device;
     int num_cu;
@@ -60,7 +40,6 @@ struct pi_ctx {
     volatile int timing_on;
     pi_timing *timing;
     pi_tuner *tuner;
-    pi_side_pool *sides;
     void *scratch; // this device's copy of the fixed sweep scratch (sweep.hip)
 };
 
