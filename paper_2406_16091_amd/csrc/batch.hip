@@ -118,14 +118,17 @@ void append(std::vector<unsigned char> &v, const void *p, size_t n)
     v.insert(v.end(), c, c + n);
 }
 
-// Chains of sweep groups that run side by side: a process has four hardware
-// queues, and every further stream with its event costs a batch's first run 0.2
-// to 0.3 ms (512 systems in six groups: first run 5.7 ms with a stream per group
-// and 5.2 with four chains, the next ones 3.23 and 3.21).
-constexpr size_t kLanes = 4;
+// Chains of sweep groups that run side by side.  A second one fills what a small group
+// leaves idle; more cost a stream each at an object's first run and branches at every
+// launch of the graph.  Batches of 4, 49, 16, 150 and 512 systems of 1 to 4 per cell,
+// two and four chains: 79 and 108, 98 and 131, 119 and 156, 405 and 437, 2910 and
+// 3020 us; first runs of 4, 49 and 16: 2.1 and 2.4, 2.6 and 3.5, 3.5 and 4.8 ms.  100
+// systems in blobs with one, two and four chains 1.84, 1.46 and 1.29 ms, 64 of 8 to 14
+// per cell 723, 603 and 625 us.
+constexpr size_t kLanes = 2;
 
-// Side streams and events for the fork of launch_all (created outside any
-// graph capture).
+// Side stream and events for the fork of launch_all (created outside any graph
+// capture).
 pi_status ensure_side(pi_batch *b)
 {
     const size_t ng = std::min(b->groups.size(), kLanes);
@@ -153,11 +156,10 @@ pi_status launch_all(pi_batch *b, const float *x, const float *y, const float *z
     // The groups write disjoint outputs and partial records, so on a real
     // stream they run side by side: in up to kLanes chains, the first on
     // `stream`, the others on side streams forked after the binning and joined
-    // back (small groups then fill the GPU together instead of one after
-    // another).  The null stream launches them in order.
+    // back.  The null stream launches them in order.
     const size_t ng = b->groups.size();
     const size_t lanes = std::min(ng, kLanes);
-    const bool fork = stream != nullptr && ng > 1;
+    const bool fork = stream != nullptr && lanes > 1;
     if (fork) {
         if (!b->binned || b->side.size() < lanes - 1) return PI_EINVAL; // ensure_side() not called
         PI_CHECK_HIP(hipEventRecord(b->binned, stream));
