@@ -42,6 +42,10 @@ struct SweepArgs {
     uint32_t *ovf;
     uint32_t epoch;
     uint32_t *host_epoch; // host memory, not read by the kernels
+    // sub-boxes of one system: unless null, the densest cell's count (M_C), and the
+    // most it may be; above that every tile is left to the dense pass
+    const int32_t *mc;
+    int32_t mc_most;
     // no-LDS walk: > 0 skips the targets of cells holding at least this many
     // particles (the cell-SM pass takes them)
     int32_t dense_min;
@@ -1007,7 +1011,8 @@ __global__ __launch_bounds__(kBlock, CAP <= 768 ? 6 : 4) void k_sweep_tile(Sweep
     // across the system.  (Two rounds of targets are a full halo's in the shapes that
     // the static rule picks; 2^13 particles of which nine in ten lie in 8 blobs,
     // 8 per cell on average: sweep 867 us without the second limit, 641 with it.)
-    const bool overflow = total > CAP || ntarget > 2 * kBlock;
+    // Or the caller's limit on the densest cell says that all are left to it.
+    const bool overflow = total > CAP || ntarget > 2 * kBlock || (!BATCH && a.mc && *a.mc > a.mc_most);
     if (tid == 0) a.tflag[lb] = overflow ? 1 : 0;
     if (overflow) {
         if (tid == 0) a.ovf[own] = a.epoch;
@@ -2110,6 +2115,24 @@ int pick_tile_default(double ppc)
     return kOrgStream;
 }
 
+// AUTO of one system: the count of the densest cell above which its sub-boxes leave
+// everything to the dense pass (0: no limit).  In a small launch the sweep lasts as
+// long as its longest chain, a wavefront in a dense core; cores in the tiles and in the
+// dense pass make two, one after the other.  The host knows the mean occupancy alone,
+// so the tiles decide, by M_C.  Sweeps with nine in ten particles in 8 or 64 blobs, by
+// tiles and dense pass, by the stream (which the dense pass then is, behind 8 us of
+// tiles) and without LDS: 2^13 at 6 per cell, M_C 287, 588, 269, 445 us; 2^14 at 10, M_C
+// 103, 230, 123, 199; 2^15 at 10, M_C 138, 277, 142, 306; 2^16 at 8, M_C 143, 336, 163,
+// 357; but 2^13 at 6, M_C 68, 74, 95, 138.  Below the line tiles gain or are equal: 2^14
+// at 10, M_C 50, 70, 74, 129; 2^15 at 10, M_C 62, 79, 80, 152; uniform 26 to 44, 46 to 62,
+// 61 to 100.  From 2^17 tiles and dense pass took no longer than the walk wherever
+// measured.  Below 6 per cell tiles more often hold such cores: 2^13 at 5 per cell, M_C 57,
+// 85, 96, 131.
+int32_t clustered_from(int64_t n, double ppc)
+{
+    return n <= ((int64_t)1 << 16) && ppc >= 6.0 ? (int32_t)fmin(8.0 * ppc + 16.0, 1e9) : 0;
+}
+
 } // namespace
 
 bool pi_tile_shape(int tile_id, int *tx, int *ty, int *tz)
@@ -2594,6 +2617,8 @@ pi_status pi_interact_run(pi_ctx *ctx, const pi_cells *cells, const pi_interact_
         pi_status ts = tuned_tile(ctx, a, o.precision, n, ppc, want_inv, stream, &tile);
         if (ts != PI_OK) return ts;
     }
+    if (o.sweep == PI_SWEEP_AUTO) a.mc_most = clustered_from(n, ppc);
+    if (a.mc_most > 0) a.mc = cells->max_per_cell;
     launch_sweep_prec<false>(ctx, o.precision, want_inv, tile, a, stream, nblk);
     if (want_inv) pi_reduce_partials(ctx, a.partials, nblk, inv, stream);
     PI_CHECK_HIP(hipGetLastError());
